@@ -6,25 +6,29 @@
 //   C[m, n] = sum_k A(m, k) B(n, k), bf16 operands, fp32 accumulation.
 //
 // Design (CDNA4):
-//  * 256 x 256 x 64 block tile (256 x 128 when the grid would not fill the
-//    chip), 4 wavefronts in a 2 x 2 grid; each wave owns a 128 x 128 (or
-//    128 x 64) sub-tile of v_mfma_f32_32x32x16_bf16 accumulators held in AGPRs.
-//  * LDS holds both operand tiles K-contiguous, 64 bf16 (128 bytes) per row,
-//    two stages.  The eight 16-byte chunks of a row are XOR-swizzled with the
-//    row index (chunk c of row r sits at position c ^ ((r >> 1) & 7)), so the
-//    16 lanes of a fragment read that the LDS serves together hit distinct
-//    banks without padding.
-//  * K-contiguous operands go HBM -> LDS directly with buffer_load ... lds
-//    (no VGPR staging, no LDS store instructions); out-of-range rows and the K
-//    tail are given an out-of-range buffer offset and read as zeros.
-//    M/N-contiguous operands (input-gradient and weight-gradient products) are
-//    loaded as 8 x 8 blocks into VGPRs, transposed with v_perm and stored.
-//  * Per K-tile: one barrier, then all MFMA fragments of the tile are read
-//    into registers, then the next tile's loads are issued into the other
-//    stage, then the 64 MFMAs run while those loads are in flight.
+//  * BT x BT x 64 block tile, BT = 128 or 64 (256 x 256 tiles are gemm256.hip),
+//    4 wavefronts in a 2 x 2 grid, each with a BT/2 x BT/2 sub-tile of
+//    v_mfma_f32_32x32x16_bf16 accumulators.  Two workgroups share a CU (64 KB
+//    of LDS each), so one's prologue, barriers and epilogue overlap the
+//    other's MFMAs: two stages of 128 x 128, or four of 64 x 64, which run
+//    three K-tiles ahead where a grid of few tiles is bound by latency
+//    (128 x 4096 x 4096: 32 us with two stages, 15.5 with four).
+//  * What bounds it: a 64 x 64 wave tile reads its operands from LDS at the
+//    LDS's full 128 bytes per clock when the MFMAs run at full rate, and a
+//    128 x 128 tile needs 64 bytes per clock from L2, so long products stop at
+//    about 1.0 PFLOP/s (8192 x 1024 x 4096: 68 us); the 256 x 256 kernel's ceiling
+//    is higher, its grid coarser (gemm_plan below).
+//  * Operands go HBM -> LDS directly with buffer_load ... lds (no VGPR
+//    staging); out-of-range rows and the K tail are given an out-of-range buffer
+//    offset and read as zeros.  K-contiguous tiles lie [row][k] in LDS,
+//    M/N-contiguous ones [k][row] and are read with the transposing LDS read
+//    (2048 x 2048 x 2048, both M/N-contiguous: 32 us; staged through registers and
+//    transposed with byte permutes 65 us; K-contiguous 31 us).
+//  * Unaligned operands are gathered with scalar loads (gemm_kernel_simple).
 //  * Workgroups are renumbered so that consecutive tiles land on the same XCD
 //    (the dispatcher deals workgroups round-robin over the 8 XCDs), then
 //    ordered in groups of 8 tile-rows for L2 reuse of the B tiles.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -47,11 +51,6 @@ constexpr uint32_t OOB = 0x80000000u;  // buffer offset that reads as zero
 __device__ __forceinline__ int swz(int row) { return (row >> 1) & 7; }
 __device__ __forceinline__ int sw(int row, int chunk) { return row * BK + ((chunk ^ swz(row)) << 3); }
 
-__device__ __forceinline__ u32x4 load_vec_guarded(const bf16* g, bool ok) {
-  u32x4 z = {0u, 0u, 0u, 0u};
-  return ok ? *reinterpret_cast<const u32x4*>(g) : z;
-}
-
 // Scalar gather of up to 8 consecutive bf16, zero beyond `n_ok`.
 __device__ __forceinline__ u32x4 load_scalar8(const bf16* g, int n_ok) {
   uint16_t h[8];
@@ -65,45 +64,6 @@ __device__ __forceinline__ u32x4 load_scalar8(const bf16* g, int n_ok) {
   r[3] = h[6] | ((uint32_t)h[7] << 16);
   return r;
 }
-
-// ---- K-contiguous operand (row r, k) at G[r * ld + k], straight to LDS.
-// Instruction i of wave w fills rows (i*4 + w)*8 .. +7 (1 KB); lane L writes
-// LDS chunk position L % 8 of row L / 8, which holds logical chunk
-// (L % 8) ^ swz(row).
-template <int ROWS>
-struct KDma {
-  static constexpr int N = 0;  // no staging registers
-  static constexpr int NI = ROWS * KV / NT;
-  // Byte offsets of this lane's chunks relative to (tile row 0, k = 0);
-  // rows past the matrix get the out-of-range offset once, up front.
-  uint32_t off[NI];
-  __device__ __forceinline__ void init(long ld, int nrows, int wave) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int row = (i * 4 + wave) * 8 + (lane >> 3);
-      const int c = (lane & 7) ^ swz(row);
-      off[i] = (row < nrows) ? (uint32_t)(((long)row * ld + c * 8) * 2) : OOB;
-    }
-  }
-  // k0: first column of the K-tile; `tail` = the tile crosses K (then the
-  // chunks at or past K are redirected out of range).
-  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, int k0, int K, bool tail, bf16* S,
-                                       int wave) const {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      uint32_t o = off[i];
-      if (tail) {
-        const int row = (i * 4 + wave) * 8 + (lane >> 3);
-        const int c = (lane & 7) ^ swz(row);
-        if (k0 + c * 8 >= K) o = OOB;
-      }
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(S + (i * 4 + wave) * 8 * BK), 16, o,
-                                               k0 * 2, 0, 0);
-    }
-  }
-};
 
 // ---- K-contiguous operand through registers (scalar fallback path).
 template <int ROWS>
@@ -138,12 +98,8 @@ struct MNReg {
   static constexpr int NB = (ROWS / 8) * KV;          // 8 x 8 blocks per tile
   static constexpr int NPT = (NB + NT - 1) / NT;      // blocks per thread
   static constexpr int N = 8 * NPT;
-  template <bool VEC>
   __device__ __forceinline__ static void load(const bf16* G, long ld, int r0, int nrows, int k0,
                                               int K, u32x4* regs) {
-    // buffer resource rebased at (k0, r0): out-of-range blocks read as zeros
-    __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(G + (long)k0 * ld + r0), (short)0, 0x7FFFFFFF, 0x00020000);
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {
       int b = threadIdx.x + j * NT;
@@ -153,13 +109,8 @@ struct MNReg {
 #pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         int gk = k0 + kb * 8 + kk;
-        if (VEC) {
-          const uint32_t off = (gk < K && gr < nrows) ? (uint32_t)((((long)(kb * 8 + kk)) * ld + rb * 8) * 2) : OOB;
-          regs[8 * j + kk] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
-        } else {
-          const bf16* src = G + (long)gk * ld + gr;
-          regs[8 * j + kk] = load_scalar8(src, (gk < K) ? max(0, min(8, nrows - gr)) : 0);
-        }
+        const bf16* src = G + (long)gk * ld + gr;
+        regs[8 * j + kk] = load_scalar8(src, (gk < K) ? max(0, min(8, nrows - gr)) : 0);
       }
     }
   }
@@ -186,27 +137,14 @@ struct MNReg {
   }
 };
 
-// Operand staging modes.
-enum { OP_DMA = 0, OP_KREG = 1, OP_MN = 2 };
-
-template <int MODE, int ROWS, bool VEC>
+template <int LAY, int ROWS>
 struct Operand {
-  static constexpr int N = MODE == OP_DMA ? 1 : (MODE == OP_KREG ? KReg<ROWS>::N : MNReg<ROWS>::N);
-  u32x4 regs[N];
-  KDma<ROWS> dma;
-  __device__ __forceinline__ void init(long ld, int nrows_from_r0, int wave) {
-    if (MODE == OP_DMA) dma.init(ld, nrows_from_r0, wave);
+  using Reg = std::conditional_t<LAY == LAY_MN, MNReg<ROWS>, KReg<ROWS>>;
+  u32x4 regs[Reg::N];
+  __device__ __forceinline__ void fetch(const bf16* G, long ld, int r0, int nrows, int k0, int K) {
+    Reg::load(G, ld, r0, nrows, k0, K, regs);
   }
-  __device__ __forceinline__ void fetch(const bf16* G, __amdgpu_buffer_rsrc_t rs, long ld, int r0,
-                                        int nrows, int k0, int K, bf16* S, int wave) {
-    if (MODE == OP_DMA) dma.issue(rs, k0, K, k0 + BK > K, S, wave);
-    else if (MODE == OP_KREG) KReg<ROWS>::load(G, ld, r0, nrows, k0, K, regs);
-    else MNReg<ROWS>::template load<VEC>(G, ld, r0, nrows, k0, K, regs);
-  }
-  __device__ __forceinline__ void commit(bf16* S) {
-    if (MODE == OP_KREG) KReg<ROWS>::store(S, regs);
-    else if (MODE == OP_MN) MNReg<ROWS>::store(S, regs);
-  }
+  __device__ __forceinline__ void commit(bf16* S) { Reg::store(S, regs); }
 };
 
 // One K-tile on stage `cur`: barrier (the tile has landed and no wave still
@@ -216,10 +154,8 @@ struct Operand {
 // the MFMAs of steps 1 to 3 while those loads are in flight.
 template <int TM, int TN, class OA, class OB>
 __device__ __forceinline__ void ktile(floatx16 (&acc)[TM][TN], OA& opA, OB& opB, const GemmArgs& p,
-                                      __amdgpu_buffer_rsrc_t rsA, __amdgpu_buffer_rsrc_t rsB,
-                                      int a_r0, int a_n, int b_r0, int b_n, const bf16* cur,
-                                      bf16* nxt, int kt, int nk, int BMr, int aoff, int boff,
-                                      int fhalf, int fsw, int wave) {
+                                      int m0, int n0, const bf16* cur, bf16* nxt, int kt, int nk,
+                                      int BMr, int aoff, int boff, int fhalf, int fsw) {
   __syncthreads();
   const bool more = kt + 1 < nk;
   const bf16* As = cur + aoff;
@@ -247,8 +183,8 @@ __device__ __forceinline__ void ktile(floatx16 (&acc)[TM][TN], OA& opA, OB& opB,
   SAT_RD(3);
   __builtin_amdgcn_sched_barrier(0);
   if (more) {
-    opA.fetch(p.A, rsA, p.lda, a_r0, a_n, (kt + 1) * BK, p.K, nxt, wave);
-    opB.fetch(p.B, rsB, p.ldb, b_r0, b_n, (kt + 1) * BK, p.K, nxt + BMr * BK, wave);
+    opA.fetch(p.A, p.lda, m0, p.M, (kt + 1) * BK, p.K);
+    opB.fetch(p.B, p.ldb, n0, p.N, (kt + 1) * BK, p.K);
   }
   __builtin_amdgcn_sched_barrier(0);
   SAT_MM(1);
@@ -263,361 +199,459 @@ __device__ __forceinline__ void ktile(floatx16 (&acc)[TM][TN], OA& opA, OB& opB,
 }
 
 // Epilogue shared by both main loops, staged through LDS one 32-row slab per
-// wave at a time: the accumulators (lane = column lane & 31, rows
-// 8*(r/4) + 4*(lane/32) + r%4) are written with compile-time indices, then
-// each row is read back so that one store instruction covers 64 consecutive
-// columns.  `smem` must hold at least 4 * 32 * (BN/2 + 4) floats.
-template <int BM, int BN, int EPI, int GE>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, floatx16 (&acc)[BM / 64][BN / 64],
-                                              bf16* smem, int m0, int n0, int wave, int lane) {
-  constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
+// wave at a time, each wave in its own region: the accumulators (lane = column
+// lane & 31, rows 8*(r/4) + 4*(lane/32) + r%4) are written with compile-time
+// indices, then each lane reads back four consecutive columns, so that an
+// output store is 16 (fp32) or 8 (bf16) bytes per lane where the rows are
+// aligned for it (`vec`) and one element otherwise.
+template <int BT, int EPI, int GE>
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, floatx16 (&acc)[BT / 64][BT / 64],
+                                              bf16* smem, int m0, int n0, int wave, int lane, bool vec) {
+  constexpr int WT = BT / 2, TT = WT / 32;
   const int M = p.M, N = p.N;
   const int wm = wave >> 1, wn = wave & 1;
-  constexpr int SP = WTN + 4;           // fp32 pitch of a slab row
-  constexpr int CPL = WTN / 64;         // columns per lane in the read phase
-  static_assert(4 * 32 * SP * 4 <= 2 * (BM + BN) * BK * 2, "epilogue slabs exceed the LDS tile space");
+  constexpr int SP = WT + 4;       // fp32 pitch of a slab row
+  constexpr int LR = WT / 4;       // lanes per row
+  constexpr int RP = 64 / LR;      // rows per pass
+  static_assert(4 * 32 * SP * 4 <= 2 * 2 * BT * BK * 2, "epilogue slabs exceed the LDS tile space");
   float* stage = reinterpret_cast<float*>(smem) + wave * 32 * SP;
-  const int colbase = n0 + wn * WTN;
-  float bias[CPL];
-  bool gel[CPL];
+  const int cl = 4 * (lane % LR);
+  const int col = n0 + wn * WT + cl;
+  const bool whole = vec && col + 3 < N;
+  floatx4 bias = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int c = 0; c < CPL; ++c) {
-    const int col = colbase + lane + 64 * c;
-    bias[c] = (p.bias != nullptr && col < N && col >= p.bias_col0) ? p.bias[col - p.bias_col0] : 0.f;
-    gel[c] = (EPI == EPI_BF16) && p.out2 != nullptr && col >= p.gelu_col0;
-  }
+  for (int e = 0; e < 4; ++e)
+    if (p.bias != nullptr && col + e < N && col + e >= p.bias_col0) bias[e] = p.bias[col + e - p.bias_col0];
+  const bool csum_on = EPI == EPI_DGELU_BF16 && p.colsum_part != nullptr;
+  __amdgpu_buffer_rsrc_t rsE;
+  if constexpr (EPI == EPI_RESID_F32)
+    rsE = __builtin_amdgcn_make_buffer_rsrc((void*)(p.resid + (long)m0 * p.ldr), (short)0, 0x7FFFFFFF, 0x00020000);
+  if constexpr (EPI == EPI_DGELU_BF16)
+    rsE = __builtin_amdgcn_make_buffer_rsrc((void*)(p.aux + (long)m0 * p.ldaux), (short)0, 0x7FFFFFFF, 0x00020000);
+  floatx4 csum = {0.f, 0.f, 0.f, 0.f};  // this lane's columns over its rows of the wave's WT
 #pragma unroll
-  for (int i = 0; i < TM; ++i) {
-    __syncthreads();
+  for (int i = 0; i < TT; ++i) {
+    const int rowbase = m0 + wm * WT + i * 32;
+    // residual / pre-activation loads of the whole slab first, in flight
+    // together (buffer loads: rows past M and ragged columns read as zeros)
+    u32x4 rv[EPI == EPI_RESID_F32 ? 32 / RP : 1];
+    u32x2 uv[EPI == EPI_DGELU_BF16 ? 32 / RP : 1];
+    if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_DGELU_BF16) {
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+      for (int q = 0; q < 32 / RP; ++q) {
+        const int row = rowbase + q * RP + lane / LR;
+        const bool ok = whole && row < M;
+        const long at = (long)(row - m0) * (EPI == EPI_RESID_F32 ? p.ldr * 4 : p.ldaux * 2) +
+                        col * (EPI == EPI_RESID_F32 ? 4 : 2);
+        if constexpr (EPI == EPI_RESID_F32)
+          rv[q] = __builtin_amdgcn_raw_buffer_load_b128(rsE, ok ? (uint32_t)at : OOB, 0, 0);
+        else
+          uv[q] = __builtin_amdgcn_raw_buffer_load_b64(rsE, ok ? (uint32_t)at : OOB, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < TT; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r)
         stage[(8 * (r >> 2) + 4 * (lane >> 5) + (r & 3)) * SP + j * 32 + (lane & 31)] = acc[i][j][r];
-    __syncthreads();
-    const int rowbase = m0 + wm * WTM + i * 32;
-    // unrolled by 8 so that the residual / pre-activation loads of 8 rows are
-    // in flight together instead of one round trip per row
-#pragma unroll 8
-    for (int rr = 0; rr < 32; ++rr) {
-      const long row = rowbase + rr;
+    wait_lgkm0();
 #pragma unroll
-      for (int c = 0; c < CPL; ++c) {
-        const int col = colbase + lane + 64 * c;
-        if (col >= N || row >= M) continue;
-        const float x = stage[rr * SP + lane + 64 * c] + bias[c];
-        const long o = row * p.ldo + col;
+    for (int q = 0; q < 32 / RP; ++q) {
+      const int rl = q * RP + lane / LR;
+      const long row = rowbase + rl;
+      if (row >= M || col >= N) continue;
+      const floatx4 x = *reinterpret_cast<const floatx4*>(stage + rl * SP + cl) + bias;
+      const long o = row * p.ldo + col;
+      if (whole) {
         if (EPI == EPI_F32) {
-          reinterpret_cast<float*>(p.out)[o] = x;
+          __builtin_nontemporal_store(x, reinterpret_cast<floatx4*>(reinterpret_cast<float*>(p.out) + o));
         } else if (EPI == EPI_RESID_F32) {
-          reinterpret_cast<float*>(p.out)[o] = p.resid[row * p.ldr + col] + x;
+          __builtin_nontemporal_store(floatx4(__builtin_bit_cast(floatx4, rv[EPI == EPI_RESID_F32 ? q : 0]) + x), reinterpret_cast<floatx4*>(reinterpret_cast<float*>(p.out) + o));
         } else if (EPI == EPI_BF16) {
-          reinterpret_cast<bf16*>(p.out)[o] = f2bf(x);
-          if (gel[c]) p.out2[row * p.ldo2 + (col - p.gelu_col0)] = f2bf(gelu_t<GE>(x));
-        } else {  // EPI_DGELU_BF16
-          const float u = bf2f(p.aux[row * p.ldaux + col]);
-          reinterpret_cast<bf16*>(p.out)[o] = f2bf(x * gelu_grad_t<GE>(u));
+          __builtin_nontemporal_store(bf16x4{f2bf(x[0]), f2bf(x[1]), f2bf(x[2]), f2bf(x[3])}, reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(p.out) + o));
+          if (p.out2 != nullptr && col >= p.gelu_col0)
+            *reinterpret_cast<bf16x4*>(p.out2 + row * p.ldo2 + (col - p.gelu_col0)) =
+                bf16x4{f2bf(gelu_t<GE>(x[0])), f2bf(gelu_t<GE>(x[1])), f2bf(gelu_t<GE>(x[2])),
+                       f2bf(gelu_t<GE>(x[3]))};
+        } else {
+          const bf16x4 u = __builtin_bit_cast(bf16x4, uv[EPI == EPI_DGELU_BF16 ? q : 0]);
+          bf16x4 y;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = f2bf(x[e] * gelu_grad_t<GE>(bf2f(u[e])));
+          __builtin_nontemporal_store(y, reinterpret_cast<bf16x4*>(reinterpret_cast<bf16*>(p.out) + o));
+          if (csum_on) csum += floatx4{bf2f(y[0]), bf2f(y[1]), bf2f(y[2]), bf2f(y[3])};
+        }
+        continue;
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = col + e;
+        if (c >= N) break;
+        if (EPI == EPI_F32) {
+          reinterpret_cast<float*>(p.out)[o + e] = x[e];
+        } else if (EPI == EPI_RESID_F32) {
+          reinterpret_cast<float*>(p.out)[o + e] = p.resid[row * p.ldr + c] + x[e];
+        } else if (EPI == EPI_BF16) {
+          reinterpret_cast<bf16*>(p.out)[o + e] = f2bf(x[e]);
+          if (p.out2 != nullptr && c >= p.gelu_col0)
+            p.out2[row * p.ldo2 + (c - p.gelu_col0)] = f2bf(gelu_t<GE>(x[e]));
+        } else {
+          const bf16 y = f2bf(x[e] * gelu_grad_t<GE>(bf2f(p.aux[row * p.ldaux + c])));
+          reinterpret_cast<bf16*>(p.out)[o + e] = y;
+          if (csum_on) csum[e] += bf2f(y);
         }
       }
     }
   }
+  if (csum_on && m0 + wm * WT < M) {
+    // the RP lane groups of a column, added in group order; one partial row per WT rows
+    wait_lgkm0();
+    *reinterpret_cast<floatx4*>(stage + (lane / LR) * WT + cl) = csum;
+    wait_lgkm0();
+    const int c = n0 + wn * WT + lane;
+    if (lane < WT && c < N) {
+      float v = stage[lane];
+#pragma unroll
+      for (int g = 1; g < RP; ++g) v += stage[g * WT + lane];
+      p.colsum_part[(long)((m0 + wm * WT) / WT) * N + c] = v;
+    }
+  }
 }
 
-// Block tile BM x BN x 64; 4 waves in a 2 x 2 grid, wave tile (BM/2) x (BN/2)
-// made of 32 x 32 MFMA tiles.
-template <int BM, int BN, int ALAY, int BLAY, int EPI, int GE, bool VEC>
-__global__ __launch_bounds__(NT) void gemm_kernel_simple(GemmArgs p) {
-  constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
-  constexpr int AMODE = ALAY == LAY_MN ? OP_MN : (VEC ? OP_DMA : OP_KREG);
-  constexpr int BMODE = BLAY == LAY_MN ? OP_MN : (VEC ? OP_DMA : OP_KREG);
-  constexpr int STAGE = (BM + BN) * BK;  // bf16 elements per stage
-  __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STAGE];
+// Whether the epilogue's 4-column vectors are aligned in every array it touches.
+template <int EPI>
+__device__ __forceinline__ bool epilogue_vec(const GemmArgs& p) {
+  auto al = [](const void* q, int b) { return (reinterpret_cast<uintptr_t>(q) & (b - 1)) == 0; };
+  bool ok = p.ldo % 4 == 0 && al(p.out, (EPI == EPI_F32 || EPI == EPI_RESID_F32) ? 16 : 8);
+  if (EPI == EPI_RESID_F32) ok = ok && p.ldr % 4 == 0 && al(p.resid, 16);
+  if (EPI == EPI_BF16 && p.out2 != nullptr)
+    ok = ok && p.ldo2 % 4 == 0 && p.gelu_col0 % 4 == 0 && al(p.out2, 8);
+  if (EPI == EPI_DGELU_BF16) ok = ok && p.ldaux % 4 == 0 && al(p.aux, 8);
+  return ok;
+}
 
-  const int M = p.M, N = p.N, K = p.K;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const int nwg = tiles_m * tiles_n;
+// This workgroup's tile, with workgroups renumbered so that each XCD walks a
+// contiguous range of the tile order and tiles ordered in groups of 8
+// tile-rows.  With split-K the grid is (slice, tile) pairs, slice-major: the
+// arguments are narrowed to the slice's K range and output block.
+template <int BT, int ALAY, int BLAY>
+__device__ __forceinline__ void tile_setup(GemmArgs& p, int& m0, int& n0) {
+  const int tiles_m = (p.M + BT - 1) / BT, tiles_n = (p.N + BT - 1) / BT;
+  const int nwg = gridDim.x;
   int bid = blockIdx.x;
   if ((nwg & 7) == 0) bid = (bid & 7) * (nwg >> 3) + (bid >> 3);
+  if (p.splitk > 1) {
+    const int split = bid / (tiles_m * tiles_n);
+    bid -= split * tiles_m * tiles_n;
+    const int kb = split * p.splitk_kc;
+    p.A += ALAY == LAY_K ? (long)kb : (long)kb * p.lda;
+    p.B += BLAY == LAY_K ? (long)kb : (long)kb * p.ldb;
+    p.K = min(p.splitk_kc, p.K - kb);
+    p.out = reinterpret_cast<float*>(p.out) + split * p.split_stride;
+  }
   constexpr int G = 8;
   const int per_group = G * tiles_n;
   const int group = bid / per_group;
   const int first_m = group * G;
   const int gsize = min(tiles_m - first_m, G);
   const int in_g = bid - group * per_group;
-  const int tile_m = first_m + in_g % gsize;
-  const int tile_n = in_g / gsize;
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
+  m0 = (first_m + in_g % gsize) * BT;
+  n0 = (in_g / gsize) * BT;
+}
+
+// Block tile BT x BT x 64; 4 waves in a 2 x 2 grid, wave tile (BT/2) x (BT/2)
+// made of 32 x 32 MFMA tiles.
+template <int BT, int ALAY, int BLAY, int EPI, int GE>
+__global__ __launch_bounds__(NT) void gemm_kernel_simple(GemmArgs p) {
+  constexpr int WT = BT / 2, TT = WT / 32;
+  constexpr int STAGE = 2 * BT * BK;  // bf16 elements per stage
+  __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STAGE];
+
+  int m0, n0;
+  tile_setup<BT, ALAY, BLAY>(p, m0, n0);
+  const int K = p.K;
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  // buffer resources rebased at the tile's first row (K-contiguous operands)
-  __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.A + (ALAY == LAY_K ? (long)m0 * p.lda : 0)), (short)0, 0x7FFFFFFF, 0x00020000);
-  __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.B + (BLAY == LAY_K ? (long)n0 * p.ldb : 0)), (short)0, 0x7FFFFFFF, 0x00020000);
-  const int a_r0 = (AMODE == OP_DMA) ? 0 : m0, a_n = (AMODE == OP_DMA) ? M - m0 : M;
-  const int b_r0 = (BMODE == OP_DMA) ? 0 : n0, b_n = (BMODE == OP_DMA) ? N - n0 : N;
+  Operand<ALAY, BT> opA;
+  Operand<BLAY, BT> opB;
 
-  Operand<AMODE, BM, VEC> opA;
-  Operand<BMODE, BN, VEC> opB;
-
-  floatx16 acc[TM][TN];
+  floatx16 acc[TT][TT];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TT; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TT; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int nk = (K + BK - 1) / BK;
-  opA.init(p.lda, M - m0, wave);
-  opB.init(p.ldb, N - n0, wave);
-  opA.fetch(p.A, rsA, p.lda, a_r0, a_n, 0, K, smem, wave);
-  opB.fetch(p.B, rsB, p.ldb, b_r0, b_n, 0, K, smem + BM * BK, wave);
+  opA.fetch(p.A, p.lda, m0, p.M, 0, K);
+  opB.fetch(p.B, p.ldb, n0, p.N, 0, K);
   opA.commit(smem);
-  opB.commit(smem + BM * BK);
+  opB.commit(smem + BT * BK);
 
   // fragment addressing: row (lane & 31) of each 32-row tile, logical chunk
   // 2 * ks + (lane >> 5), swizzled with swz(row) == swz(lane & 31)
   const int frow = lane & 31, fhalf = lane >> 5, fsw = swz(lane & 31);
-  const int aoff = (wm * WTM + frow) * BK, boff = (wn * WTN + frow) * BK;
+  const int aoff = (wm * WT + frow) * BK, boff = (wn * WT + frow) * BK;
   for (int kt = 0; kt < nk; ++kt) {
     bf16* cur = smem + (kt & 1) * STAGE;
     bf16* nxt = smem + ((kt + 1) & 1) * STAGE;
-    ktile<TM, TN>(acc, opA, opB, p, rsA, rsB, a_r0, a_n, b_r0, b_n, cur, nxt, kt, nk, BM, aoff,
-                  boff, fhalf, fsw, wave);
+    ktile<TT, TT>(acc, opA, opB, p, m0, n0, cur, nxt, kt, nk, BT, aoff, boff, fhalf, fsw);
   }
+  __syncthreads();
 
-  gemm_epilogue<BM, BN, EPI, GE>(p, acc, smem, m0, n0, wave, lane);
+  gemm_epilogue<BT, EPI, GE>(p, acc, smem, m0, n0, wave, lane, epilogue_vec<EPI>(p));
 }
 
 // ------------------------------------------------------------------------
-// Pipelined main loop (16-byte aligned operands).
+// Pipelined main loop (16-byte aligned operands), NS stages of one K-tile.
 //
-// Per K-tile k (stage k & 1): MFMAs of k-step 0, fragment reads of k-steps 2
+// Per K-tile k (stage k % NS): MFMAs of k-step 0, fragment reads of k-steps 2
 // and 3, MFMAs of steps 1 and 2, then [wait for this wave's copies of tile
 // k + 1, barrier], fragment reads of steps 0 and 1 of tile k + 1, the copies of
-// tile k + 2 into stage k & 1 (now free), and only then the MFMAs of step 3 of
-// tile k, so the matrix cores keep working across the barrier.  Waits are
-// explicit s_waitcnt and the barrier carries no memory fence: a fence would
+// tile k + NS into the stage that tile k just left, and only then the MFMAs of
+// step 3 of tile k, so the matrix cores keep working across the barrier.  Waits
+// are explicit s_waitcnt and the barrier carries no memory fence: a fence would
 // also wait for the copies that are meant to stay in flight.  The tile
 // stages are passed to the inlined helpers as __restrict__ pointers, which
 // tells the compiler that reads of one stage never wait on copies into the
-// other.
+// others.  Tiles past the last one copy zeros, so the wait counts are constant.
 
-// Operand of the pipelined loop: MODE OP_DMA (K-contiguous, straight to LDS)
-// or OP_MN (M/N-contiguous, through registers).
-template <int MODE, int ROWS>
-struct PipeOperand {
-  static constexpr int NREG = MODE == OP_MN ? MNReg<ROWS>::N : 1;
-  u32x4 regs[NREG];
-  KDma<ROWS> dma;
-  // loads issued per wave by one `load` (OP_MN) -- waves past the block
-  // count issue none
-  __device__ __forceinline__ static int mn_loads(int wave) {
-    if (MODE != OP_MN) return 0;
-    int n = 0;
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+__device__ __forceinline__ bf16x4 ds_read_tr(const lds_bf16x4* __restrict__ p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(const_cast<lds_bf16x4*>(p));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* p) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, 0x7FFFFFFF, 0x00020000);
+}
+
+// One operand: its copies HBM -> LDS (16 bytes per lane, 1 KB per instruction)
+// and its fragment reads.
+//
+// K-contiguous: [BT rows][64 k], chunk c of row r at c ^ swz(r) (see `sw`); a
+// fragment is one 16-byte read per lane.
+//
+// M/N-contiguous: [64 k][BT rows] as it lies in memory, read with the
+// transposing LDS read: 16 lanes hand in a 4 (k) x 16 (rows) block, lane
+// 4 e + q the 8 bytes at k-row e, rows 4 q .. 4 q + 3, and each receives one
+// row's four k values, so a fragment (8 k values) is two such reads.  The 16-byte
+// chunks of a k-row are XOR-swizzled by 4 * (k % 4) (128 rows: a k-row is 256
+// bytes) or 4 * (k / 2 % 2) (64 rows: two k-rows per 256 bytes), so that the
+// 4 k-rows x 4 chunks that 32 lanes read at once are on distinct banks.
+template <int LAY, int BT>
+struct TileOp {
+  static constexpr int NI = BT / 32;           // copy instructions per wave
+  static constexpr int CPR = BT / 8;           // M/N-contiguous: chunks per k-row
+  uint32_t off[NI];
+  int kof[NI];                                 // first k of this lane's chunk, within the tile
+  int fr[LAY == LAY_K ? 4 : 1];                // fragment offsets (K-contiguous: per k-step)
+  __device__ __forceinline__ static int swz_mn(int k) { return BT == 128 ? 4 * (k & 3) : 4 * ((k >> 1) & 1); }
+  __device__ __forceinline__ void init(long ld, int nrows, int wave, int w0) {
+    const int lane = threadIdx.x & 63;
 #pragma unroll
-    for (int j = 0; j < MNReg<ROWS>::NPT; ++j)
-      if (wave * 64 + j * NT < MNReg<ROWS>::NB) n += 8;
-    return n;
+    for (int i = 0; i < NI; ++i) {
+      if (LAY == LAY_K) {
+        const int row = (i * 4 + wave) * 8 + (lane >> 3);
+        const int c = (lane & 7) ^ swz(row);
+        off[i] = row < nrows ? (uint32_t)(((long)row * ld + c * 8) * 2) : OOB;
+        kof[i] = c * 8;
+      } else {
+        const int k = ((i * 4 + wave) * 64 + lane) / CPR;
+        const int r = 8 * ((lane % CPR) ^ swz_mn(k));
+        off[i] = r < nrows ? (uint32_t)(((long)k * ld + r) * 2) : OOB;
+        kof[i] = k;
+      }
+    }
+    if constexpr (LAY == LAY_K) {
+      const int r = lane & 31;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) fr[ks] = (w0 + r) * BK + (((2 * ks + (lane >> 5)) ^ swz(r)) << 3);
+    } else {
+      // lane group G = lane / 16: k-rows 8 (G / 2) + e, rows 16 (G % 2) + 4 q
+      const int G = lane >> 4, ll = lane & 15;
+      const int k = 8 * (G >> 1) + (ll >> 2);
+      const int c = w0 / 8 + 2 * (G & 1) + ((ll >> 1) & 1);
+      fr[0] = k * BT + 8 * (c ^ swz_mn(k)) + 4 * (ll & 1);
+    }
   }
+  // G: the operand at (tile row 0, k = 0)
+  __device__ __forceinline__ void copy(const bf16* G, long ld, int k0, int K, bf16* __restrict__ S,
+                                       int wave) const {
+    __amdgpu_buffer_rsrc_t rs = make_rsrc(G + (LAY == LAY_K ? (long)k0 : (long)k0 * ld));
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const uint32_t o = k0 + kof[i] < K ? off[i] : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(S + (i * 4 + wave) * 512), 16, o, 0, 0, 0);
+    }
+  }
+  // 32 x 16 fragment of rows w0 + 32 sub .. + 31 and k-step ks
+  __device__ __forceinline__ bf16x8 frag(const bf16* __restrict__ S, int sub, int ks) const {
+    if constexpr (LAY == LAY_K) {
+      return *reinterpret_cast<const bf16x8*>(S + fr[ks] + sub * 32 * BK);
+    } else {
+      // rows + 32: chunk + 4.  With 128 rows the swizzle is 4 (k % 4), an XOR of
+      // bits 2 - 3 of the chunk index, so the sum is formed before the XOR;
+      // the wave's rows start at a multiple of 64 (128-row tiles) or 32.
+      const int o = (BT == 128 && sub) ? fr[0] ^ 32 : fr[0];
+      const bf16x4 lo = ds_read_tr((const lds_bf16x4*)LDS_PTR(const_cast<bf16*>(S) + o + ks * 16 * BT));
+      const bf16x4 hi = ds_read_tr((const lds_bf16x4*)LDS_PTR(const_cast<bf16*>(S) + hi4(o) + ks * 16 * BT));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+  }
+  // k + 4: the same k % 4, and (64 rows) the same k / 2 % 2
+  __device__ __forceinline__ static int hi4(int o) { return o + 4 * BT; }
 };
 
-template <int MODE, int ROWS>
-__device__ __forceinline__ void op_copy(PipeOperand<MODE, ROWS>& o, __amdgpu_buffer_rsrc_t rs,
-                                        int k0, int K, bf16* __restrict__ S, int wave) {
-  if (MODE == OP_DMA) o.dma.issue(rs, k0, K, k0 + BK > K, S, wave);
-}
-template <int MODE, int ROWS>
-__device__ __forceinline__ void op_load(PipeOperand<MODE, ROWS>& o, const bf16* G, long ld, int r0,
-                                        int nrows, int k0, int K) {
-  if (MODE == OP_MN) MNReg<ROWS>::template load<true>(G, ld, r0, nrows, k0, K, o.regs);
-}
-template <int MODE, int ROWS>
-__device__ __forceinline__ void op_store(PipeOperand<MODE, ROWS>& o, bf16* __restrict__ S) {
-  if (MODE == OP_MN) MNReg<ROWS>::store(S, o.regs);
-}
-
-template <int TM, int TN>
-__device__ __forceinline__ void frag_read(bf16x8 (&af)[2][TM], bf16x8 (&bfv)[2][TN],
-                                          const bf16* __restrict__ stage, int BMr, int aoff,
-                                          int boff, int ks0, int fhalf, int fsw) {
+template <int BT, int AL, int BL>
+__device__ __forceinline__ void frag_read(bf16x8 (&af)[2][BT / 64], bf16x8 (&bfv)[2][BT / 64],
+                                          const TileOp<AL, BT>& A, const TileOp<BL, BT>& B,
+                                          const bf16* __restrict__ stage, int ks0) {
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
-    const int pos = ((2 * (ks0 + h) + fhalf) ^ fsw) << 3;
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-      af[h][i] = *reinterpret_cast<const bf16x8*>(stage + aoff + i * 32 * BK + pos);
+    for (int i = 0; i < BT / 64; ++i) af[h][i] = A.frag(stage, i, ks0 + h);
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
-      bfv[h][j] = *reinterpret_cast<const bf16x8*>(stage + BMr * BK + boff + j * 32 * BK + pos);
+    for (int j = 0; j < BT / 64; ++j) bfv[h][j] = B.frag(stage + BT * BK, j, ks0 + h);
   }
 }
 
-template <int TM, int TN>
-__device__ __forceinline__ void mfma_step(floatx16 (&acc)[TM][TN], const bf16x8 (&af)[TM],
-                                          const bf16x8 (&bfv)[TN]) {
+// Copies of K-tile t into stage S (past the last tile every chunk is past K)
+template <int BT, int AL, int BL>
+__device__ __forceinline__ void tile_copy(const TileOp<AL, BT>& A, const TileOp<BL, BT>& B,
+                                          const bf16* GA, const bf16* GB, long lda, long ldb, int t,
+                                          int nk, int K, bf16* __restrict__ S, int wave) {
+  const int k0 = min(t, nk) * BK;
+  A.copy(GA, lda, k0, K, S, wave);
+  B.copy(GB, ldb, k0, K, S + BT * BK, wave);
+}
+
+template <int TT>
+__device__ __forceinline__ void mfma_step(floatx16 (&acc)[TT][TT], const bf16x8 (&af)[TT],
+                                          const bf16x8 (&bfv)[TT]) {
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TT; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TT; ++j)
       acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[i], bfv[j], acc[i][j], 0, 0, 0);
 }
 
-// After barrier B_j: start tile j + 1 (copies into `nxt`, or register store),
-// then the register loads of tile j + 2.
-template <int AM, int BMODE, int BM, int BN>
-__device__ __forceinline__ void post_barrier(PipeOperand<AM, BM>& A, PipeOperand<BMODE, BN>& B,
-                                             const GemmArgs& p, __amdgpu_buffer_rsrc_t rsA,
-                                             __amdgpu_buffer_rsrc_t rsB, int m0, int n0, int j,
-                                             int nk, bf16* __restrict__ nxt, int wave) {
-  if (j + 1 < nk) {
-    op_copy(A, rsA, (j + 1) * BK, p.K, nxt, wave);
-    op_copy(B, rsB, (j + 1) * BK, p.K, nxt + BM * BK, wave);
-    op_store(A, nxt);
-    op_store(B, nxt + BM * BK);
-  }
-  if (j + 2 < nk) {
-    op_load(A, p.A, p.lda, m0, p.M, (j + 2) * BK, p.K);
-    op_load(B, p.B, p.ldb, n0, p.N, (j + 2) * BK, p.K);
-  }
-}
+template <int BT, int NS, int ALAY, int BLAY, int EPI, int GE>
+__global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
+  constexpr int WT = BT / 2, TT = WT / 32;
+  constexpr int STAGE = 2 * BT * BK;
+  __shared__ __attribute__((aligned(1024))) bf16 smem[NS * STAGE];
 
-template <int BM, int BN, int ALAY, int BLAY, int EPI, int GE>
-__global__ __launch_bounds__(NT) void gemm_kernel_pipe(GemmArgs p) {
-  constexpr int WTM = BM / 2, WTN = BN / 2, TM = WTM / 32, TN = WTN / 32;
-  constexpr int AM = ALAY == LAY_MN ? OP_MN : OP_DMA;
-  constexpr int BMD = BLAY == LAY_MN ? OP_MN : OP_DMA;
-  constexpr int STAGE = (BM + BN) * BK;
-  __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STAGE];
-
-  const int M = p.M, N = p.N, K = p.K;
-  const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
-  const int nwg = tiles_m * tiles_n;
-  int bid = blockIdx.x;
-  if ((nwg & 7) == 0) bid = (bid & 7) * (nwg >> 3) + (bid >> 3);
-  constexpr int G = 8;
-  const int per_group = G * tiles_n;
-  const int group = bid / per_group;
-  const int first_m = group * G;
-  const int gsize = min(tiles_m - first_m, G);
-  const int in_g = bid - group * per_group;
-  const int m0 = (first_m + in_g % gsize) * BM, n0 = (in_g / gsize) * BN;
-
+  int m0, n0;
+  tile_setup<BT, ALAY, BLAY>(p, m0, n0);
+  const int K = p.K;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
+  const bf16* GA = p.A + (ALAY == LAY_K ? (long)m0 * p.lda : (long)m0);
+  const bf16* GB = p.B + (BLAY == LAY_K ? (long)n0 * p.ldb : (long)n0);
+  TileOp<ALAY, BT> A;
+  TileOp<BLAY, BT> B;
+  A.init(p.lda, p.M - m0, wave, wm * WT);
+  B.init(p.ldb, p.N - n0, wave, wn * WT);
+  constexpr int NC = 2 * TileOp<LAY_K, BT>::NI;  // copies per wave and K-tile
 
-  __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.A + (ALAY == LAY_K ? (long)m0 * p.lda : 0)), (short)0, 0x7FFFFFFF, 0x00020000);
-  __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.B + (BLAY == LAY_K ? (long)n0 * p.ldb : 0)), (short)0, 0x7FFFFFFF, 0x00020000);
-  PipeOperand<AM, BM> A;
-  PipeOperand<BMD, BN> B;
-  if (AM == OP_DMA) A.dma.init(p.lda, M - m0, wave);
-  if (BMD == OP_DMA) B.dma.init(p.ldb, N - n0, wave);
-  // register loads outstanding after a post_barrier (per wave)
-  const int vm_mn = PipeOperand<AM, BM>::mn_loads(wave) + PipeOperand<BMD, BN>::mn_loads(wave);
-
-  floatx16 acc[TM][TN];
+  floatx16 acc[TT][TT];
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
+  for (int i = 0; i < TT; ++i)
 #pragma unroll
-    for (int j = 0; j < TN; ++j)
+    for (int j = 0; j < TT; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   const int nk = (K + BK - 1) / BK;
-  // prologue: tile 0 resident in stage 0, registers of tile 1 requested
-  op_copy(A, rsA, 0, K, smem, wave);
-  op_copy(B, rsB, 0, K, smem + BM * BK, wave);
-  op_load(A, p.A, p.lda, m0, M, 0, K);
-  op_load(B, p.B, p.ldb, n0, N, 0, K);
-  op_store(A, smem);
-  op_store(B, smem + BM * BK);
-  if (1 < nk) {
-    op_load(A, p.A, p.lda, m0, M, BK, K);
-    op_load(B, p.B, p.ldb, n0, N, BK, K);
-  }
-  if (1 < nk && vm_mn == 16) wait_vm_lgkm0<16>();
-  else if (1 < nk && vm_mn == 8) wait_vm_lgkm0<8>();
-  else wait_vm_lgkm0<0>();
+#pragma unroll
+  for (int t = 0; t < NS; ++t) tile_copy(A, B, GA, GB, p.lda, p.ldb, t, nk, K, smem + t * STAGE, wave);
+  wait_vm_lgkm0<(NS - 1) * NC>();
   cta_barrier();
+  bf16x8 f01a[2][TT], f01b[2][TT], f23a[2][TT], f23b[2][TT];
+  frag_read(f01a, f01b, A, B, smem, 0);
 
-  const int frow = lane & 31, fhalf = lane >> 5, fsw = swz(lane & 31);
-  const int aoff = (wm * WTM + frow) * BK, boff = (wn * WTN + frow) * BK;
-  bf16x8 f01a[2][TM], f01b[2][TN], f23a[2][TM], f23b[2][TN];
-  frag_read<TM, TN>(f01a, f01b, smem, BM, aoff, boff, 0, fhalf, fsw);
-  post_barrier<AM, BMD, BM, BN>(A, B, p, rsA, rsB, m0, n0, 0, nk, smem + STAGE, wave);
-
+  int st = 0;
   for (int kt = 0; kt < nk; ++kt) {
-    const bf16* cur = smem + (kt & 1) * STAGE;
-    bf16* other = smem + ((kt + 1) & 1) * STAGE;
+    bf16* cur = smem + st * STAGE;
+    st = st + 1 == NS ? 0 : st + 1;
     __builtin_amdgcn_sched_barrier(0);
-    mfma_step<TM, TN>(acc, f01a[0], f01b[0]);
-    frag_read<TM, TN>(f23a, f23b, cur, BM, aoff, boff, 2, fhalf, fsw);
+    mfma_step<TT>(acc, f01a[0], f01b[0]);
+    frag_read(f23a, f23b, A, B, cur, 2);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_step<TM, TN>(acc, f01a[1], f01b[1]);
-    mfma_step<TM, TN>(acc, f23a[0], f23b[0]);
-    if (kt + 1 < nk) {
-      // tile kt + 1 resident: this wave's copies done (only the register
-      // loads of tile kt + 2, issued after them, may remain) and its reads done
-      const bool loads = kt + 2 < nk;
-      if (loads && vm_mn == 16) wait_vm_lgkm0<16>();
-      else if (loads && vm_mn == 8) wait_vm_lgkm0<8>();
-      else wait_vm_lgkm0<0>();
-      cta_barrier();
-      frag_read<TM, TN>(f01a, f01b, other, BM, aoff, boff, 0, fhalf, fsw);
-      post_barrier<AM, BMD, BM, BN>(A, B, p, rsA, rsB, m0, n0, kt + 1, nk,
-                                    smem + (kt & 1) * STAGE, wave);
-    }
+    mfma_step<TT>(acc, f01a[1], f01b[1]);
+    mfma_step<TT>(acc, f23a[0], f23b[0]);
+    // tile kt + 1 resident, this wave's reads of tile kt done
+    wait_vm_lgkm0<(NS - 2) * NC>();
+    cta_barrier();
+    frag_read(f01a, f01b, A, B, smem + st * STAGE, 0);
+    tile_copy(A, B, GA, GB, p.lda, p.ldb, kt + NS, nk, K, cur, wave);
     __builtin_amdgcn_sched_barrier(0);
-    mfma_step<TM, TN>(acc, f23a[1], f23b[1]);
+    mfma_step<TT>(acc, f23a[1], f23b[1]);
   }
+  wait_vm_lgkm0<0>();  // the zero-filling copies past the last tile
   __syncthreads();
-  gemm_epilogue<BM, BN, EPI, GE>(p, acc, smem, m0, n0, wave, lane);
+  gemm_epilogue<BT, EPI, GE>(p, acc, smem, m0, n0, wave, lane, epilogue_vec<EPI>(p));
 }
 
-template <int BM, int BN, int ALAY, int BLAY, int EPI, int GE>
+template <int BT, int ALAY, int BLAY, int EPI, int GE>
 hipError_t launch5(const GemmArgs& a, bool vec, hipStream_t s) {
-  dim3 grid((unsigned)(sat_cdiv(a.M, BM) * sat_cdiv(a.N, BN)));
-  if (vec) hipLaunchKernelGGL((gemm_kernel_pipe<BM, BN, ALAY, BLAY, EPI, GE>), grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL((gemm_kernel_simple<BM, BN, ALAY, BLAY, EPI, GE, false>), grid, dim3(NT), 0, s, a);
+  dim3 grid((unsigned)(sat_cdiv(a.M, BT) * sat_cdiv(a.N, BT) * std::max(a.splitk, 1)));
+  if (vec) hipLaunchKernelGGL((gemm_tile_kernel<BT, BT == 64 ? 4 : 2, ALAY, BLAY, EPI, GE>), grid, dim3(NT), 0, s, a);
+  else hipLaunchKernelGGL((gemm_kernel_simple<BT, ALAY, BLAY, EPI, GE>), grid, dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 
-template <int BM, int BN, int ALAY, int BLAY, int EPI>
+template <int BT, int ALAY, int BLAY, int EPI>
 hipError_t launch4(const GemmArgs& a, bool vec, hipStream_t s) {
-  if (EPI == EPI_BF16 || EPI == EPI_DGELU_BF16) {
-    if (a.gelu_erf) return launch5<BM, BN, ALAY, BLAY, EPI, 1>(a, vec, s);
+  if constexpr (EPI == EPI_BF16 || EPI == EPI_DGELU_BF16) {
+    if (a.gelu_erf) return launch5<BT, ALAY, BLAY, EPI, 1>(a, vec, s);
   }
-  return launch5<BM, BN, ALAY, BLAY, EPI, 0>(a, vec, s);
+  return launch5<BT, ALAY, BLAY, EPI, 0>(a, vec, s);
 }
 
 template <int ALAY, int BLAY, int EPI>
-hipError_t launch3(const GemmArgs& a, bool vec, hipStream_t s) {
-  // 256 x 256 tiles when they still give every CU at least one tile,
-  // 256 x 128 otherwise (and for the scalar-load fallback).
-  const long big_tiles = (long)sat_cdiv(a.M, 256) * sat_cdiv(a.N, 256);
-  if (vec && big_tiles >= 256) return launch4<256, 256, ALAY, BLAY, EPI>(a, vec, s);
-  return launch4<256, 128, ALAY, BLAY, EPI>(a, vec, s);
+hipError_t launch3(const GemmArgs& a, int bt, bool vec, hipStream_t s) {
+  if (bt == 64) return launch4<64, ALAY, BLAY, EPI>(a, vec, s);
+  return launch4<128, ALAY, BLAY, EPI>(a, vec, s);
 }
 
 template <int ALAY, int BLAY>
-hipError_t launch2(const GemmArgs& a, int epi, bool vec, hipStream_t s) {
+hipError_t launch2(const GemmArgs& a, int epi, int bt, bool vec, hipStream_t s) {
   switch (epi) {
-    case EPI_F32: return launch3<ALAY, BLAY, EPI_F32>(a, vec, s);
-    case EPI_RESID_F32: return launch3<ALAY, BLAY, EPI_RESID_F32>(a, vec, s);
-    case EPI_BF16: return launch3<ALAY, BLAY, EPI_BF16>(a, vec, s);
-    case EPI_DGELU_BF16: return launch3<ALAY, BLAY, EPI_DGELU_BF16>(a, vec, s);
+    case EPI_F32: return launch3<ALAY, BLAY, EPI_F32>(a, bt, vec, s);
+    case EPI_RESID_F32: return launch3<ALAY, BLAY, EPI_RESID_F32>(a, bt, vec, s);
+    case EPI_BF16: return launch3<ALAY, BLAY, EPI_BF16>(a, bt, vec, s);
+    case EPI_DGELU_BF16: return launch3<ALAY, BLAY, EPI_DGELU_BF16>(a, bt, vec, s);
   }
   return hipErrorInvalidValue;
 }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
+
+// Whether both operands can be copied in 16-byte pieces.  Along K a partial
+// piece would mix in values past K, so K must be a multiple of 8; along M / N a
+// partial piece only feeds output rows / columns that are never stored, so it
+// suffices that the rows are long enough (ld >= M or N rounded up to 8) to stay
+// in bounds.
+bool tile_vec(const GemmArgs& a, int alay, int blay) {
+  auto r8 = [](long x) { return (x + 7) / 8 * 8; };
+  return aligned16(a.A) && aligned16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
+         (alay == LAY_K ? a.K % 8 == 0 : a.lda >= r8(a.M)) &&
+         (blay == LAY_K ? a.K % 8 == 0 : a.ldb >= r8(a.N));
+}
+
+hipError_t launch_tiles(const GemmArgs& a, int bt, int alay, int blay, int epi, hipStream_t s) {
+  const bool vec = tile_vec(a, alay, blay);
+  if (alay == LAY_K && blay == LAY_K) return launch2<LAY_K, LAY_K>(a, epi, bt, vec, s);
+  if (alay == LAY_K && blay == LAY_MN) return launch2<LAY_K, LAY_MN>(a, epi, bt, vec, s);
+  if (alay == LAY_MN && blay == LAY_K) return launch2<LAY_MN, LAY_K>(a, epi, bt, vec, s);
+  return launch2<LAY_MN, LAY_MN>(a, epi, bt, vec, s);
+}
 
 }  // namespace
 
@@ -649,37 +683,121 @@ long gemm_tail_ws_elems(int M, int N, int K, int smax) {
   return gemm_tail_split(M, N, K, smax, &m1, &s, &c) ? (long)s * (M - m1) * N : 0;
 }
 
+namespace {
+
+// Estimated time (us) of an [M, N] product of depth K in S slices on tiles of
+// bt x bt, from measured products (random operands, 0.5 to 300 GFLOP):
+//  * 256: rounds of one tile per CU; a K-tile of 64 takes 1.5 us, a tile's
+//    prologue and epilogue 6.5 us (1.75 and 8 with an M/N-contiguous operand);
+//  * 128: two tiles share a CU; 0.39 us per K-tile and 4.5 us per tile of a CU,
+//    0.62 and 5 us for a CU that has one;
+//  * 64: 0.215 us per K-tile and 0.6 us per tile of a CU, 3 us in all;
+//  * the reduction of the slices: 4 us and its traffic at 6 TB/s.
+double gemm_estimate(int bt, bool mn, long M, long N, long K, int S) {
+  const double kt = (double)((sat_cdiv(K, S) + 63) / 64);
+  const long n = ((long)sat_cdiv(M, bt) * sat_cdiv(N, bt) * S + 255) / 256;
+  const double red = S > 1 ? 4.0 + (S + 1.0) * M * N * 4.0 / 6e6 : 0.0;
+  if (bt == 256) return n * (mn ? 1.75 * kt + 8.0 : 1.5 * kt + 6.5) + red;
+  if (bt == 128) return (n == 1 ? 0.62 * kt + 5.0 : n * (0.39 * kt + 4.5)) + red;
+  return 3.0 + n * (0.6 + 0.215 * kt) + red;
+}
+
+struct GemmPlan {
+  int bt;  // 256: gemm256.hip, else the BT x BT kernel
+  int S;   // K slices, kc deep
+  int kc;
+  double us;
+};
+
+// Which kernel runs a product, and in how many K slices.  Fewer than 256 tiles
+// of 256 x 256 leave CUs idle, and the last of a few rounds is mostly empty:
+// 128 x 128 tiles then win on a finer grid and on two workgroups per CU whose
+// epilogues and main loops overlap (8192 x 768 x 3072: 60 us as two slices of
+// 256 x 256 tiles and a reduction, 47 us; 1285 x 5120 x 1280: 30 and 26 us), 64 x 64
+// tiles on a grid that would leave most CUs without a 128 x 128 tile
+// (128 x 4096 x 4096: 48 and 16 us; 64 x 64 x 512: 8.5 and 4.5 us).
+// Large products keep the 256 x 256 kernel: it moves half the bytes per FLOP
+// (4096 x 28672 x 4096: 720 us, 128 x 128 1040 us).  So do products whose
+// operands exceed the 256 MB Infinity Cache, where each re-read of a panel comes
+// from HBM (the LM head's 8192 x 768 x 50264 input gradient: 630 us in eight
+// slices of 256 x 256 tiles, 1070 us in two of 128 x 128).  bf16 outputs weigh the
+// smaller tiles 15 % heavier: with cold operands and outputs their many small
+// tiles lose what they win on warm ones (8192 x 2304 x 768 in a step: 47 us
+// on 256 x 256 tiles, 60 on 128 x 128; called alone 46 and 45).
+//
+// Slices: an fp32-output product on K-contiguous operands splits as
+// gemm_splitk says (never in more slices, so its workspace holds them), or
+// not at all where unsplit 128 x 128 or 64 x 64 tiles fill the chip and are
+// faster.  With an M/N-contiguous operand it splits where the workspace holds it.
+GemmPlan gemm_plan(const GemmArgs& a, int alay, int blay, int epi) {
+  const bool kl = alay == LAY_K && blay == LAY_K;
+  const bool may_split = (epi == EPI_F32 || epi == EPI_RESID_F32) && a.splitk_ws != nullptr;
+  const bool big = ((double)a.M + a.N) * a.K * 2.0 > 256e6;
+  GemmPlan best{128, 1, 0, 1e30};
+  auto consider = [&](int bt, int S, int kc) {
+    const double us = gemm_estimate(bt, !kl, a.M, a.N, a.K, S) *
+                      (bt != 256 && (epi == EPI_BF16 || epi == EPI_DGELU_BF16) ? 1.15 : 1.0);
+    if (us < best.us) best = GemmPlan{bt, S, kc, us};
+  };
+  auto slices = [&](int bt, int smax) {
+    for (int S = 2; S <= smax; ++S) {
+      const int kc = (sat_cdiv(a.K, S) + BK - 1) / BK * BK;
+      consider(bt, sat_cdiv(a.K, kc), kc);
+    }
+  };
+  int kc256 = 0;
+  int S256 = may_split && kl ? gemm_splitk(a.M, a.N, a.K, &kc256, a.splitk_max) : 1;
+  if (S256 > 1 && (long)S256 * a.M * a.N > a.splitk_ws_elems) S256 = 1;
+  GemmArgs b = a;
+  if (S256 > 1) {
+    b.out = a.splitk_ws;
+    b.ldo = a.N;
+    b.bias = nullptr;
+    b.resid = nullptr;
+    b.splitk = S256;
+    b.splitk_kc = kc256;
+    b.split_stride = (long)a.M * a.N;
+    if (gemm256_eligible(b, LAY_K, LAY_K, EPI_F32)) {
+      consider(256, S256, kc256);
+      if (big) return best;
+      slices(128, S256);
+      slices(64, S256);
+    } else {
+      S256 = 1;
+    }
+  } else if (may_split && !kl && a.K >= 1024 && tile_vec(a, alay, blay)) {
+    const long fit = a.splitk_ws_elems / std::max(1L, (long)a.M * a.N);
+    const int smax = (int)std::min<long>(std::min<long>(16, a.K / 512), fit);
+    slices(128, smax);
+    slices(64, smax);
+  }
+  if (S256 <= 1 && big && gemm256_eligible(a, alay, blay, epi)) {
+    consider(256, 1, 0);
+    return best;
+  }
+  for (int bt : {128, 64})
+    if (S256 <= 1 || (long)sat_cdiv(a.M, bt) * sat_cdiv(a.N, bt) >= 256) consider(bt, 1, 0);
+  if (S256 <= 1 && gemm256_eligible(a, alay, blay, epi)) consider(256, 1, 0);
+  return best;
+}
+
+}  // namespace
+
+int gemm_colsum_rows(const GemmArgs& a) {
+  const GemmPlan p = gemm_plan(a, LAY_K, LAY_K, EPI_DGELU_BF16);
+  return p.bt / 2;
+}
+
 hipError_t launch_gemm(const GemmArgs& a, int alay, int blay, int epi, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.K <= 0) return hipErrorInvalidValue;
-  // fp32 outputs with too few tiles to fill the chip: split-K into the
-  // caller's workspace, then one reduction that applies bias and residual
-  if ((epi == EPI_F32 || epi == EPI_RESID_F32) && alay == LAY_K && blay == LAY_K &&
-      a.splitk <= 1 && a.splitk_ws != nullptr) {
-    int kc = 0;
-    const int S = gemm_splitk(a.M, a.N, a.K, &kc, a.splitk_max);
-    if (S > 1 && (long)S * a.M * a.N <= a.splitk_ws_elems) {
-      GemmArgs b = a;
-      b.out = a.splitk_ws;
-      b.ldo = a.N;
-      b.bias = nullptr;
-      b.resid = nullptr;
-      b.splitk = S;
-      b.splitk_kc = kc;
-      b.split_stride = (long)a.M * a.N;
-      if (gemm256_eligible(b, LAY_K, LAY_K, EPI_F32)) {
-        hipError_t e = launch_gemm256(b, LAY_K, LAY_K, EPI_F32, s);
-        if (e != hipSuccess) return e;
-        return launch_splitk_reduce(a.splitk_ws, S, b.split_stride, a.M, a.N,
-                                    reinterpret_cast<float*>(a.out), a.ldo, a.bias, a.bias_col0,
-                                    epi == EPI_RESID_F32 ? a.resid : nullptr, a.ldr, s);
-      }
-    }
-  }
+  if (epi == EPI_ADAMW)  // the optimizer epilogue exists in the 256 x 256 kernel only
+    return gemm256_eligible(a, alay, blay, epi) ? launch_gemm256(a, alay, blay, epi, s)
+                                                : hipErrorInvalidValue;
   // more than 256 tiles with a mostly empty last round: whole rounds of rows
   // unsplit, the remaining rows split-K into the workspace
   if ((epi == EPI_F32 || epi == EPI_RESID_F32) && alay == LAY_K && blay == LAY_K &&
-      a.splitk <= 1 && a.splitk_ws != nullptr && !a.no_tail_split) {
+      a.splitk_ws != nullptr && !a.no_tail_split) {
     int M1 = 0, S = 0, kc = 0;
     if (gemm_tail_split(a.M, a.N, a.K, a.splitk_max, &M1, &S, &kc) &&
         (long)S * (a.M - M1) * a.N <= a.splitk_ws_elems) {
@@ -708,19 +826,24 @@ hipError_t launch_gemm(const GemmArgs& a, int alay, int blay, int epi, hipStream
       }
     }
   }
-  if (gemm256_eligible(a, alay, blay, epi)) return launch_gemm256(a, alay, blay, epi, s);
-  // the optimizer epilogue and the fused column sums exist in the 256 x 256 kernel only
-  if (epi == EPI_ADAMW || a.colsum_part != nullptr) return hipErrorInvalidValue;
-  // 16-byte loads need aligned rows.  Along K a partial vector would mix in
-  // values past K, so K must be a multiple of 8; along M / N a partial vector
-  // only feeds output rows / columns that are never stored, so it suffices that
-  // the rows are long enough (ld >= M or N rounded up to 8) to stay in bounds.
-  auto r8 = [](long x) { return (x + 7) / 8 * 8; };
-  bool vec = aligned16(a.A) && aligned16(a.B) && (a.lda % 8 == 0) && (a.ldb % 8 == 0);
-  vec = vec && (alay == LAY_K ? (a.K % 8 == 0) : (a.lda >= r8(a.M)));
-  vec = vec && (blay == LAY_K ? (a.K % 8 == 0) : (a.ldb >= r8(a.N)));
-  if (alay == LAY_K && blay == LAY_K) return launch2<LAY_K, LAY_K>(a, epi, vec, s);
-  if (alay == LAY_K && blay == LAY_MN) return launch2<LAY_K, LAY_MN>(a, epi, vec, s);
-  if (alay == LAY_MN && blay == LAY_K) return launch2<LAY_MN, LAY_K>(a, epi, vec, s);
-  return launch2<LAY_MN, LAY_MN>(a, epi, vec, s);
+  const GemmPlan plan = gemm_plan(a, alay, blay, epi);
+  if (plan.S <= 1)
+    return plan.bt == 256 ? launch_gemm256(a, alay, blay, epi, s)
+                          : launch_tiles(a, plan.bt, alay, blay, epi, s);
+  // K slices into the caller's workspace, then one reduction that applies bias
+  // and residual
+  GemmArgs b = a;
+  b.out = a.splitk_ws;
+  b.ldo = a.N;
+  b.bias = nullptr;
+  b.resid = nullptr;
+  b.splitk = plan.S;
+  b.splitk_kc = plan.kc;
+  b.split_stride = (long)a.M * a.N;
+  const hipError_t e = plan.bt == 256 ? launch_gemm256(b, alay, blay, EPI_F32, s)
+                                      : launch_tiles(b, plan.bt, alay, blay, EPI_F32, s);
+  if (e != hipSuccess) return e;
+  return launch_splitk_reduce(a.splitk_ws, plan.S, b.split_stride, a.M, a.N,
+                              reinterpret_cast<float*>(a.out), a.ldo, a.bias, a.bias_col0,
+                              epi == EPI_RESID_F32 ? a.resid : nullptr, a.ldr, s);
 }

@@ -960,14 +960,6 @@ bool gemm256_eligible(const GemmArgs& a, int alay, int blay, int epi) {
         a.split_stride < (long)(a.M - 1) * a.ldo + a.N)
       return false;
   }
-  // at least 64 tiles of 256 x 256: down to a quarter of the CUs, this kernel
-  // still beats the general one on twice as many 256 x 128 tiles (measured on
-  // the ResNet convolutions, the grid's GPT-2-medium members and GPT-2-small:
-  // 1.9 %, 3.1 % and 2.1 % per step), even when half of every tile is padding
-  // (128 output columns); split-K products are small by construction and run
-  // whatever their tile count
-  if (a.splitk <= 1 && (long)sat_cdiv(a.M, BT) * sat_cdiv(a.N, BT) < 64 && a.colsum_part == nullptr)
-    return false;
   if (a.colsum_part != nullptr) {
     // DGELU column sums: K-contiguous operands and the 16-byte epilogue for
     // every interior tile

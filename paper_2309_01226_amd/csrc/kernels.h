@@ -61,7 +61,7 @@ struct GemmArgs {
   bf16* opt_sht;
   long opt_trows;
   AdamWConsts opt_c;
-  // Split-K (256 x 256 kernel, EPI_F32, both operands K-contiguous, no bias):
+  // Split-K (EPI_F32, no bias; set by launch_gemm for its own launches):
   // splitk > 1 cuts K into slices of splitk_kc (a multiple of 64); slice s
   // writes its fp32 partial product to out + s * split_stride.
   int splitk;
@@ -76,10 +76,9 @@ struct GemmArgs {
   // output tiles and very long K (the convolution weight gradients, K =
   // pixels) fill the chip only with more.
   int splitk_max;
-  // EPI_DGELU_BF16 in the 256 x 256 kernel: when not null, also the column
-  // sums of the bf16 results over each block of 128 rows, block b at
-  // colsum_part[b * N + n] (cdiv(M, 128) rows; launch_colsum_partials then
-  // adds them in order).  Needs gemm256_eligible to hold with it set.
+  // EPI_DGELU_BF16: when not null, also the column sums of the bf16 results
+  // over each block of R = gemm_colsum_rows rows, block b at colsum_part[b * N
+  // + n] (cdiv(M, R) rows; launch_colsum_partials then adds them in order).
   float* colsum_part;
   // Keeps launch_gemm from splitting the rows of a mostly empty last round
   // (gemm_tail_split): a weight gradient whose AdamW step may instead be
@@ -88,6 +87,10 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(const GemmArgs& a, int alay, int blay, int epi, hipStream_t s);
+// Rows per block of the column sums that launch_gemm writes for this
+// EPI_DGELU_BF16 product on K-contiguous operands: half the tile of the kernel
+// it runs (128, 64 or 32).
+int gemm_colsum_rows(const GemmArgs& a);
 // The 256 x 256 four-stage kernel (gemm256.hip) for large aligned problems;
 // launch_gemm dispatches to it when gemm256_eligible holds.
 bool gemm256_eligible(const GemmArgs& a, int alay, int blay, int epi);

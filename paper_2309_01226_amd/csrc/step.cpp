@@ -273,16 +273,18 @@ static sat_status wgrad(sat_model* M, bool trans, bool y_ready, const bf16* Y, l
 }
 
 // The fc1 bias gradient is the column sum of the fc2 input-gradient product's
-// output.  Where the 256 x 256 kernel runs that product, its epilogue writes
-// the column sums of every 128-row block into the partial buffer, which one
-// launch of the partial-sum kernel then adds in order; otherwise the output is
-// summed by the column-sum kernels afterwards.
-static bool with_colsums(sat_model* M, GemmArgs& a) {
-  a.colsum_part = sat_fc1_bias_in_epilogue(M->D) ? M->part : nullptr;
-  if (!a.colsum_part) return false;
-  if (((long)a.M + 127) / 128 * a.N > M->part_elems || !gemm256_eligible(a, LAY_K, LAY_K, EPI_DGELU_BF16))
-    a.colsum_part = nullptr;
-  return a.colsum_part != nullptr;
+// output.  The product's epilogue writes the column sums of every block of rows
+// into the partial buffer, which one launch of the partial-sum kernel then adds
+// in order.  Returns the number of partial rows (0: none, the output is summed
+// by the column-sum kernels afterwards).
+static int with_colsums(sat_model* M, GemmArgs& a) {
+  if (!sat_fc1_bias_in_epilogue(M->D)) return 0;
+  a.colsum_part = M->part;
+  const int rows = gemm_colsum_rows(a);
+  const long np = ((long)a.M + rows - 1) / rows;
+  if (np * a.N <= M->part_elems) return (int)np;
+  a.colsum_part = nullptr;
+  return 0;
 }
 
 // Weight-gradient stream.  fork: what the model's stream has enqueued so far
@@ -439,10 +441,10 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       du.aux = A.qkv + 3 * d;
       du.ldaux = D.qkv_ld;
       du.gelu_erf = 0;
-      const bool fc1b_fused = with_colsums(M, du);
+      const int fc1b_parts = with_colsums(M, du);
       TRY(gemm(M, du, LAY_K, LAY_K, EPI_DGELU_BF16));
-      if (fc1b_fused)
-        SAT_HIP(launch_colsum_partials(M->part, (int)((T + 127) / 128), m, grad(M, pb + J_FC1B), s));
+      if (fc1b_parts)
+        SAT_HIP(launch_colsum_partials(M->part, fc1b_parts, m, grad(M, pb + J_FC1B), s));
       GemmArgs go = gargs(M->dh_bf, d, shadow_t(M, pb + J_PROJW), d, T, d, d, M->dout, d);
       TRY(gemm(M, go, LAY_K, LAY_K, EPI_BF16));
       if (ov) {
@@ -474,7 +476,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
         TRY(wgrad(M, tr, false, M->dqkv, D.qkv_ld, D.qkv_ld, A.a, d, D.qkv_ld, d, T, pb + J_QKVW,
                   TK_QKV_WGRAD));
       }
-      if (!fc1b_fused)
+      if (!fc1b_parts)
         SAT_HIP(launch_colsum_bf16(M->dqkv + 3 * d, D.qkv_ld, T, m, M->part, npT,
                                    grad(M, pb + J_FC1B), s));
       TRY(ln_bwd(M, M->dA, M->h_in[l], 1, pb + J_LN1G, A.mean1, A.rstd1, T,
@@ -487,10 +489,10 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       du.aux = A.u;
       du.ldaux = m;
       du.gelu_erf = gelu_erf;
-      const bool fc1b_fused = with_colsums(M, du);
+      const int fc1b_parts = with_colsums(M, du);
       TRY(gemm(M, du, LAY_K, LAY_K, EPI_DGELU_BF16));
-      if (fc1b_fused)
-        SAT_HIP(launch_colsum_partials(M->part, (int)((T + 127) / 128), m, grad(M, pb + B_FC1B), s));
+      if (fc1b_parts)
+        SAT_HIP(launch_colsum_partials(M->part, fc1b_parts, m, grad(M, pb + B_FC1B), s));
       GemmArgs gc = gargs(M->du, m, shadow_t(M, pb + B_FC1W), m, T, d, m, M->dA, d);
       TRY(gemm(M, gc, LAY_K, LAY_K, EPI_F32));
       if (ov) {
@@ -505,7 +507,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
         TRY(wgrad(M, tr, false, M->dh_bf, d, d, A.g, m, d, m, T, pb + B_FC2W));
         TRY(wgrad(M, tr, false, M->du, m, m, A.c, d, m, d, T, pb + B_FC1W));
       }
-      if (!fc1b_fused)
+      if (!fc1b_parts)
         SAT_HIP(launch_colsum_bf16(M->du, m, T, m, M->part, npT, grad(M, pb + B_FC1B), s));
       TRY(ln_bwd(M, M->dA, A.h_mid, 1, pb + B_LN2G, A.mean2, A.rstd2, T,
                  bias_in_ln_bwd(M) ? grad(M, pb + B_PROJB) : nullptr));

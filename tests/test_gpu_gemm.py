@@ -214,3 +214,73 @@ def test_gemm_tail_split(M, N, K, resid):
     # fewer than a split of every row would write
     n_used = int(torch.isfinite(ws).sum().item())
     assert 2 * N * 16 <= n_used < 2 * M * N, n_used
+
+
+# The 128 x 128 and 64 x 64 tile kernels at grids that fill the chip: ragged last
+# tiles in M and N, a K tail, rows whose 4-column vectors are aligned and rows
+# where they are not (N odd, so every layout but (0, 0) is gathered), every
+# layout and epilogue.
+TILES = [(3001, 1288, 712), (1285, 520, 200), (2100, 1301, 328)]
+
+
+@pytest.mark.parametrize("a_layout,b_layout", [(0, 0), (0, 1), (1, 1), (1, 0)])
+@pytest.mark.parametrize("epi", [0, 1, 2, 3])
+@pytest.mark.parametrize("M,N,K", TILES)
+def test_gemm_tile_kernels(M, N, K, epi, a_layout, b_layout):
+    from paper_2309_01226_amd import ops
+    flush(f"gemm tiles lay=({a_layout},{b_layout}) epi={epi} M={M} N={N} K={K}")
+    rng = np.random.default_rng(M + epi + 4 * a_layout + 8 * b_layout)
+    A = bf16_round(rng.normal(size=(M, K)))
+    B = bf16_round(rng.normal(size=(N, K)))
+    up = lambda n: (n + 7) // 8 * 8  # noqa: E731  (row pitches of whole 16-byte pieces)
+
+    def stored(X, layout):
+        X = X if layout == 0 else X.T
+        pad = np.zeros((X.shape[0], up(X.shape[1])))
+        pad[:, :X.shape[1]] = X
+        return to_dev_bf16(pad), pad.shape[1]
+
+    Ad, lda = stored(A, a_layout)
+    Bd, ldb = stored(B, b_layout)
+    kw = dict(lda=lda, ldb=ldb, a_layout=a_layout, b_layout=b_layout, epilogue=epi)
+    C = O.gemm(A, B)
+    bias = rng.normal(size=N - 8)
+    pre = C.copy()
+    pre[:, 8:] += bias
+    if epi < 2:
+        R = rng.normal(size=(M, N)).astype(np.float32)
+        out = to_dev_f32(R)
+        ops.gemm(Ad, Bd, M, N, K, out, resid=out if epi else None, bias=to_dev_f32(bias), bias_col0=8, **kw)
+        torch.cuda.synchronize()
+        assert rel(host(out), pre + (R if epi else 0.0)) < 2e-6
+    elif epi == 2:
+        o1 = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+        o2 = torch.empty(M, N - 72, device="cuda", dtype=torch.bfloat16)
+        ops.gemm(Ad, Bd, M, N, K, o1, bias=to_dev_f32(bias), bias_col0=8, out2=o2, ldo2=N - 72, gelu_col0=72, **kw)
+        torch.cuda.synchronize()
+        assert rel(host(o1), pre) < 4e-3
+        assert rel(host(o2), O.gelu(pre[:, 72:], 0)) < 4e-3
+    else:
+        U = bf16_round(rng.normal(size=(M, N)))
+        o3 = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
+        ops.gemm(Ad, Bd, M, N, K, o3, aux=to_dev_bf16(U), ldaux=N, gelu_erf=1, **kw)
+        torch.cuda.synchronize()
+        assert rel(host(o3), C * O.gelu_grad(U, 1)) < 4e-3
+
+
+@pytest.mark.parametrize("a_layout,b_layout", [(0, 1), (1, 1), (1, 0)])
+def test_gemm_splitk_mn_layouts(a_layout, b_layout):
+    """An M/N-contiguous operand with a workspace: K slices, the last one short."""
+    from paper_2309_01226_amd import ops
+    M, N, K = 264, 392, 4168
+    flush(f"gemm split-K lay=({a_layout},{b_layout})")
+    rng = np.random.default_rng(23)
+    A, B, Ad, Bd, lda, ldb = _operands(rng, M, N, K, a_layout, b_layout)
+    R = rng.normal(size=(M, N)).astype(np.float32)
+    ws = torch.full((16 * M * N,), float("nan"), device="cuda", dtype=torch.float32)
+    out = to_dev_f32(R)
+    ops.gemm(Ad, Bd, M, N, K, out, lda=lda, ldb=ldb, a_layout=a_layout, b_layout=b_layout, epilogue=1, resid=out,
+             splitk_ws=ws)
+    torch.cuda.synchronize()
+    assert rel(host(out), R + O.gemm(A, B)) < 2e-6
+    assert int(torch.isfinite(ws).sum().item()) >= 2 * M * N
