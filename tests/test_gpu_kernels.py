@@ -293,6 +293,23 @@ def test_embedding(T, d, V):
     assert rel(host(dw), O.embed_bwd(tok, dh, V)) < 1e-6
 
 
+# Frequent tokens (runs longer than the loads in flight, and not a multiple of them), columns in
+# more than one block of 1024 with a ragged last one, a vocabulary that ends inside a group of
+# rows, every key in one thread (T < 1024) and 16 per thread (T = 16384).
+@pytest.mark.parametrize("T,d,V", [(77, 1028, 5), (3000, 2052, 1022), (16384, 16, 65535)])
+def test_embedding_bwd_skewed(T, d, V):
+    flush(f"embedding skewed T={T} d={d} V={V}")
+    rng = np.random.default_rng(T + d)
+    tok = (V * rng.random(T) ** 4).astype(np.int32)
+    tok[::7] = V - 1
+    dh = rng.normal(size=(T, d)).astype(np.float32)
+    dw = torch.full((V, d), 7.0, device="cuda")
+    ops().embed_bwd(torch.as_tensor(tok).cuda(), to_dev_f32(dh), dw, T, d, V)
+    ref = np.zeros((V, d), np.float32)
+    np.add.at(ref, tok, dh)  # fp32, in position order: the same sums
+    assert np.array_equal(host(dw), ref)
+
+
 def test_colsum():
     rng = np.random.default_rng(2)
     X = rng.normal(size=(1000, 333)).astype(np.float32)
