@@ -15,7 +15,17 @@
 // only on blocks that cross the diagonal or the sequence end) and keep
 // several waves per SIMD so that one wave's exp overlaps another's MFMAs.
 //
-// Workgroup = 4 waves x 32 rows (queries for the forward and dQ kernels,
+// They are bound by latency before either unit is full: a wave's block is a chain of LDS
+// reads, MFMAs, the max, the exponentials and MFMAs again (vector unit busy a
+// third, matrix cores a sixth of the cycles at 8 x 12 heads of 1024 x 64).  So the
+// row fragments of a step are read together ahead of its MFMAs, whose two
+// chains alternate, the transposed ones ahead of the exponentials where
+// registers allow, and masked and whole blocks run in loops of their own.
+// Forward / backward, before and after: 1 x 8 heads of 1359 x 64 causal 25 / 68 and
+// 17.6 / 52 us; 2 x 12 of 2048 x 80 causal 45 / 128 and 37 / 104; 8 x 12 of 1024 x 64
+// causal 31 / 84 and 28 / 76.
+//
+// Workgroup = 2 to 4 waves x 32 rows (queries for the forward and dQ kernels,
 // keys for the dK/dV kernel) of one (batch, head); the other operand streams
 // through LDS in blocks of 64 rows, two stages, copied HBM -> LDS with
 // buffer_load ... lds (no VGPR staging).
@@ -31,14 +41,14 @@
 // Products whose output rows are head dims (O^T, dV^T, dK^T, dQ^T) use
 // 32-row MFMA tiles; for 80-wide heads the third tile's rows 80..95 read
 // dims 64..79 again and are discarded at the store.
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
 namespace {
 
-constexpr int NT = 256;        // 4 waves
 constexpr int WR = 32;         // rows owned by a wave
-constexpr int WGR = 4 * WR;    // rows owned by a workgroup
 constexpr int KB = 64;         // rows per staged block
 constexpr float LOG2E = 1.4426950408889634f;
 constexpr float LN2 = 0.6931471805599453f;
@@ -77,8 +87,45 @@ __device__ __forceinline__ floatx16 zero16() {
 }
 // Row (within a 32 x 32 tile) held by accumulator register r of lane group g.
 __device__ __forceinline__ int acc_row(int r, int g) { return 8 * (r >> 2) + 4 * g + (r & 3); }
-__device__ __forceinline__ float halves_max(float x) { return fmaxf(x, __shfl_xor(x, 32, 64)); }
+// Maximum over the two half-waves, exchanged on the vector unit (a shuffle goes
+// through the LDS unit).
+__device__ __forceinline__ float halves_max(float x) {
+  const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(s[0]), __uint_as_float(s[1]));
+}
 __device__ __forceinline__ float halves_sum(float x) { return x + __shfl_xor(x, 32, 64); }
+
+// Maximum of three.  fmaxf first quiets each operand (v_max x, x), since the
+// compiler cannot know that an MFMA result is no signaling NaN; this does not.
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+// Which head and which block of its rows a workgroup takes.  Workgroups are dealt
+// round-robin over the 8 XCDs, each with its own 4 MB L2.  With at least 64
+// heads, each XCD takes a contiguous eighth of them, in groups whose staged
+// operands (K and V, or Q and dO: 4 S dh bytes per head) fit its L2 together, and
+// within a group all first (with a causal mask: heaviest) blocks, then all second
+// ones.  So a head's blocks read the staged operand from HBM once, and
+// neighbouring 80-wide heads, whose rows share 128-byte lines, share the L2.
+// 64 x 16 heads of 257 x 80, blocks outermost over all heads: the forward read K and V
+// three times (forward 79 us, backward 229), now 53 and 175.  Fewer heads are dealt out one by one.
+__device__ __forceinline__ bool wg_item(int BH, int nb, int group, int& blk, int& bh) {
+  const int id = blockIdx.x;
+  if (BH < 64) {
+    blk = id / BH;
+    bh = id % BH;
+    return true;
+  }
+  const int hx = (BH + 7) >> 3, slot = id >> 3;
+  const int g = slot / (group * nb), r = slot - g * group * nb;
+  const int gh = min(group, hx - g * group);
+  blk = r / gh;
+  bh = (id & 7) * hx + g * group + r % gh;
+  return bh < BH;
+}
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, long byte_off) {
   return __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)base + byte_off), (short)0, 0x7FFFFFFF,
@@ -87,15 +134,15 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows_rsrc(const void* base, lo
 
 // Copies of R rows (a block of K, V, Q or dO) into an LDS tile; rows >=
 // nvalid read zero.  rs addresses row 0 of the block, rows ld elements apart.
-template <int DH, int R>
+template <int DH, int R, int NW>
 __device__ __forceinline__ void copy_tile(__amdgpu_buffer_rsrc_t rs, long ld, int nvalid, bf16* dst,
                                           int wave) {
   const int lane = threadIdx.x & 63;
   constexpr int NM = R / 8;  // 1 KB instructions of the 64-dim part
 #pragma unroll
-  for (int i = 0; i < (NM + 3) / 4; ++i) {
-    const int j = 4 * i + wave;
-    if (NM % 4 == 0 || j < NM) {
+  for (int i = 0; i < (NM + NW - 1) / NW; ++i) {
+    const int j = NW * i + wave;
+    if (NM % NW == 0 || j < NM) {
       const int row = 8 * j + (lane >> 3);
       const int c = (lane & 7) ^ swz(row);
       const uint32_t o = row < nvalid ? (uint32_t)(((long)row * ld + 8 * c) * 2) : OOB;
@@ -199,24 +246,40 @@ template <int DH>
 struct FwdState {
   bf16x8 qf[Cfg<DH>::KS];
   floatx16 o[Cfg<DH>::OT];
-  float m, l;  // running max (base 2, scaled, lazily raised) and sum
+  float m, l;  // running max (base 2, scaled, lazily raised); sum over this lane's keys
 };
 
-// One block of up to 64 keys.  two: keys 32..63 of the block hold a valid
-// key for some query of the wave; MASK: some score of the block is masked
-// (key >= lim, lim = first excluded key of this lane's query), always the
-// case when `two` is false.
-template <int DH, bool MASK>
+// One block of up to 64 keys.  MASK: some score of the block is masked (key >=
+// lim, lim_rel = first excluded key of this lane's query relative to the block start
+// and 4 g); two: keys 32..63 of the block hold a valid key for some query of
+// the wave (always the case without MASK).
+// PF: 16-key steps whose V fragments are read ahead of the exponentials (80-wide
+// heads: one keeps three waves per SIMD, two make it two: 53 -> 60 us at 64 x 16 x 257).
+template <int DH, bool MASK, int PF = DH == 64 ? 4 : 1>
 __device__ __forceinline__ void fwd_block(FwdState<DH>& st, const TileOfs<DH, KB>& to, const bf16* Ks,
                                           const bf16* Vs, float sc, bool two, int lim_rel) {
   using C = Cfg<DH>;
   floatx16 s0 = zero16(), s1 = zero16();
+  {
+    bf16x8 k0[C::KS], k1[C::KS];
 #pragma unroll
-  for (int c = 0; c < C::KS; ++c) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.row(Ks, 0, c), st.qf[c], s0, 0, 0, 0);
-  if (two) {
+    for (int c = 0; c < C::KS; ++c) {
+      k0[c] = to.row(Ks, 0, c);
+      k1[c] = to.row(Ks, 1, c);
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.row(Ks, 1, c), st.qf[c], s1, 0, 0, 0);
+    for (int c = 0; c < C::KS; ++c) {
+      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.qf[c], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.qf[c], s1, 0, 0, 0);
+    }
   }
+  bf16x8 vf[PF ? PF : 1][C::OT];
+#pragma unroll
+  for (int kk = 0; kk < PF; ++kk)
+#pragma unroll
+    for (int ot = 0; ot < C::OT; ++ot) vf[kk][ot] = to.trans(Vs, kk, ot);
+  __builtin_amdgcn_sched_barrier(0);
   float x[32];
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -224,16 +287,22 @@ __device__ __forceinline__ void fwd_block(FwdState<DH>& st, const TileOfs<DH, KB
     x[16 + r] = s1[r];
   }
   if (MASK) {
-    // lim_rel: first excluded key, relative to the block start and 4 g
 #pragma unroll
     for (int r = 0; r < 32; ++r) {
       const int kr = 32 * (r >> 4) + 8 * ((r & 15) >> 2) + (r & 3);
       x[r] = kr < lim_rel ? x[r] : -INFINITY;
     }
   }
-  float mx = fmaxf(x[0], x[1]);
+  float mx4[4];
 #pragma unroll
-  for (int r = 2; r < 32; r += 2) mx = fmaxf(mx, fmaxf(x[r], x[r + 1]));
+  for (int i = 0; i < 4; ++i) {
+    mx4[i] = max3(x[i], x[4 + i], x[8 + i]);
+    mx4[i] = max3(mx4[i], x[12 + i], x[16 + i]);
+    mx4[i] = max3(mx4[i], x[20 + i], x[24 + i]);
+  }
+  mx4[0] = max3(mx4[0], x[28], x[29]);
+  mx4[1] = max3(mx4[1], x[30], x[31]);
+  const float mx = max3(mx4[0], mx4[1], max3(mx4[2], mx4[3], mx4[0]));
   const float mloc = halves_max(mx) * sc;
   const bool raise = mloc > st.m + RESCALE_SLACK;
   if (__builtin_amdgcn_ballot_w64(raise) != 0) {
@@ -255,26 +324,28 @@ __device__ __forceinline__ void fwd_block(FwdState<DH>& st, const TileOfs<DH, KB
     lsum += pr;
     pb[r >> 3][r & 7] = f2bf(pr);
   }
-  st.l += halves_sum(lsum);
+  st.l += lsum;
 #pragma unroll
   for (int kk = 0; kk < 4; ++kk) {
-    if (kk >= 2 && !two) break;
+    if (MASK && kk >= 2 && !two) break;
 #pragma unroll
     for (int ot = 0; ot < C::OT; ++ot)
-      st.o[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.trans(Vs, kk, ot), pb[kk], st.o[ot], 0, 0, 0);
+      st.o[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kk < PF ? vf[kk < PF ? kk : 0][ot] : to.trans(Vs, kk, ot),
+                                                         pb[kk], st.o[ot], 0, 0, 0);
   }
 }
 
-template <int DH>
-__global__ __launch_bounds__(NT, 2) void attn_small_fwd_kernel(AttnArgs a) {
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_small_fwd_kernel(AttnArgs a, int group) {
   using C = Cfg<DH>;
-  constexpr int TILE = KB * DH;
+  constexpr int TILE = KB * DH, WGR = NW * WR;
   __shared__ __attribute__((aligned(1024))) bf16 smem[2 * 2 * TILE];  // 2 stages x (K, V)
   const int S = a.S;
   const int nqb = (S + WGR - 1) / WGR;
-  // query blocks outermost; causal: heaviest block of every head first
+  // causal: heaviest block of every head first
   const int BH = a.B * a.H;
-  const int xb = (int)blockIdx.x / BH, bh = (int)blockIdx.x % BH;
+  int xb, bh;
+  if (!wg_item(BH, nqb, group, xb, bh)) return;
   const int qb = a.causal ? (nqb - 1 - xb) : xb;
   const int b = bh / a.H, h = bh % a.H;
   const int lane = threadIdx.x & 63;
@@ -297,35 +368,38 @@ __global__ __launch_bounds__(NT, 2) void attn_small_fwd_kernel(AttnArgs a) {
   const int kv_end = a.causal ? min(S, q0 + WGR) : S;
   const int nblk = (kv_end + KB - 1) / KB;
   // keys this wave's queries may see: [0, wk_end); this lane's: [0, lim)
-  const int wk_end = a.causal ? min(S, wq0 + WR) : S;
+  const int wk_end = wq0 >= S ? 0 : a.causal ? min(S, wq0 + WR) : S;
   const int lim = a.causal ? min(S, q + 1) : S;
-  const bool wave_live = wq0 < S;
+  // blocks that every query of the wave sees whole; the rest run the masked variant (two
+  // loops, not a branch in one: where the variants join, the accumulators
+  // would be copied on every block)
+  const int nfull = (wq0 >= S ? 0 : a.causal ? min(S, wq0 + 1) : S) / KB;
 
-  copy_tile<DH, KB>(rows_rsrc(Kb, 0), a.ldk, S, smem, wave);
-  copy_tile<DH, KB>(rows_rsrc(Vb, 0), a.ldv, S, smem + TILE, wave);
+  auto copy = [&](int j) {
+    bf16* dst = smem + (j & 1) * 2 * TILE;
+    copy_tile<DH, KB, NW>(rows_rsrc(Kb, (long)j * KB * a.ldk * 2), a.ldk, S - j * KB, dst, wave);
+    copy_tile<DH, KB, NW>(rows_rsrc(Vb, (long)j * KB * a.ldv * 2), a.ldv, S - j * KB, dst + TILE, wave);
+  };
+  copy(0);
   wait_vm_lgkm0<0>();
   cta_barrier();
-
-  for (int j = 0; j < nblk; ++j) {
+  int j = 0;
+  for (; j < nfull; ++j) {
+    const bf16* Ks = smem + (j & 1) * 2 * TILE;
+    if (j + 1 < nblk) copy(j + 1);
+    fwd_block<DH, false>(st, to, Ks, Ks + TILE, sc, true, 0);
+    wait_vm_lgkm0<0>();
+    cta_barrier();
+  }
+  for (; j < nblk; ++j) {
     const int kv0 = j * KB;
     const bf16* Ks = smem + (j & 1) * 2 * TILE;
-    bf16* nxt = smem + ((j + 1) & 1) * 2 * TILE;
-    if (j + 1 < nblk) {
-      copy_tile<DH, KB>(rows_rsrc(Kb, (long)(kv0 + KB) * a.ldk * 2), a.ldk, S - kv0 - KB, nxt, wave);
-      copy_tile<DH, KB>(rows_rsrc(Vb, (long)(kv0 + KB) * a.ldv * 2), a.ldv, S - kv0 - KB, nxt + TILE, wave);
-    }
-    if (wave_live && kv0 < wk_end) {
-      const int nk = min(KB, wk_end - kv0);
-      const bool two = nk > 32;
-      const bool mask = kv0 + KB > wk_end || (a.causal && kv0 + KB - 1 > wq0);
-      if (mask) fwd_block<DH, true>(st, to, Ks, Ks + TILE, sc, two, lim - kv0 - 4 * g);
-      else fwd_block<DH, false>(st, to, Ks, Ks + TILE, sc, two, lim - kv0 - 4 * g);
-    }
-    if (j + 1 < nblk) {
-      wait_vm_lgkm0<0>();
-      cta_barrier();
-    }
+    if (j + 1 < nblk) copy(j + 1);
+    if (kv0 < wk_end) fwd_block<DH, true>(st, to, Ks, Ks + TILE, sc, wk_end - kv0 > 32, lim - kv0 - 4 * g);
+    wait_vm_lgkm0<0>();
+    cta_barrier();
   }
+  st.l = halves_sum(st.l);
   if (q < S) {
     const float inv = (st.l > 0.f) ? 1.f / st.l : 0.f;
     store_rowT<DH>(a.o + ((long)b * S + q) * a.ldo + (long)h * DH, st.o, inv, g);
@@ -340,20 +414,76 @@ __global__ __launch_bounds__(NT, 2) void attn_small_fwd_kernel(AttnArgs a) {
 // key), P = exp2(S scale log2e - lse2), dS = P (dP - delta), then
 // dV^T += dO^T P and dK^T += Q^T dS with dO^T / Q^T from transposing reads.
 template <int DH>
-__global__ __launch_bounds__(NT, 2) void attn_small_dkdv_kernel(AttnBwdArgs a) {
+struct DkvState {
+  bf16x8 kf[Cfg<DH>::KS], vf[Cfg<DH>::KS];
+  floatx16 dk[Cfg<DH>::OT], dv[Cfg<DH>::OT];
+};
+
+// Sub-tile u (32 queries) of a staged block.  MASK: query rows acc_row(r, g) are
+// valid when acc_row - 4 g < lim_q and >= lim_k.
+template <int DH, bool MASK>
+__device__ __forceinline__ void dkdv_sub(DkvState<DH>& st, const TileOfs<DH, KB>& to, const bf16* Qs,
+                                         const bf16* dOs, const float* l2s, const float* dls, int u,
+                                         int g, float sc, int lim_q, int lim_k) {
   using C = Cfg<DH>;
-  constexpr int BQ = KB;
+  floatx16 x = zero16(), y = zero16();
+  {
+    bf16x8 k0[C::KS], k1[C::KS];
+#pragma unroll
+    for (int c = 0; c < C::KS; ++c) {
+      k0[c] = to.row(Qs, u, c);
+      k1[c] = to.row(dOs, u, c);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < C::KS; ++c) {
+      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.kf[c], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.vf[c], y, 0, 0, 0);
+    }
+  }
+  bf16x8 pb[2], db[2];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const floatx4 l4 = *reinterpret_cast<const floatx4*>(l2s + 32 * u + 8 * i + 4 * g);
+    const floatx4 d4 = *reinterpret_cast<const floatx4*>(dls + 32 * u + 8 * i + 4 * g);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 4 * i + e;
+      float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], sc, -l4[e]));
+      if (MASK) {
+        const int rr = 8 * i + e;  // acc_row - 4 g
+        pr = (rr < lim_q && rr >= lim_k) ? pr : 0.f;
+      }
+      pb[r >> 3][r & 7] = f2bf(pr);
+      db[r >> 3][r & 7] = f2bf(pr * (y[r] - d4[e]));
+    }
+  }
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int ot = 0; ot < C::OT; ++ot) {
+      st.dv[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.trans(dOs, 2 * u + hh, ot), pb[hh], st.dv[ot], 0, 0, 0);
+      st.dk[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.trans(Qs, 2 * u + hh, ot), db[hh], st.dk[ot], 0, 0, 0);
+    }
+}
+
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_small_dkdv_kernel(AttnBwdArgs a, int group) {
+  using C = Cfg<DH>;
+  constexpr int BQ = KB, WGR = NW * WR;
   constexpr int QT = BQ * DH;
   constexpr int STG = 2 * QT + 2 * 2 * BQ;  // Q, dO, lse2[64], delta[64]
   __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STG];
   const int S = a.f.S;
-  // key blocks outermost: with a causal mask the first keys see the most queries
+  // with a causal mask the first keys see the most queries
   const int BH = a.f.B * a.f.H;
-  const int bh = (int)blockIdx.x % BH, b = bh / a.f.H, h = bh % a.f.H;
+  int kblk, bh;
+  if (!wg_item(BH, (S + WGR - 1) / WGR, group, kblk, bh)) return;
+  const int b = bh / a.f.H, h = bh % a.f.H;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int g = lane >> 5;
-  const int k0 = ((int)blockIdx.x / BH) * WGR;
+  const int k0 = kblk * WGR;
   const int kmin = k0 + wave * WR;
   const int key = kmin + (lane & 31);
   const long hs = ((long)b * a.f.H + h) * S;
@@ -363,29 +493,27 @@ __global__ __launch_bounds__(NT, 2) void attn_small_dkdv_kernel(AttnBwdArgs a) {
   const bf16* dOb = a.dout + (long)b * S * a.lddo + (long)h * DH;
   const float sc = a.f.scale * LOG2E;
 
-  bf16x8 kf[C::KS], vf[C::KS];
-  load_rows<DH>(Kb, a.f.ldk, kmin, S - kmin, lane, kf);
-  load_rows<DH>(Vb, a.f.ldv, kmin, S - kmin, lane, vf);
-  floatx16 dk[C::OT], dv[C::OT];
+  DkvState<DH> st;
+  load_rows<DH>(Kb, a.f.ldk, kmin, S - kmin, lane, st.kf);
+  load_rows<DH>(Vb, a.f.ldv, kmin, S - kmin, lane, st.vf);
 #pragma unroll
   for (int t = 0; t < C::OT; ++t) {
-    dk[t] = zero16();
-    dv[t] = zero16();
+    st.dk[t] = zero16();
+    st.dv[t] = zero16();
   }
   TileOfs<DH, BQ> to;
   to.init(lane);
 
   const int q_start = a.f.causal ? k0 : 0;
   const int nqb = (S - q_start + BQ - 1) / BQ;
-  const bool wave_live = kmin < S;
   float lsd = 0.f;  // wave 0: lse of the next block's query `lane`; wave 1: its delta
 
   auto stage = [&](int j) { return smem + (j & 1) * STG; };
   auto fetch = [&](int j) {
     const int qs = q_start + j * BQ;
-    bf16* st = stage(j);
-    copy_tile<DH, BQ>(rows_rsrc(Qb, (long)qs * a.f.ldq * 2), a.f.ldq, S - qs, st, wave);
-    copy_tile<DH, BQ>(rows_rsrc(dOb, (long)qs * a.lddo * 2), a.lddo, S - qs, st + QT, wave);
+    bf16* sj = stage(j);
+    copy_tile<DH, BQ, NW>(rows_rsrc(Qb, (long)qs * a.f.ldq * 2), a.f.ldq, S - qs, sj, wave);
+    copy_tile<DH, BQ, NW>(rows_rsrc(dOb, (long)qs * a.lddo * 2), a.lddo, S - qs, sj + QT, wave);
     if (wave < 2) {
       const int qi = qs + lane;
       lsd = qi < S ? (wave ? a.delta[hs + qi] : a.f.lse[hs + qi]) : 0.f;
@@ -394,6 +522,26 @@ __global__ __launch_bounds__(NT, 2) void attn_small_dkdv_kernel(AttnBwdArgs a) {
   auto publish = [&](int j) {
     if (wave < 2) reinterpret_cast<float*>(stage(j) + 2 * QT)[wave * BQ + lane] = wave ? lsd : lsd * LOG2E;
   };
+  auto next = [&](int j) {
+    if (j + 1 < nqb) {
+      wait_vm_lgkm0<0>();
+      publish(j + 1);
+      wait_vm_lgkm0<0>();
+      cta_barrier();
+    }
+  };
+  // the masked variant of a block: sub-tiles without a valid pair are skipped
+  auto masked = [&](int j) {
+    const bf16* Qs = stage(j);
+    const float* l2s = reinterpret_cast<const float*>(Qs + 2 * QT);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int qs = q_start + j * BQ + 32 * u;
+      if (kmin >= S || qs >= S || (a.f.causal && qs + 31 < kmin)) continue;
+      dkdv_sub<DH, true>(st, to, Qs, Qs + QT, l2s, l2s + BQ, u, g, sc, S - qs - 4 * g,
+                         a.f.causal ? key - qs - 4 * g : -(1 << 30));
+    }
+  };
 
   fetch(0);
   wait_vm_lgkm0<0>();
@@ -401,61 +549,32 @@ __global__ __launch_bounds__(NT, 2) void attn_small_dkdv_kernel(AttnBwdArgs a) {
   wait_vm_lgkm0<0>();
   cta_barrier();
 
-  for (int j = 0; j < nqb; ++j) {
-    const int qs0 = q_start + j * BQ;
+  // blocks [j1, j2) hold only valid pairs for this wave: past the diagonal, short of S
+  // (loops of their own: a join of two variants would copy the accumulators)
+  const int j1 = a.f.causal ? min(nqb, (kmin + 31 - q_start + BQ - 1) / BQ) : 0;
+  const int j2 = kmin >= S ? j1 : max(j1, (S - q_start) / BQ);
+  int j = 0;
+  for (; j < j1; ++j) {
+    if (j + 1 < nqb) fetch(j + 1);
+    masked(j);
+    next(j);
+  }
+  for (; j < j2; ++j) {
     const bf16* Qs = stage(j);
-    const bf16* dOs = Qs + QT;
     const float* l2s = reinterpret_cast<const float*>(Qs + 2 * QT);
-    const float* dls = l2s + BQ;
     if (j + 1 < nqb) fetch(j + 1);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int qs = qs0 + 32 * u;
-      if (!wave_live || qs >= S || (a.f.causal && qs + 31 < kmin)) continue;
-      floatx16 x = zero16(), y = zero16();
-#pragma unroll
-      for (int c = 0; c < C::KS; ++c) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.row(Qs, u, c), kf[c], x, 0, 0, 0);
-#pragma unroll
-      for (int c = 0; c < C::KS; ++c) y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.row(dOs, u, c), vf[c], y, 0, 0, 0);
-      const bool mask = qs + 32 > S || (a.f.causal && qs < kmin + 31);
-      // query rows acc_row(r, g): valid when row < lim_q and (causal) row >= lim_k
-      const int lim_q = S - qs - 4 * g;
-      const int lim_k = a.f.causal ? key - qs - 4 * g : -(1 << 30);
-      bf16x8 pb[2], db[2];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const floatx4 l4 = *reinterpret_cast<const floatx4*>(l2s + 32 * u + 8 * i + 4 * g);
-        const floatx4 d4 = *reinterpret_cast<const floatx4*>(dls + 32 * u + 8 * i + 4 * g);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = 4 * i + e;
-          float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], sc, -l4[e]));
-          if (mask) {
-            const int rr = 8 * i + e;  // acc_row - 4 g
-            pr = (rr < lim_q && rr >= lim_k) ? pr : 0.f;
-          }
-          pb[r >> 3][r & 7] = f2bf(pr);
-          db[r >> 3][r & 7] = f2bf(pr * (y[r] - d4[e]));
-        }
-      }
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-        for (int ot = 0; ot < C::OT; ++ot) {
-          dv[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.trans(dOs, 2 * u + hh, ot), pb[hh], dv[ot], 0, 0, 0);
-          dk[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.trans(Qs, 2 * u + hh, ot), db[hh], dk[ot], 0, 0, 0);
-        }
-    }
-    if (j + 1 < nqb) {
-      wait_vm_lgkm0<0>();
-      publish(j + 1);
-      wait_vm_lgkm0<0>();
-      cta_barrier();
-    }
+    for (int u = 0; u < 2; ++u) { dkdv_sub<DH, false>(st, to, Qs, Qs + QT, l2s, l2s + BQ, u, g, sc, 0, 0); __builtin_amdgcn_sched_barrier(0); }
+    next(j);
+  }
+  for (; j < nqb; ++j) {
+    if (j + 1 < nqb) fetch(j + 1);
+    masked(j);
+    next(j);
   }
   if (key < S) {
-    store_rowT<DH>(a.dk + ((long)b * S + key) * a.lddk + (long)h * DH, dk, a.f.scale, g);
-    store_rowT<DH>(a.dv + ((long)b * S + key) * a.lddv + (long)h * DH, dv, 1.f, g);
+    store_rowT<DH>(a.dk + ((long)b * S + key) * a.lddk + (long)h * DH, st.dk, a.f.scale, g);
+    store_rowT<DH>(a.dv + ((long)b * S + key) * a.lddv + (long)h * DH, st.dv, 1.f, g);
   }
 }
 
@@ -467,14 +586,65 @@ __global__ __launch_bounds__(NT, 2) void attn_small_dkdv_kernel(AttnBwdArgs a) {
 // This kernel runs first and also computes delta = rowsum(dO * O) for the
 // dK / dV kernel.
 template <int DH>
-__global__ __launch_bounds__(NT, 2) void attn_small_dq_kernel(AttnBwdArgs a) {
+struct DqState {
+  bf16x8 qf[Cfg<DH>::KS], of[Cfg<DH>::KS];
+  floatx16 dq[Cfg<DH>::OT];
+  float nl2, dlt;  // -lse * log2 e and delta of this lane's query
+};
+
+// Sub-tile u (32 keys) of a staged block.  MASK: keys with acc_row - 4 g < lim_rel are valid.
+template <int DH, bool MASK>
+__device__ __forceinline__ void dq_sub(DqState<DH>& st, const TileOfs<DH, KB>& to, const bf16* Ks,
+                                       const bf16* Vs, int u, float sc, int lim_rel) {
   using C = Cfg<DH>;
-  constexpr int TILE = KB * DH;
+  floatx16 x = zero16(), y = zero16();
+  {
+    bf16x8 k0[C::KS], k1[C::KS];
+#pragma unroll
+    for (int c = 0; c < C::KS; ++c) {
+      k0[c] = to.row(Ks, u, c);
+      k1[c] = to.row(Vs, u, c);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int c = 0; c < C::KS; ++c) {
+      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.qf[c], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.of[c], y, 0, 0, 0);
+    }
+  }
+  bf16x8 kt[2][C::OT];
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int ot = 0; ot < C::OT; ++ot) kt[hh][ot] = to.trans(Ks, 2 * u + hh, ot);
+  __builtin_amdgcn_sched_barrier(0);
+  bf16x8 db[2];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], sc, st.nl2));
+    if (MASK) {
+      const int kr = 8 * (r >> 2) + (r & 3);
+      pr = kr < lim_rel ? pr : 0.f;
+    }
+    db[r >> 3][r & 7] = f2bf(pr * (y[r] - st.dlt));
+  }
+#pragma unroll
+  for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+    for (int ot = 0; ot < C::OT; ++ot)
+      st.dq[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kt[hh][ot], db[hh], st.dq[ot], 0, 0, 0);
+}
+
+template <int DH, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void attn_small_dq_kernel(AttnBwdArgs a, int group) {
+  using C = Cfg<DH>;
+  constexpr int TILE = KB * DH, WGR = NW * WR;
   __shared__ __attribute__((aligned(1024))) bf16 smem[2 * 2 * TILE];  // 2 stages x (K, V)
   const int S = a.f.S;
   const int nqb = (S + WGR - 1) / WGR;
   const int BH = a.f.B * a.f.H;
-  const int xb = (int)blockIdx.x / BH, bh = (int)blockIdx.x % BH;
+  int xb, bh;
+  if (!wg_item(BH, nqb, group, xb, bh)) return;
   const int qb = a.f.causal ? (nqb - 1 - xb) : xb;
   const int b = bh / a.f.H, h = bh % a.f.H;
   const int lane = threadIdx.x & 63;
@@ -488,12 +658,11 @@ __global__ __launch_bounds__(NT, 2) void attn_small_dq_kernel(AttnBwdArgs a) {
   const bf16* dOb = a.dout + (long)b * S * a.lddo + (long)h * DH;
   const float sc = a.f.scale * LOG2E;
 
-  bf16x8 qf[C::KS], of[C::KS];
-  load_rows<DH>(Qb, a.f.ldq, wq0, S - wq0, lane, qf);
-  load_rows<DH>(dOb, a.lddo, wq0, S - wq0, lane, of);
-  const float nl2 = q < S ? -a.f.lse[hs + q] * LOG2E : 0.f;
+  DqState<DH> st;
+  load_rows<DH>(Qb, a.f.ldq, wq0, S - wq0, lane, st.qf);
+  load_rows<DH>(dOb, a.lddo, wq0, S - wq0, lane, st.of);
+  st.nl2 = q < S ? -a.f.lse[hs + q] * LOG2E : 0.f;
   // delta = rowsum(dO * O) of this lane's query, from the two halves of its row
-  float dlt;
   {
     bf16x8 ov[C::KS];
     load_rows<DH>(a.f.o + (long)b * S * a.f.ldo + (long)h * DH, a.f.ldo, wq0, S - wq0, lane, ov);
@@ -501,75 +670,73 @@ __global__ __launch_bounds__(NT, 2) void attn_small_dq_kernel(AttnBwdArgs a) {
 #pragma unroll
     for (int c = 0; c < C::KS; ++c)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc = __builtin_fmaf(bf2f(of[c][e]), bf2f(ov[c][e]), acc);
-    dlt = halves_sum(acc);
-    if (g == 0 && q < S) a.delta[hs + q] = dlt;
+      for (int e = 0; e < 8; ++e) acc = __builtin_fmaf(bf2f(st.of[c][e]), bf2f(ov[c][e]), acc);
+    st.dlt = halves_sum(acc);
+    if (g == 0 && q < S) a.delta[hs + q] = st.dlt;
   }
-  floatx16 dq[C::OT];
 #pragma unroll
-  for (int t = 0; t < C::OT; ++t) dq[t] = zero16();
+  for (int t = 0; t < C::OT; ++t) st.dq[t] = zero16();
   TileOfs<DH, KB> to;
   to.init(lane);
 
   const int kv_end = a.f.causal ? min(S, q0 + WGR) : S;
   const int nkb = (kv_end + KB - 1) / KB;
-  const int wk_end = a.f.causal ? min(S, wq0 + WR) : S;
+  const int wk_end = wq0 >= S ? 0 : a.f.causal ? min(S, wq0 + WR) : S;
   const int lim = a.f.causal ? min(S, q + 1) : S;
-  const bool wave_live = wq0 < S;
+  const int nfull = (wq0 >= S ? 0 : a.f.causal ? min(S, wq0 + 1) : S) / KB;  // as in the forward
 
-  copy_tile<DH, KB>(rows_rsrc(Kb, 0), a.f.ldk, S, smem, wave);
-  copy_tile<DH, KB>(rows_rsrc(Vb, 0), a.f.ldv, S, smem + TILE, wave);
+  auto copy = [&](int j) {
+    bf16* dst = smem + (j & 1) * 2 * TILE;
+    copy_tile<DH, KB, NW>(rows_rsrc(Kb, (long)j * KB * a.f.ldk * 2), a.f.ldk, S - j * KB, dst, wave);
+    copy_tile<DH, KB, NW>(rows_rsrc(Vb, (long)j * KB * a.f.ldv * 2), a.f.ldv, S - j * KB, dst + TILE, wave);
+  };
+  copy(0);
   wait_vm_lgkm0<0>();
   cta_barrier();
-
-  for (int j = 0; j < nkb; ++j) {
-    const int kv0 = j * KB;
+  int j = 0;
+  for (; j < nfull; ++j) {
     const bf16* Ks = smem + (j & 1) * 2 * TILE;
-    const bf16* Vs = Ks + TILE;
-    bf16* nxt = smem + ((j + 1) & 1) * 2 * TILE;
-    if (j + 1 < nkb) {
-      copy_tile<DH, KB>(rows_rsrc(Kb, (long)(kv0 + KB) * a.f.ldk * 2), a.f.ldk, S - kv0 - KB, nxt, wave);
-      copy_tile<DH, KB>(rows_rsrc(Vb, (long)(kv0 + KB) * a.f.ldv * 2), a.f.ldv, S - kv0 - KB, nxt + TILE, wave);
-    }
+    if (j + 1 < nkb) copy(j + 1);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) { dq_sub<DH, false>(st, to, Ks, Ks + TILE, u, sc, 0); __builtin_amdgcn_sched_barrier(0); }
+    wait_vm_lgkm0<0>();
+    cta_barrier();
+  }
+  for (; j < nkb; ++j) {
+    const bf16* Ks = smem + (j & 1) * 2 * TILE;
+    if (j + 1 < nkb) copy(j + 1);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const int kv = kv0 + 32 * u;
-      if (!wave_live || kv >= wk_end) continue;
-      floatx16 x = zero16(), y = zero16();
-#pragma unroll
-      for (int c = 0; c < C::KS; ++c) x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.row(Ks, u, c), qf[c], x, 0, 0, 0);
-#pragma unroll
-      for (int c = 0; c < C::KS; ++c) y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.row(Vs, u, c), of[c], y, 0, 0, 0);
-      const bool mask = kv + 32 > wk_end || (a.f.causal && kv + 31 > wq0);
-      const int lim_rel = lim - kv - 4 * g;  // keys with acc_row - 4 g < lim_rel are valid
-      bf16x8 db[2];
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(x[r], sc, nl2));
-        if (mask) {
-          const int kr = 8 * (r >> 2) + (r & 3);
-          pr = kr < lim_rel ? pr : 0.f;
-        }
-        db[r >> 3][r & 7] = f2bf(pr * (y[r] - dlt));
-      }
-#pragma unroll
-      for (int hh = 0; hh < 2; ++hh)
-#pragma unroll
-        for (int ot = 0; ot < C::OT; ++ot)
-          dq[ot] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(to.trans(Ks, 2 * u + hh, ot), db[hh], dq[ot], 0, 0, 0);
+      const int kv = j * KB + 32 * u;
+      if (kv < wk_end) dq_sub<DH, true>(st, to, Ks, Ks + TILE, u, sc, lim - kv - 4 * g);
     }
-    if (j + 1 < nkb) {
-      wait_vm_lgkm0<0>();
-      cta_barrier();
-    }
+    wait_vm_lgkm0<0>();
+    cta_barrier();
   }
-  if (q < S) store_rowT<DH>(a.dq + ((long)b * S + q) * a.lddq + (long)h * DH, dq, a.f.scale, g);
+  if (q < S) store_rowT<DH>(a.dq + ((long)b * S + q) * a.lddq + (long)h * DH, st.dq, a.f.scale, g);
+}
+
+// Staged operand bytes of the heads an XCD works on at a time, of its 4 MB L2.
+// Causal blocks differ in work: a larger group balances them better (96 heads of
+// 1024 x 64, 3 MB per XCD: forward 28 us as one group, 33 us as 10 + 2 heads).
+inline long l2_group(bool causal) { return causal ? 9L << 19 : 3L << 19; }
+
+// Waves (of 32 rows) per workgroup.  Four, which share the staged blocks of the
+// other operand; fewer where that leaves wave slots or CUs idle: in the forward
+// three when the rows then fill the last workgroup better (257 rows are 9 wave
+// tiles: three workgroups either way, of 9 waves instead of 12; 64 x 16 heads 58 ->
+// 56 us; the backward, at two waves per SIMD either way, took 185 -> 196), two
+// when four give fewer than 192 workgroups.
+int waves_per_wg(int S, long BH, bool fwd) {
+  const int tiles = (S + WR - 1) / WR;
+  if ((long)((tiles + 3) / 4) * BH < 192) return 2;
+  return fwd && (tiles + 2) / 3 * 3 < (tiles + 3) / 4 * 4 ? 3 : 4;
 }
 
 bool ok16(const void* p, long ld) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0 && ld % 8 == 0; }
 bool ok8(const void* p, long ld) { return (reinterpret_cast<uintptr_t>(p) & 7) == 0 && ld % 4 == 0; }
-// byte offsets of a 128-row block stay below 2^31
-bool rows_fit(long ld) { return (long)WGR * ld * 2 < (1L << 30); }
+// byte offsets of a staged block and of a wave's rows stay below 2^31
+bool rows_fit(long ld) { return 128 * ld * 2 < (1L << 30); }
 
 }  // namespace
 
@@ -584,21 +751,31 @@ bool attn_small_bwd_eligible(const AttnBwdArgs& a) {
          ok8(a.dk, a.lddk) && ok8(a.dv, a.lddv);
 }
 
+#define SMALL_LAUNCH(KERNEL, DH, args, f, fwd)                                                          \
+  do {                                                                                             \
+    const int BH_ = (f).B * (f).H, hx_ = (BH_ + 7) / 8;                                            \
+    const int nw_ = waves_per_wg((f).S, BH_, fwd);                                                      \
+    const long nb_ = sat_cdiv((f).S, nw_ * WR);                                                    \
+    const int group_ = (int)std::max(1L, std::min((long)hx_, l2_group((f).causal) / (4L * (f).S * DH)));       \
+    const dim3 grid_((unsigned)(nb_ * (BH_ < 64 ? BH_ : 8 * hx_)));                                \
+    if (nw_ == 2) hipLaunchKernelGGL((KERNEL<DH, 2>), grid_, dim3(128), 0, s, args, group_);       \
+    else if (nw_ == 3) hipLaunchKernelGGL((KERNEL<DH, 3>), grid_, dim3(192), 0, s, args, group_);  \
+    else hipLaunchKernelGGL((KERNEL<DH, 4>), grid_, dim3(256), 0, s, args, group_);                \
+  } while (0)
+
 hipError_t launch_attn_small_fwd(const AttnArgs& a, hipStream_t s) {
-  dim3 grid((unsigned)(((a.S + WGR - 1) / WGR) * a.B * a.H));
-  if (a.dh == 64) hipLaunchKernelGGL(attn_small_fwd_kernel<64>, grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL(attn_small_fwd_kernel<80>, grid, dim3(NT), 0, s, a);
+  if (a.dh == 64) SMALL_LAUNCH(attn_small_fwd_kernel, 64, a, a, true);
+  else SMALL_LAUNCH(attn_small_fwd_kernel, 80, a, a, true);
   return hipGetLastError();
 }
 
 // dQ (which also writes delta), then dK / dV.
 hipError_t launch_attn_small_bwd(const AttnBwdArgs& a, hipStream_t s) {
-  dim3 grid((unsigned)(((a.f.S + WGR - 1) / WGR) * a.f.B * a.f.H));
-  if (a.f.dh == 64) hipLaunchKernelGGL(attn_small_dq_kernel<64>, grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL(attn_small_dq_kernel<80>, grid, dim3(NT), 0, s, a);
+  if (a.f.dh == 64) SMALL_LAUNCH(attn_small_dq_kernel, 64, a, a.f, false);
+  else SMALL_LAUNCH(attn_small_dq_kernel, 80, a, a.f, false);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (a.f.dh == 64) hipLaunchKernelGGL(attn_small_dkdv_kernel<64>, grid, dim3(NT), 0, s, a);
-  else hipLaunchKernelGGL(attn_small_dkdv_kernel<80>, grid, dim3(NT), 0, s, a);
+  if (a.f.dh == 64) SMALL_LAUNCH(attn_small_dkdv_kernel, 64, a, a.f, false);
+  else SMALL_LAUNCH(attn_small_dkdv_kernel, 80, a, a.f, false);
   return hipGetLastError();
 }

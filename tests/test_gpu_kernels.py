@@ -151,6 +151,15 @@ def test_attention_fwd_bwd(B, H, S, dh, causal):
         assert err <= 2e-2 * max(np.linalg.norm(ref), floor), (part, err, np.linalg.norm(ref))
 
 
+# 64- and 80-wide heads dealt to the XCDs in groups (64 heads or more, not a multiple of
+# 8: workgroups without a head) and two, three (9 and 3 wave tiles) and four waves per workgroup.
+@pytest.mark.parametrize("B,H,S,dh,causal", [(6, 11, 130, 80, False), (3, 22, 290, 64, True), (65, 1, 33, 80, True),
+                                             (66, 1, 257, 80, False), (13, 15, 65, 64, False),
+                                             (50, 2, 250, 64, False), (25, 4, 255, 80, True)])
+def test_attention_small_heads_grid(B, H, S, dh, causal):
+    test_attention_fwd_bwd(B, H, S, dh, causal)
+
+
 # Attention at the full per-layer shapes the step launches (GPT-J, GPT-2-small,
 # ViT-H/14, a grid member at batch 16), checked on sampled heads (the first
 # and the last (batch, head) plus one in between) against the oracle.
