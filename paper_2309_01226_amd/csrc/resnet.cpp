@@ -9,8 +9,10 @@
 // a stride-2 1 x 1 projection the every-other-pixel subsample.  Its input
 // gradient is one GEMM against the transposed bf16 weight copy, scattered
 // back by col2im where the convolution is not 1 x 1; its weight gradient is
-// one GEMM over the pixels (K = N H W) on token-contiguous copies of both
-// operands, split over K so that the few output tiles still fill the chip.
+// one GEMM over the pixels (K = N H W) on the row-major operands, split over K
+// so that the few output tiles still fill the chip (pixel-contiguous copies of both
+// operands for the 256 x 256 kernel cost more than they gave: 12 blocks at batch 64,
+// 21.0 ms per step with them, 19.5 without).
 // Batch norm runs in training mode: statistics of the batch, then a fused
 // normalise (+ ReLU, + shortcut add) pass; its backward reduces the two
 // per-channel sums, then applies the closed-form input gradient.
@@ -83,8 +85,6 @@ struct ResNetPlan {
   float* dsub = nullptr;
   bf16* dc = nullptr;
   bf16* dcd = nullptr;
-  bf16* tA = nullptr;
-  bf16* tB = nullptr;
   float* part = nullptr;
   float* dfeat = nullptr;
 };
@@ -336,8 +336,6 @@ void sat_resnet_carve(sat_model* M, SatCarver& c) {
   R.dcol = c.take<float>(std::max(dcol, 8L));
   R.dc = c.take<bf16>(maxPC);
   R.dcd = c.take<bf16>(maxPC);
-  R.tA = c.take<bf16>(maxPC);
-  R.tB = c.take<bf16>(std::max(col, maxPC));
   R.dfeat = c.take<float>((long)R.N * R.F);
   // column sums of the head bias gradient use the same partial buffer
   part = std::max(part, 2L * std::min(R.N, 256) * R.Vp);
@@ -401,36 +399,18 @@ sat_status conv_gemm(sat_model* M, const bf16* A, long lda, int w, long P, int c
   return gemm(M, a, LAY_K, LAY_K, EPI_F32, tk);
 }
 
-// Weight gradient [cout, ncols] = dY^T X over P pixels (dY [P, cout] bf16;
-// X [P, >= ncols] bf16 with row pitch ldx): on token-contiguous copies of both
-// operands (xcols columns of X transposed) so the product splits K, else
-// straight on the row-major operands.
-sat_status rwgrad(sat_model* M, const bf16* dY, int cout, const bf16* X, long ldx, int ncols,
-                  int xcols, long P, float* out) {
-  ResNetPlan& R = *M->rn;
-  if (P % 8 == 0 && cout % 8 == 0 && xcols % 8 == 0 && ldx % 8 == 0) {
-    SAT_HIP(launch_transpose_bf16(dY, cout, R.tA, P, (int)P, cout, M->stream));
-    SAT_HIP(launch_transpose_bf16(X, ldx, R.tB, P, (int)P, xcols, M->stream));
-    GemmArgs w = gargs(R.tA, P, R.tB, P, cout, ncols, (int)P, out, ncols);
-    w.splitk_max = kSplitMax;
-    return gemm(M, w, LAY_K, LAY_K, EPI_F32);
-  }
+// Weight gradient [cout, ncols] = dY^T X over P pixels (dY [P, cout] bf16; X
+// [P, >= ncols] bf16 with row pitch ldx), straight on the row-major operands
+// (read with the transposing LDS read), split over the pixels.
+sat_status rwgrad(sat_model* M, const bf16* dY, int cout, const bf16* X, long ldx, int ncols, long P,
+                  float* out) {
   GemmArgs w = gargs(dY, cout, X, ldx, cout, ncols, (int)P, out, ncols);
+  w.splitk_max = kSplitMax;
   return gemm(M, w, LAY_MN, LAY_MN, EPI_F32);
 }
 
 // dX [P, n] fp32 = dY [P, cout] (bf16) times weight w [cout, n] (through its
 // transposed copy); resid (may equal out) is added when not null.
-// The same with X already token-contiguous: XT [ncols, P] (row stride P).
-sat_status rwgrad_t(sat_model* M, const bf16* dY, int cout, const bf16* XT, int ncols, long P,
-                    float* out) {
-  ResNetPlan& R = *M->rn;
-  SAT_HIP(launch_transpose_bf16(dY, cout, R.tA, P, (int)P, cout, M->stream));
-  GemmArgs w = gargs(R.tA, P, XT, P, cout, ncols, (int)P, out, ncols);
-  w.splitk_max = kSplitMax;
-  return gemm(M, w, LAY_K, LAY_K, EPI_F32);
-}
-
 sat_status dgrad(sat_model* M, const bf16* dY, int cout, int w, long P, int n, float* out,
                  const float* resid) {
   const ParamDesc& p = M->params[w];
@@ -543,7 +523,7 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
                             b.cout, R.part, grad(M, b.nd.g), grad(M, b.nd.g + 1), R.dcd, s));
     // conv3 (1 x 1)
     TRY(dgrad(M, R.dc, b.cout, b.w3, b.Pout, b.mid, R.da, nullptr));
-    TRY(rwgrad(M, R.dc, b.cout, b.a2, b.mid, b.mid, b.mid, b.Pout, grad(M, b.w3)));
+    TRY(rwgrad(M, R.dc, b.cout, b.a2, b.mid, b.mid, b.Pout, grad(M, b.w3)));
     SAT_HIP(launch_bn_bwd(R.da, 1, b.a2, b.c2, b.n2.mean, b.n2.rstd, gam(M, b.n2), b.Pout, b.mid,
                           R.part, grad(M, b.n2.g), grad(M, b.n2.g + 1), R.dc, s));
     // conv2 (3 x 3, the block's stride): input gradient through col2im, weight
@@ -551,41 +531,26 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
     TRY(dgrad(M, R.dc, b.mid, b.w2, b.Pout, 9 * b.mid, R.dcol, nullptr));
     SAT_HIP(launch_col2im(R.dcol, 9L * b.mid, R.da, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
                           0, s));
-    // (the im2col matrix written token-contiguous when the shapes allow)
-    if (b.Pout % 8 == 0 && b.mid % 8 == 0) {
-      SAT_HIP(launch_im2col_t(b.a1, R.tB, b.Pout, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo, s));
-      TRY(rwgrad_t(M, R.dc, b.mid, R.tB, 9 * b.mid, b.Pout, grad(M, b.w2)));
-    } else {
-      SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
-                            s));
-      TRY(rwgrad(M, R.dc, b.mid, R.col, 9L * b.mid, 9 * b.mid, 9 * b.mid, b.Pout, grad(M, b.w2)));
-    }
+    SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo, s));
+    TRY(rwgrad(M, R.dc, b.mid, R.col, 9L * b.mid, 9 * b.mid, b.Pout, grad(M, b.w2)));
     SAT_HIP(launch_bn_bwd(R.da, 1, b.a1, b.c1, b.n1.mean, b.n1.rstd, gam(M, b.n1), b.Pin, b.mid,
                           R.part, grad(M, b.n1.g), grad(M, b.n1.g + 1), R.dc, s));
     // conv1 (1 x 1) and the shortcut; the input gradient only when something
     // below this block trains
     const bool need_dx = i > k || k == 0;
     if (need_dx) TRY(dgrad(M, R.dc, b.mid, b.w1, b.Pin, b.cin, dx, b.proj ? nullptr : R.gdo));
-    TRY(rwgrad(M, R.dc, b.mid, R.xb[i], b.cin, b.cin, b.cin, b.Pin, grad(M, b.w1)));
+    TRY(rwgrad(M, R.dc, b.mid, R.xb[i], b.cin, b.cin, b.Pin, grad(M, b.w1)));
     if (b.proj) {
       if (b.stride != 1) {
         if (need_dx) {
           TRY(dgrad(M, R.dcd, b.cout, b.wd, b.Pout, b.cin, R.dsub, nullptr));
           SAT_HIP(launch_stride2_add(R.dsub, R.N, b.Ho, b.Wo, b.cin, b.H, b.W, dx, s));
         }
-        // the every-other-pixel subsample, token-contiguous when the shapes allow
-        if (b.Pout % 8 == 0 && b.cin % 8 == 0) {
-          SAT_HIP(launch_im2col_t(R.xb[i], R.tB, b.Pout, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho,
-                                  b.Wo, s));
-          TRY(rwgrad_t(M, R.dcd, b.cout, R.tB, b.cin, b.Pout, grad(M, b.wd)));
-        } else {
-          SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho,
-                                b.Wo, s));
-          TRY(rwgrad(M, R.dcd, b.cout, R.col, b.cin, b.cin, b.cin, b.Pout, grad(M, b.wd)));
-        }
+        SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho, b.Wo, s));
+        TRY(rwgrad(M, R.dcd, b.cout, R.col, b.cin, b.cin, b.Pout, grad(M, b.wd)));
       } else {
         if (need_dx) TRY(dgrad(M, R.dcd, b.cout, b.wd, b.Pout, b.cin, dx, dx));
-        TRY(rwgrad(M, R.dcd, b.cout, R.xb[i], b.cin, b.cin, b.cin, b.Pout, grad(M, b.wd)));
+        TRY(rwgrad(M, R.dcd, b.cout, R.xb[i], b.cin, b.cin, b.Pout, grad(M, b.wd)));
       }
     }
     std::swap(dy, dx);
@@ -599,7 +564,7 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
                              R.Hs, R.Hs, s));
   // over the zero-padded columns (whole 4-column output vectors, so the
   // product splits K), then the 7 x 7 x C columns into the gradient arena
-  TRY(rwgrad(M, R.dc, R.width, R.col, R.stem_kp, R.stem_kp, R.stem_kp, R.Ps, R.dsub));
+  TRY(rwgrad(M, R.dc, R.width, R.col, R.stem_kp, R.stem_kp, R.Ps, R.dsub));
   SAT_HIP(hipMemcpy2DAsync(grad(M, R.stem_w), (size_t)49 * R.C * 4, R.dsub, (size_t)R.stem_kp * 4,
                            (size_t)49 * R.C * 4, R.width, hipMemcpyDeviceToDevice, s));
   return SAT_OK;

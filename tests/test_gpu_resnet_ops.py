@@ -143,3 +143,9 @@ def test_maxpool(N, H, W, C):
         assert np.array_equal(host(y), ry.reshape(-1, C))
         assert np.array_equal(arg.cpu().numpy().astype(np.int64), cache[1].reshape(-1, C))
         assert rel(host(dx), OR.maxpool_bwd(dy.astype(np.float64), cache).reshape(-1, C)) < 1e-6
+
+
+@pytest.mark.parametrize("N,H,W,C", [(2, 7, 9, 6), (1, 3, 2, 1), (2, 5, 8, 12)])
+def test_maxpool_channel_tails(N, H, W, C):
+    """One channel per thread where C % 4 != 0, four otherwise; odd and even sides."""
+    test_maxpool(N, H, W, C)
