@@ -196,8 +196,10 @@ sat_status sat_model_stats(const sat_model* m, int64_t* n_params, int64_t* n_tra
  *   alternating sets, and the step joins that stream back into the model's
  *   stream before the backward ends, so a caller that synchronizes the
  *   model's stream sees the whole step.  Results are bitwise those with 0
- *   (the same kernels on the same operands).  Needs batch * seq_len % 8 == 0
- *   (otherwise ignored).
+ *   (the same kernels on the same operands).  Applies to models with a block
+ *   weight whose AdamW step can be fused (SAT_OPT_FUSED_ADAMW: wide models)
+ *   and batch * seq_len % 8 == 0; the others' products read the row-major
+ *   tensors on the model's stream (otherwise ignored).
  * value is 0 or 1; the setting applies from the next train step.
  * Errors: SAT_EINVAL (null model, unknown option or value), SAT_ESTATE. */
 typedef enum {

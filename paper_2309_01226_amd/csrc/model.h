@@ -167,12 +167,18 @@ struct sat_model {
   bf16* du;
   bf16* dout;
   // Token-contiguous (transposed) copies of the operands of the weight-gradient
-  // products dW = dY^T X: tA holds dY^T, tB holds X^T (null when the token
-  // count is not a multiple of 8; those products then read the row-major copies).
+  // products dW = dY^T X: tA holds dY^T, tB holds X^T.  They serve models with a
+  // weight whose AdamW step is fused into its product (fused_opt: at least 256
+  // tiles of 256 x 256), when the token count is a multiple of 8.  The other
+  // models' products read the row-major tensors through the tile kernels'
+  // transposing LDS reads, on the model's stream: without the copies, two
+  // streams gain nothing (GPT-2-small: 14.65 ms per step with copies and the second
+  // stream, 13.98 without either; 8 ViT-H blocks 25.7 and 24.6 ms; the tiny
+  // decoder 0.43 and 0.24 ms).
   bf16* tA;
   bf16* tB;
-  bool trans_blocks;  // tA / tB serve the blocks (T % 8 == 0)
-  bool trans_head;    // ... and the head (rows_head % 8 == 0)
+  bool trans_blocks;  // tA / tB (and the two operand sets) serve the blocks
+  bool trans_head;    // ... and tA / tB the head
   // split-K workspace of the fp32-output products with too few tiles
   float* splitk_ws;
   long splitk_ws_elems;

@@ -225,7 +225,8 @@ sat_status sat_run_forward(sat_model* M, const void* inputs, const int32_t* labe
 // dW[Mr, N] = sum over the T rows of Y[t, m] X[t, n] (Y, X bf16 row-major).
 // With token-contiguous scratch (trans), both operands are first transposed
 // into it (ycols >= Mr: the transposed width of Y, a multiple of 8), so the
-// product reads K-contiguous operands; y_ready: tA already holds Y^T.
+// product reads K-contiguous operands; y_ready: tA already holds Y^T.  Without,
+// the product reads the row-major operands.
 // pidx: the weight's parameter index.  When its AdamW step is fused, the
 // product's epilogue applies the step to the weight (and writes the gradient
 // only if the model keeps gradients).
