@@ -31,6 +31,12 @@ CASES = {
                       seq_len=40, batch=2, rotary_dim=16, lr=1e-3, checkpoint=1),
     "gpt2_splitk": dict(arch="gpt2", n_layers=2, d_model=256, n_heads=4, d_mlp=1024, vocab=512,
                         seq_len=1024, batch=2, lr=1e-3),
+    # wide enough that a block weight's AdamW step is fused into its product (8192 x 2048:
+    # 256 tiles), so the products run on the second stream; the other weights' split K
+    "gpt2_wide": dict(arch="gpt2", n_layers=3, d_model=2048, n_heads=16, d_mlp=8192, vocab=64,
+                      seq_len=64, batch=2, lr=1e-3, frozen_layers=1),
+    "gptj_wide_ckpt": dict(arch="gptj", n_layers=2, d_model=2048, n_heads=8, d_mlp=8192, vocab=64,
+                           seq_len=64, batch=2, rotary_dim=16, lr=1e-3, checkpoint=1),
     # every block weight's AdamW step fused into its weight-gradient product
     "gptj_fused": dict(arch="gptj", n_layers=2, d_model=2048, n_heads=8, d_mlp=8192, vocab=8200,
                        seq_len=2048, batch=2, rotary_dim=64, lr=1e-3),
@@ -74,7 +80,7 @@ def test_overlap_bitwise_equal(name):
     b.close()
 
 
-@pytest.mark.parametrize("name", ["gptj", "gpt2_splitk"])
+@pytest.mark.parametrize("name", ["gptj", "gpt2_splitk", "gpt2_wide"])
 def test_overlap_gradients_and_separate_adamw(name):
     """Kept gradients (fused step) and the separate AdamW pass: gradients and
     parameters bitwise equal with and without the second stream."""
@@ -98,7 +104,7 @@ def test_overlap_two_models_on_their_own_streams():
     """Two models with second streams stepping at once (as the grid runs
     them) match their serial twins."""
     from paper_2309_01226_amd.model import Model, device_batch
-    kws = [CASES["gptj"], dict(CASES["gpt2"], lr=3e-4)]
+    kws = [CASES["gptj_wide_ckpt"], dict(CASES["gpt2"], lr=3e-4), CASES["gpt2_wide"]]
     streams = [torch.cuda.Stream() for _ in kws]
     conc = [Model(kw, stream=s) for kw, s in zip(kws, streams)]
     ser = [Model(kw) for kw in kws]
