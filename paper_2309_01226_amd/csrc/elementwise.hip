@@ -120,15 +120,19 @@ __global__ void embed_fwd_kernel(const int32_t* __restrict__ tok, const float* _
 // Sorts the keys (token << 15 | position) of T <= 16384 tokens: a stable radix
 // sort by the token's low `bits` bits, four at a time, in LDS (one workgroup; the
 // positions start in order, so equal tokens keep theirs).  A thread owns
-// ceil(T / 1024) consecutive keys and one column of 16 counters per pass.
+// ceil(T / TH) consecutive keys and one column of 16 counters per pass; up to
+// 1024 tokens take one wave (64 tokens of 9 bits: 8.6 us with 1024 threads,
+// 5.1 with one wave).
 // Latency-bound (one CU): 8192 tokens of 16 bits 26 us, where a bitonic network
 // over the whole keys took 102.
 // Longer inputs are processed in chunks of this many positions.
 constexpr int EMB_MAXT = 16384;
-__global__ __launch_bounds__(1024) void embed_sort_kernel(const int32_t* __restrict__ tok, int T,
-                                                          int32_t* __restrict__ sorted, int bits) {
-  constexpr int TH = 1024, IMAX = EMB_MAXT / TH;
-  __shared__ uint32_t key[EMB_MAXT];
+template <int TH>
+__global__ __launch_bounds__(TH) void embed_sort_kernel(const int32_t* __restrict__ tok, int T,
+                                                        int32_t* __restrict__ sorted, int bits) {
+  constexpr int IMAX = 16;
+  static_assert(IMAX * 1024 == EMB_MAXT, "keys per thread");
+  __shared__ uint32_t key[IMAX * TH];
   __shared__ __attribute__((aligned(16))) uint16_t cnt[16 * TH];  // [digit][thread]
   __shared__ uint32_t wsum[TH / 64];
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
@@ -693,7 +697,10 @@ hipError_t launch_embed_bwd(const int32_t* tok, const float* dh, float* dwte, in
   const dim3 grid(sat_cdiv(V, EMB_ROWS), sat_cdiv(d, 1024));
   for (int t0 = 0; t0 < T; t0 += EMB_MAXT) {
     const int n = T - t0 < EMB_MAXT ? T - t0 : EMB_MAXT;
-    hipLaunchKernelGGL(embed_sort_kernel, dim3(1), dim3(1024), 0, s, tok + t0, n, work, bits);
+    if (n <= 1024)
+      hipLaunchKernelGGL(embed_sort_kernel<64>, dim3(1), dim3(64), 0, s, tok + t0, n, work, bits);
+    else
+      hipLaunchKernelGGL(embed_sort_kernel<1024>, dim3(1), dim3(1024), 0, s, tok + t0, n, work, bits);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float* dhc = dh + (long)t0 * d;

@@ -334,8 +334,11 @@ __device__ __forceinline__ bool epilogue_vec(const GemmArgs& p) {
 // contiguous range of the tile order and tiles ordered in groups of 8
 // tile-rows.  With split-K the grid is (slice, tile) pairs, slice-major: the
 // arguments are narrowed to the slice's K range and output block.
+// kb: first k of the slice (gathered operands keep their pointers).
+constexpr int LAY_TAPS = 2;  // A gathered per ConvTaps, B K-contiguous within a tap
 template <int BT, int ALAY, int BLAY>
-__device__ __forceinline__ void tile_setup(GemmArgs& p, int& m0, int& n0) {
+__device__ __forceinline__ void tile_setup(GemmArgs& p, int& m0, int& n0, int& kb) {
+  kb = 0;
   const int tiles_m = (p.M + BT - 1) / BT, tiles_n = (p.N + BT - 1) / BT;
   const int nwg = gridDim.x;
   int bid = blockIdx.x;
@@ -343,9 +346,11 @@ __device__ __forceinline__ void tile_setup(GemmArgs& p, int& m0, int& n0) {
   if (p.splitk > 1) {
     const int split = bid / (tiles_m * tiles_n);
     bid -= split * tiles_m * tiles_n;
-    const int kb = split * p.splitk_kc;
-    p.A += ALAY == LAY_K ? (long)kb : (long)kb * p.lda;
-    p.B += BLAY == LAY_K ? (long)kb : (long)kb * p.ldb;
+    kb = split * p.splitk_kc;
+    if (ALAY != LAY_TAPS) {
+      p.A += ALAY == LAY_K ? (long)kb : (long)kb * p.lda;
+      p.B += BLAY == LAY_K ? (long)kb : (long)kb * p.ldb;
+    }
     p.K = min(p.splitk_kc, p.K - kb);
     p.out = reinterpret_cast<float*>(p.out) + split * p.split_stride;
   }
@@ -367,8 +372,8 @@ __global__ __launch_bounds__(NT) void gemm_kernel_simple(GemmArgs p) {
   constexpr int STAGE = 2 * BT * BK;  // bf16 elements per stage
   __shared__ __attribute__((aligned(1024))) bf16 smem[2 * STAGE];
 
-  int m0, n0;
-  tile_setup<BT, ALAY, BLAY>(p, m0, n0);
+  int m0, n0, kb;
+  tile_setup<BT, ALAY, BLAY>(p, m0, n0, kb);
   const int K = p.K;
 
   const int lane = threadIdx.x & 63;
@@ -478,10 +483,9 @@ struct TileOp {
       fr[0] = k * BT + 8 * (c ^ swz_mn(k)) + 4 * (ll & 1);
     }
   }
-  // G: the operand at (tile row 0, k = 0)
-  __device__ __forceinline__ void copy(const bf16* G, long ld, int k0, int K, bf16* __restrict__ S,
-                                       int wave) const {
-    __amdgpu_buffer_rsrc_t rs = make_rsrc(G + (LAY == LAY_K ? (long)k0 : (long)k0 * ld));
+  // src: the operand at (tile row 0, k = k0)
+  __device__ __forceinline__ void copy(const bf16* src, int k0, int K, bf16* __restrict__ S, int wave) const {
+    __amdgpu_buffer_rsrc_t rs = make_rsrc(src);
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const uint32_t o = k0 + kof[i] < K ? off[i] : OOB;
@@ -506,6 +510,59 @@ struct TileOp {
   __device__ __forceinline__ static int hi4(int o) { return o + 4 * BT; }
 };
 
+// The gathered operand (a 3 x 3 convolution without its im2col matrix, which held the
+// input nine times, and without the nine-fold fp32 column gradient of the input
+// gradient): 12 ResNet blocks at batch 64, 19.9 ms per step through the matrices,
+// 18.3 gathered; 12544 x 512 x 4608: 79 us where im2col and product took 33 + 67.
+// The K-contiguous tile layout and fragments, each copied
+// 16-byte piece from its pixel's place in the tensor.  A K-tile lies in one tap, so
+// a copy adds one uniform offset per tap and checks the pixel's coordinates.
+template <int BT>
+struct TileOp<LAY_TAPS, BT> : TileOp<LAY_K, BT> {
+  using Base = TileOp<LAY_K, BT>;
+  int hw[Base::NI];  // h0 (low 16 bits) and w0 of this lane's row; far outside past M
+  int a, b, c0;      // tap and first channel of the next K-tile
+  __device__ __forceinline__ void init_taps(const GemmArgs& p, int m0, int kb, int wave, int w0) {
+    Base::init(0, 0, wave, w0);  // fragment offsets
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int i = 0; i < Base::NI; ++i) {
+      const int row = (i * 4 + wave) * 8 + (lane >> 3);
+      const int m = m0 + row;
+      const int j = m % p.cv.oW, q = m / p.cv.oW;
+      const int h0 = q % p.cv.oH * p.cv.stride + p.cv.org, v0 = j * p.cv.stride + p.cv.org;
+      const int n = q / p.cv.oH;
+      Base::off[i] = (uint32_t)((((n * p.cv.H + h0) * p.cv.W + v0) * p.cv.C + Base::kof[i]) * 2);
+      hw[i] = m < p.M ? (h0 & 0xFFFF) | (int)((uint32_t)v0 << 16) : (int)0x80008000u;
+    }
+    const int tap = kb / p.cv.C;
+    c0 = kb - tap * p.cv.C;
+    a = tap / p.cv.ksize;
+    b = tap - a * p.cv.ksize;
+  }
+  // the next K-tile of A (k0: its first k in the slice), then on to the tile after it
+  __device__ __forceinline__ void copy_taps(const GemmArgs& p, int k0, int K, bf16* __restrict__ S, int wave) {
+    __amdgpu_buffer_rsrc_t rs = make_rsrc(p.A);
+    const int da = p.cv.sgn * a, db = p.cv.sgn * b;
+    const uint32_t step = (uint32_t)(((da * p.cv.W + db) * p.cv.C + c0) * 2);
+#pragma unroll
+    for (int i = 0; i < Base::NI; ++i) {
+      const int h = (int)(short)hw[i] + da, w = (hw[i] >> 16) + db;
+      const bool ok = (uint32_t)h < (uint32_t)p.cv.H && (uint32_t)w < (uint32_t)p.cv.W && k0 < K;
+      const uint32_t o = ok ? Base::off[i] + step : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(S + (i * 4 + wave) * 512), 16, o, 0, 0, 0);
+    }
+    c0 += BK;
+    if (c0 == p.cv.C) {
+      c0 = 0;
+      if (++b == p.cv.ksize) {
+        b = 0;
+        ++a;
+      }
+    }
+  }
+};
+
 template <int BT, int AL, int BL>
 __device__ __forceinline__ void frag_read(bf16x8 (&af)[2][BT / 64], bf16x8 (&bfv)[2][BT / 64],
                                           const TileOp<AL, BT>& A, const TileOp<BL, BT>& B,
@@ -519,14 +576,21 @@ __device__ __forceinline__ void frag_read(bf16x8 (&af)[2][BT / 64], bf16x8 (&bfv
   }
 }
 
-// Copies of K-tile t into stage S (past the last tile every chunk is past K)
+// Copies of K-tile t into stage S (past the last tile every chunk is past K).
+// GA, GB: the operands at (tile row 0, k = 0); called for t = 0, 1, 2, ... in order.
 template <int BT, int AL, int BL>
-__device__ __forceinline__ void tile_copy(const TileOp<AL, BT>& A, const TileOp<BL, BT>& B,
-                                          const bf16* GA, const bf16* GB, long lda, long ldb, int t,
-                                          int nk, int K, bf16* __restrict__ S, int wave) {
+__device__ __forceinline__ void tile_copy(TileOp<AL, BT>& A, const TileOp<BL, BT>& B, const GemmArgs& p,
+                                          const bf16* GA, const bf16* GB, int t, int nk, int K,
+                                          bf16* __restrict__ S, int wave) {
   const int k0 = min(t, nk) * BK;
-  A.copy(GA, lda, k0, K, S, wave);
-  B.copy(GB, ldb, k0, K, S + BT * BK, wave);
+  if constexpr (AL == LAY_TAPS) {
+    const bf16* src = GB + (long)(A.a * p.cv.ksize + A.b) * p.cv.b_tap + A.c0;
+    B.copy(src, k0, K, S + BT * BK, wave);
+    A.copy_taps(p, k0, K, S, wave);
+  } else {
+    A.copy(GA + (AL == LAY_K ? (long)k0 : (long)k0 * p.lda), k0, K, S, wave);
+    B.copy(GB + (BL == LAY_K ? (long)k0 : (long)k0 * p.ldb), k0, K, S + BT * BK, wave);
+  }
 }
 
 template <int TT>
@@ -545,8 +609,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
   constexpr int STAGE = 2 * BT * BK;
   __shared__ __attribute__((aligned(1024))) bf16 smem[NS * STAGE];
 
-  int m0, n0;
-  tile_setup<BT, ALAY, BLAY>(p, m0, n0);
+  int m0, n0, kb;
+  tile_setup<BT, ALAY, BLAY>(p, m0, n0, kb);
   const int K = p.K;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -555,7 +619,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
   const bf16* GB = p.B + (BLAY == LAY_K ? (long)n0 * p.ldb : (long)n0);
   TileOp<ALAY, BT> A;
   TileOp<BLAY, BT> B;
-  A.init(p.lda, p.M - m0, wave, wm * WT);
+  if constexpr (ALAY == LAY_TAPS) A.init_taps(p, m0, kb, wave, wm * WT);
+  else A.init(p.lda, p.M - m0, wave, wm * WT);
   B.init(p.ldb, p.N - n0, wave, wn * WT);
   constexpr int NC = 2 * TileOp<LAY_K, BT>::NI;  // copies per wave and K-tile
 
@@ -569,7 +634,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
 
   const int nk = (K + BK - 1) / BK;
 #pragma unroll
-  for (int t = 0; t < NS; ++t) tile_copy(A, B, GA, GB, p.lda, p.ldb, t, nk, K, smem + t * STAGE, wave);
+  for (int t = 0; t < NS; ++t) tile_copy(A, B, p, GA, GB, t, nk, K, smem + t * STAGE, wave);
   wait_vm_lgkm0<(NS - 1) * NC>();
   cta_barrier();
   bf16x8 f01a[2][TT], f01b[2][TT], f23a[2][TT], f23b[2][TT];
@@ -589,7 +654,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
     wait_vm_lgkm0<(NS - 2) * NC>();
     cta_barrier();
     frag_read(f01a, f01b, A, B, smem + st * STAGE, 0);
-    tile_copy(A, B, GA, GB, p.lda, p.ldb, kt + NS, nk, K, cur, wave);
+    tile_copy(A, B, p, GA, GB, kt + NS, nk, K, cur, wave);
     __builtin_amdgcn_sched_barrier(0);
     mfma_step<TT>(acc, f23a[1], f23b[1]);
   }
@@ -782,6 +847,48 @@ GemmPlan gemm_plan(const GemmArgs& a, int alay, int blay, int epi) {
 }
 
 }  // namespace
+
+bool gemm_conv_eligible(const GemmArgs& a) {
+  const ConvTaps& v = a.cv;
+  const long lim = 1L << 31;
+  return v.C % BK == 0 && a.K == v.ksize * v.ksize * v.C && aligned16(a.A) && aligned16(a.B) &&
+         a.ldb % 8 == 0 && v.b_tap % 8 == 0 && v.H < (1 << 14) && v.W < (1 << 14) && v.oH < (1 << 14) &&
+         v.oW < (1 << 14) && a.M % (v.oH * v.oW) == 0 &&
+         (long)(a.M / (v.oH * v.oW)) * v.H * v.W * v.C * 2 < lim && 128L * a.ldb * 2 < lim;
+}
+
+// The gathered product runs on 128 x 128 or 64 x 64 tiles, unsplit or in K slices
+// where the workspace holds them, by the same estimate.
+hipError_t launch_gemm_conv(const GemmArgs& a, hipStream_t s) {
+  if (!gemm_conv_eligible(a)) return hipErrorInvalidValue;
+  GemmPlan best{128, 1, 0, 1e30};
+  const long fit = a.splitk_ws != nullptr ? a.splitk_ws_elems / std::max(1L, (long)a.M * a.N) : 1;
+  const int smax = (int)std::max(1L, std::min(std::min(16L, (long)a.K / 512), fit));
+  for (int bt : {128, 64})
+    for (int S = 1; S <= smax; ++S) {
+      const int kc = (sat_cdiv(a.K, S) + BK - 1) / BK * BK;
+      const int Se = sat_cdiv(a.K, kc);
+      const double us = gemm_estimate(bt, false, a.M, a.N, a.K, Se);
+      if (us < best.us) best = GemmPlan{bt, Se, kc, us};
+    }
+  GemmArgs b = a;
+  if (best.S > 1) {
+    b.out = a.splitk_ws;
+    b.ldo = a.N;
+    b.splitk = best.S;
+    b.splitk_kc = best.kc;
+    b.split_stride = (long)a.M * a.N;
+  }
+  const dim3 grid((unsigned)(sat_cdiv(a.M, best.bt) * sat_cdiv(a.N, best.bt) * best.S));
+  if (best.bt == 128)
+    hipLaunchKernelGGL((gemm_tile_kernel<128, 2, LAY_TAPS, LAY_K, EPI_F32, 0>), grid, dim3(NT), 0, s, b);
+  else
+    hipLaunchKernelGGL((gemm_tile_kernel<64, 4, LAY_TAPS, LAY_K, EPI_F32, 0>), grid, dim3(NT), 0, s, b);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || best.S <= 1) return e;
+  return launch_splitk_reduce(a.splitk_ws, best.S, b.split_stride, a.M, a.N,
+                              reinterpret_cast<float*>(a.out), a.ldo, nullptr, 0, nullptr, 0, s);
+}
 
 int gemm_colsum_rows(const GemmArgs& a) {
   const GemmPlan p = gemm_plan(a, LAY_K, LAY_K, EPI_DGELU_BF16);

@@ -31,6 +31,18 @@ enum GemmEpilogue {
   EPI_ADAMW = 4,      // C is the gradient of a weight: one AdamW step on it (opt_* below)
 };
 
+// A operand gathered from an NHWC tensor [N, H, W, C] (a convolution without its
+// im2col matrix): row m is the output pixel (n, i, j) of oH x oW, k the pair
+// (tap (a, b) of a ksize x ksize window, channel c), and A(m, k) = A[((n H + h) W +
+// w) C + c] with h = h0 + sgn a, w = w0 + sgn b, zero outside the image.
+//   forward:        h0 = i stride - pad,  sgn = +1
+//   input gradient: h0 = i + pad,         sgn = -1 (stride 1)
+// B(n, k) = B[tap * b_tap + n * ldb + c].
+struct ConvTaps {
+  int H, W, C, oH, oW, ksize, stride, org, sgn;  // h0 = i * stride + org
+  long b_tap;
+};
+
 struct GemmArgs {
   const bf16* A;
   const bf16* B;
@@ -84,9 +96,15 @@ struct GemmArgs {
   // (gemm_tail_split): a weight gradient whose AdamW step may instead be
   // fused into this kernel's epilogue must sum in the same order either way.
   int no_tail_split;
+  ConvTaps cv;  // launch_gemm_conv only
 };
 
 hipError_t launch_gemm(const GemmArgs& a, int alay, int blay, int epi, hipStream_t s);
+// out_f32[m, n] = sum_k A(m, k) B(n, k) with A gathered per a.cv (a.lda unused),
+// a.K = ksize^2 C.  Eligible: C a multiple of 64 (a K-tile lies in one tap),
+// 16-byte aligned operands, ldb and b_tap multiples of 8, tensors below 2^31 bytes.
+bool gemm_conv_eligible(const GemmArgs& a);
+hipError_t launch_gemm_conv(const GemmArgs& a, hipStream_t s);
 // Rows per block of the column sums that launch_gemm writes for this
 // EPI_DGELU_BF16 product on K-contiguous operands: half the tile of the kernel
 // it runs (128, 64 or 32).

@@ -5,10 +5,12 @@
 //
 // Every convolution is one MFMA GEMM over NHWC activations (rows = output
 // pixels, columns = channels): a 1 x 1 convolution multiplies the activation
-// matrix itself, a 3 x 3 (or the 7 x 7 stem) the im2col matrix of its input,
+// matrix itself, a 3 x 3 gathers its input tap by tap inside the product (channel
+// counts that are multiples of 64; else, and for the 7 x 7 stem, through the im2col
+// matrix of its input),
 // a stride-2 1 x 1 projection the every-other-pixel subsample.  Its input
-// gradient is one GEMM against the transposed bf16 weight copy, scattered
-// back by col2im where the convolution is not 1 x 1; its weight gradient is
+// gradient is one GEMM against the transposed bf16 weight copy, gathered in the
+// same way (stride 1) or scattered back by col2im where the convolution is not 1 x 1; its weight gradient is
 // one GEMM over the pixels (K = N H W) on the row-major operands, split over K
 // so that the few output tiles still fill the chip (pixel-contiguous copies of both
 // operands for the 256 x 256 kernel cost more than they gave: 12 blocks at batch 64,
@@ -399,6 +401,29 @@ sat_status conv_gemm(sat_model* M, const bf16* A, long lda, int w, long P, int c
   return gemm(M, a, LAY_K, LAY_K, EPI_F32, tk);
 }
 
+// The 3 x 3 convolution of block b without its im2col matrix: forward c2 = conv(a1,
+// w2), or, for stride 1, the input gradient da = conv^T(dY, w2), gathered tap by
+// tap.  Returns false when the shapes need the im2col path.
+bool conv3(sat_model* M, const RBlock& b, bool fwd, const bf16* A, float* out, sat_status* st) {
+  const ParamDesc& p = M->params[b.w2];
+  if (!fwd && b.stride != 1) return false;
+  GemmArgs a = fwd ? gargs(A, 0, shadow(M, b.w2), 9L * b.mid, (int)b.Pout, b.mid, 9 * b.mid, out, b.mid)
+                   : gargs(A, 0, shadow_t(M, b.w2), p.trows, (int)b.Pin, b.mid, 9 * b.mid, out, b.mid);
+  a.cv = fwd ? ConvTaps{b.H, b.W, b.mid, b.Ho, b.Wo, 3, b.stride, -1, 1, b.mid}
+             : ConvTaps{b.Ho, b.Wo, b.mid, b.H, b.W, 3, 1, 1, -1, (long)b.mid * p.trows};
+  if (!gemm_conv_eligible(a)) return false;
+  Timed t(M, fwd ? TK_QKV_FWD : TK_ALL_GEMM, 2.0 * a.M * a.N * (double)a.K);
+  a.splitk_ws = M->splitk_ws;
+  a.splitk_ws_elems = M->splitk_ws_elems;
+  const hipError_t e = launch_gemm_conv(a, M->stream);
+  *st = SAT_OK;
+  if (e != hipSuccess) {
+    sat_set_error("conv3: %s", hipGetErrorString(e));
+    *st = SAT_EHIP;
+  }
+  return true;
+}
+
 // Weight gradient [cout, ncols] = dY^T X over P pixels (dY [P, cout] bf16; X
 // [P, >= ncols] bf16 with row pitch ldx), straight on the row-major operands
 // (read with the transposing LDS read), split over the pixels.
@@ -450,9 +475,13 @@ sat_status sat_resnet_forward(sat_model* M, const void* inputs, const int32_t* l
     SAT_HIP(launch_bn_stats(b.c1, b.Pin, b.mid, eps, R.part, b.n1.mean, b.n1.rstd, s));
     SAT_HIP(launch_bn_apply(b.c1, b.Pin, b.mid, b.n1.mean, b.n1.rstd, gam(M, b.n1), bet(M, b.n1), 1,
                             b.a1, nullptr, s));
-    SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
-                          s));
-    TRY(conv_gemm(M, R.col, 9L * b.mid, b.w2, b.Pout, b.mid, 9 * b.mid, b.c2, TK_QKV_FWD));
+    sat_status st = SAT_OK;
+    if (!conv3(M, b, true, b.a1, b.c2, &st)) {
+      SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
+                            s));
+      TRY(conv_gemm(M, R.col, 9L * b.mid, b.w2, b.Pout, b.mid, 9 * b.mid, b.c2, TK_QKV_FWD));
+    }
+    TRY(st);
     SAT_HIP(launch_bn_stats(b.c2, b.Pout, b.mid, eps, R.part, b.n2.mean, b.n2.rstd, s));
     SAT_HIP(launch_bn_apply(b.c2, b.Pout, b.mid, b.n2.mean, b.n2.rstd, gam(M, b.n2), bet(M, b.n2), 1,
                             b.a2, nullptr, s));
@@ -526,11 +555,15 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
     TRY(rwgrad(M, R.dc, b.cout, b.a2, b.mid, b.mid, b.Pout, grad(M, b.w3)));
     SAT_HIP(launch_bn_bwd(R.da, 1, b.a2, b.c2, b.n2.mean, b.n2.rstd, gam(M, b.n2), b.Pout, b.mid,
                           R.part, grad(M, b.n2.g), grad(M, b.n2.g + 1), R.dc, s));
-    // conv2 (3 x 3, the block's stride): input gradient through col2im, weight
-    // gradient against the im2col matrix rebuilt from a1
-    TRY(dgrad(M, R.dc, b.mid, b.w2, b.Pout, 9 * b.mid, R.dcol, nullptr));
-    SAT_HIP(launch_col2im(R.dcol, 9L * b.mid, R.da, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
-                          0, s));
+    // conv2 (3 x 3, the block's stride): input gradient gathered from dY (stride 1)
+    // or through col2im, weight gradient against the im2col matrix of a1
+    sat_status st = SAT_OK;
+    if (!conv3(M, b, false, R.dc, R.da, &st)) {
+      TRY(dgrad(M, R.dc, b.mid, b.w2, b.Pout, 9 * b.mid, R.dcol, nullptr));
+      SAT_HIP(launch_col2im(R.dcol, 9L * b.mid, R.da, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
+                            0, s));
+    }
+    TRY(st);
     SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo, s));
     TRY(rwgrad(M, R.dc, b.mid, R.col, 9L * b.mid, 9 * b.mid, b.Pout, grad(M, b.w2)));
     SAT_HIP(launch_bn_bwd(R.da, 1, b.a1, b.c1, b.n1.mean, b.n1.rstd, gam(M, b.n1), b.Pin, b.mid,
