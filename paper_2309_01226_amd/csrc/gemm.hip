@@ -335,7 +335,8 @@ __device__ __forceinline__ bool epilogue_vec(const GemmArgs& p) {
 // tile-rows.  With split-K the grid is (slice, tile) pairs, slice-major: the
 // arguments are narrowed to the slice's K range and output block.
 // kb: first k of the slice (gathered operands keep their pointers).
-constexpr int LAY_TAPS = 2;  // A gathered per ConvTaps, B K-contiguous within a tap
+constexpr int LAY_TAPS = 2;     // A gathered per ConvTaps, B K-contiguous within a tap
+constexpr int LAY_TAPS_MN = 3;  // B gathered per ConvTaps, its pixels along k (the weight gradient)
 template <int BT, int ALAY, int BLAY>
 __device__ __forceinline__ void tile_setup(GemmArgs& p, int& m0, int& n0, int& kb) {
   kb = 0;
@@ -347,10 +348,8 @@ __device__ __forceinline__ void tile_setup(GemmArgs& p, int& m0, int& n0, int& k
     const int split = bid / (tiles_m * tiles_n);
     bid -= split * tiles_m * tiles_n;
     kb = split * p.splitk_kc;
-    if (ALAY != LAY_TAPS) {
-      p.A += ALAY == LAY_K ? (long)kb : (long)kb * p.lda;
-      p.B += BLAY == LAY_K ? (long)kb : (long)kb * p.ldb;
-    }
+    if (ALAY != LAY_TAPS) p.A += ALAY == LAY_K ? (long)kb : (long)kb * p.lda;
+    if (ALAY != LAY_TAPS && BLAY != LAY_TAPS_MN) p.B += BLAY == LAY_K ? (long)kb : (long)kb * p.ldb;
     p.K = min(p.splitk_kc, p.K - kb);
     p.out = reinterpret_cast<float*>(p.out) + split * p.split_stride;
   }
@@ -563,6 +562,57 @@ struct TileOp<LAY_TAPS, BT> : TileOp<LAY_K, BT> {
   }
 };
 
+// The weight gradient's gathered operand: the M/N-contiguous tile layout and
+// fragments; k-row = one output pixel, columns = BT channels of one tap.  Every lane
+// keeps its pieces' pixels and moves them on by a K-tile of 64 pixels: 64 = (dn
+// images, di rows, dj columns), one carry each.  (12 ResNet blocks at batch 64:
+// rebuilding the im2col matrix for these products took 0.7 ms of the step.)
+template <int BT>
+struct TileOp<LAY_TAPS_MN, BT> : TileOp<LAY_MN, BT> {
+  using Base = TileOp<LAY_MN, BT>;
+  int pn[Base::NI], pi[Base::NI], pj[Base::NI];
+  int a, b;             // this tile's tap
+  int dn, di, dj;
+  __device__ __forceinline__ void init_taps(const GemmArgs& p, int n0, int kb, int wave, int w0) {
+    Base::init(0, 0, wave, w0);  // fragment offsets, k of this lane's pieces
+    const int lane = threadIdx.x & 63;
+    const int tap = n0 / p.cv.C, c0 = n0 - tap * p.cv.C;
+    a = tap / p.cv.ksize;
+    b = tap - a * p.cv.ksize;
+#pragma unroll
+    for (int i = 0; i < Base::NI; ++i) {
+      const int m = kb + Base::kof[i];
+      const int q = m / p.cv.oW;
+      pj[i] = m - q * p.cv.oW;
+      pn[i] = q / p.cv.oH;
+      pi[i] = q - pn[i] * p.cv.oH;
+      Base::off[i] = (uint32_t)((c0 + 8 * ((lane % Base::CPR) ^ Base::swz_mn(Base::kof[i]))) * 2);
+    }
+    dn = BK / (p.cv.oH * p.cv.oW);
+    const int rem = BK - dn * p.cv.oH * p.cv.oW;
+    di = rem / p.cv.oW;
+    dj = rem - di * p.cv.oW;
+  }
+  __device__ __forceinline__ void copy_taps(const GemmArgs& p, int k0, int K, bf16* __restrict__ S, int wave) {
+    __amdgpu_buffer_rsrc_t rs = make_rsrc(p.B);
+#pragma unroll
+    for (int i = 0; i < Base::NI; ++i) {
+      const int h = pi[i] * p.cv.stride + p.cv.org + a, w = pj[i] * p.cv.stride + p.cv.org + b;
+      const bool ok = (uint32_t)h < (uint32_t)p.cv.H && (uint32_t)w < (uint32_t)p.cv.W && k0 + Base::kof[i] < K;
+      const uint32_t o =
+          ok ? (uint32_t)(((pn[i] * p.cv.H + h) * p.cv.W + w) * p.cv.C * 2) + Base::off[i] : OOB;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, LDS_PTR(S + (i * 4 + wave) * 512), 16, o, 0, 0, 0);
+      pj[i] += dj;
+      const int cj = pj[i] >= p.cv.oW ? 1 : 0;
+      pj[i] -= cj ? p.cv.oW : 0;
+      pi[i] += di + cj;
+      const int ci = pi[i] >= p.cv.oH ? 1 : 0;
+      pi[i] -= ci ? p.cv.oH : 0;
+      pn[i] += dn + ci;
+    }
+  }
+};
+
 template <int BT, int AL, int BL>
 __device__ __forceinline__ void frag_read(bf16x8 (&af)[2][BT / 64], bf16x8 (&bfv)[2][BT / 64],
                                           const TileOp<AL, BT>& A, const TileOp<BL, BT>& B,
@@ -579,7 +629,7 @@ __device__ __forceinline__ void frag_read(bf16x8 (&af)[2][BT / 64], bf16x8 (&bfv
 // Copies of K-tile t into stage S (past the last tile every chunk is past K).
 // GA, GB: the operands at (tile row 0, k = 0); called for t = 0, 1, 2, ... in order.
 template <int BT, int AL, int BL>
-__device__ __forceinline__ void tile_copy(TileOp<AL, BT>& A, const TileOp<BL, BT>& B, const GemmArgs& p,
+__device__ __forceinline__ void tile_copy(TileOp<AL, BT>& A, TileOp<BL, BT>& B, const GemmArgs& p,
                                           const bf16* GA, const bf16* GB, int t, int nk, int K,
                                           bf16* __restrict__ S, int wave) {
   const int k0 = min(t, nk) * BK;
@@ -587,6 +637,9 @@ __device__ __forceinline__ void tile_copy(TileOp<AL, BT>& A, const TileOp<BL, BT
     const bf16* src = GB + (long)(A.a * p.cv.ksize + A.b) * p.cv.b_tap + A.c0;
     B.copy(src, k0, K, S + BT * BK, wave);
     A.copy_taps(p, k0, K, S, wave);
+  } else if constexpr (BL == LAY_TAPS_MN) {
+    A.copy(GA + (long)k0 * p.lda, k0, K, S, wave);
+    B.copy_taps(p, k0, K, S + BT * BK, wave);
   } else {
     A.copy(GA + (AL == LAY_K ? (long)k0 : (long)k0 * p.lda), k0, K, S, wave);
     B.copy(GB + (BL == LAY_K ? (long)k0 : (long)k0 * p.ldb), k0, K, S + BT * BK, wave);
@@ -615,13 +668,14 @@ __global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const bf16* GA = p.A + (ALAY == LAY_K ? (long)m0 * p.lda : (long)m0);
+  const bf16* GA = p.A + (ALAY == LAY_K ? (long)m0 * p.lda : (long)m0);  // (gathered operands: unused)
   const bf16* GB = p.B + (BLAY == LAY_K ? (long)n0 * p.ldb : (long)n0);
   TileOp<ALAY, BT> A;
   TileOp<BLAY, BT> B;
   if constexpr (ALAY == LAY_TAPS) A.init_taps(p, m0, kb, wave, wm * WT);
   else A.init(p.lda, p.M - m0, wave, wm * WT);
-  B.init(p.ldb, p.N - n0, wave, wn * WT);
+  if constexpr (BLAY == LAY_TAPS_MN) B.init_taps(p, n0, kb, wave, wn * WT);
+  else B.init(p.ldb, p.N - n0, wave, wn * WT);
   constexpr int NC = 2 * TileOp<LAY_K, BT>::NI;  // copies per wave and K-tile
 
   floatx16 acc[TT][TT];
@@ -756,7 +810,8 @@ namespace {
 //    prologue and epilogue 6.5 us (1.75 and 8 with an M/N-contiguous operand);
 //  * 128: two tiles share a CU; 0.39 us per K-tile and 4.5 us per tile of a CU,
 //    0.62 and 5 us for a CU that has one;
-//  * 64: 0.215 us per K-tile and 0.6 us per tile of a CU, 3 us in all;
+//  * 64: 0.215 us per K-tile and 0.6 us per tile of a CU (1.8 past 16 tiles, where
+//    the outputs stream to memory), 3 us in all;
 //  * the reduction of the slices: 4 us and its traffic at 6 TB/s.
 double gemm_estimate(int bt, bool mn, long M, long N, long K, int S) {
   const double kt = (double)((sat_cdiv(K, S) + 63) / 64);
@@ -764,7 +819,7 @@ double gemm_estimate(int bt, bool mn, long M, long N, long K, int S) {
   const double red = S > 1 ? 4.0 + (S + 1.0) * M * N * 4.0 / 6e6 : 0.0;
   if (bt == 256) return n * (mn ? 1.75 * kt + 8.0 : 1.5 * kt + 6.5) + red;
   if (bt == 128) return (n == 1 ? 0.62 * kt + 5.0 : n * (0.39 * kt + 4.5)) + red;
-  return 3.0 + n * (0.6 + 0.215 * kt) + red;
+  return 3.0 + n * ((n > 16 ? 1.8 : 0.6) + 0.215 * kt) + red;
 }
 
 struct GemmPlan {
@@ -857,15 +912,26 @@ bool gemm_conv_eligible(const GemmArgs& a) {
          (long)(a.M / (v.oH * v.oW)) * v.H * v.W * v.C * 2 < lim && 128L * a.ldb * 2 < lim;
 }
 
-// The gathered product runs on 128 x 128 or 64 x 64 tiles, unsplit or in K slices
-// where the workspace holds them, by the same estimate.
-hipError_t launch_gemm_conv(const GemmArgs& a, hipStream_t s) {
-  if (!gemm_conv_eligible(a)) return hipErrorInvalidValue;
-  GemmPlan best{128, 1, 0, 1e30};
+bool gemm_conv_wgrad_eligible(const GemmArgs& a) {
+  const ConvTaps& v = a.cv;
+  const long lim = 1L << 31;
+  return v.C % 64 == 0 && a.N == v.ksize * v.ksize * v.C && aligned16(a.A) && aligned16(a.B) &&
+         a.lda % 8 == 0 && a.lda >= (a.M + 7) / 8 * 8 && a.K % (v.oH * v.oW) == 0 &&
+         (long)(a.K / (v.oH * v.oW)) * v.H * v.W * v.C * 2 < lim && 64L * a.lda * 2 < lim;
+}
+
+namespace {
+
+// A gathered product runs on 128 x 128 (wide: allowed) or 64 x 64 tiles, unsplit or in
+// at most smax K slices where the workspace holds them, by the same estimate.
+template <int AL, int BL>
+hipError_t launch_conv(const GemmArgs& a, bool wide, long smax, hipStream_t s) {
+  GemmPlan best{64, 1, 0, 1e30};
   const long fit = a.splitk_ws != nullptr ? a.splitk_ws_elems / std::max(1L, (long)a.M * a.N) : 1;
-  const int smax = (int)std::max(1L, std::min(std::min(16L, (long)a.K / 512), fit));
+  smax = std::max(1L, std::min({smax, (long)a.K / 512, fit}));
   for (int bt : {128, 64})
-    for (int S = 1; S <= smax; ++S) {
+    for (int S = 1; S <= (int)smax; ++S) {
+      if (bt == 128 && !wide) break;
       const int kc = (sat_cdiv(a.K, S) + BK - 1) / BK * BK;
       const int Se = sat_cdiv(a.K, kc);
       const double us = gemm_estimate(bt, false, a.M, a.N, a.K, Se);
@@ -880,14 +946,25 @@ hipError_t launch_gemm_conv(const GemmArgs& a, hipStream_t s) {
     b.split_stride = (long)a.M * a.N;
   }
   const dim3 grid((unsigned)(sat_cdiv(a.M, best.bt) * sat_cdiv(a.N, best.bt) * best.S));
-  if (best.bt == 128)
-    hipLaunchKernelGGL((gemm_tile_kernel<128, 2, LAY_TAPS, LAY_K, EPI_F32, 0>), grid, dim3(NT), 0, s, b);
-  else
-    hipLaunchKernelGGL((gemm_tile_kernel<64, 4, LAY_TAPS, LAY_K, EPI_F32, 0>), grid, dim3(NT), 0, s, b);
+  if (best.bt == 128) hipLaunchKernelGGL((gemm_tile_kernel<128, 2, AL, BL, EPI_F32, 0>), grid, dim3(NT), 0, s, b);
+  else hipLaunchKernelGGL((gemm_tile_kernel<64, 4, AL, BL, EPI_F32, 0>), grid, dim3(NT), 0, s, b);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || best.S <= 1) return e;
   return launch_splitk_reduce(a.splitk_ws, best.S, b.split_stride, a.M, a.N,
                               reinterpret_cast<float*>(a.out), a.ldo, nullptr, 0, nullptr, 0, s);
+}
+
+}  // namespace
+
+hipError_t launch_gemm_conv(const GemmArgs& a, hipStream_t s) {
+  if (!gemm_conv_eligible(a)) return hipErrorInvalidValue;
+  return launch_conv<LAY_TAPS, LAY_K>(a, true, 16, s);
+}
+
+hipError_t launch_gemm_conv_wgrad(const GemmArgs& a, hipStream_t s) {
+  if (!gemm_conv_wgrad_eligible(a)) return hipErrorInvalidValue;
+  // a tile's columns lie in one tap
+  return launch_conv<LAY_MN, LAY_TAPS_MN>(a, a.cv.C % 128 == 0, a.splitk_max > 0 ? a.splitk_max : 16, s);
 }
 
 int gemm_colsum_rows(const GemmArgs& a) {

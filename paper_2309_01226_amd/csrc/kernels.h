@@ -38,6 +38,8 @@ enum GemmEpilogue {
 //   forward:        h0 = i stride - pad,  sgn = +1
 //   input gradient: h0 = i + pad,         sgn = -1 (stride 1)
 // B(n, k) = B[tap * b_tap + n * ldb + c].
+// The weight gradient gathers B instead: C[m, n] = sum over pixels k of A[k lda + m]
+// B(n, k), n the pair (tap, c) and k the output pixel, with the forward's h and w.
 struct ConvTaps {
   int H, W, C, oH, oW, ksize, stride, org, sgn;  // h0 = i * stride + org
   long b_tap;
@@ -105,6 +107,11 @@ hipError_t launch_gemm(const GemmArgs& a, int alay, int blay, int epi, hipStream
 // 16-byte aligned operands, ldb and b_tap multiples of 8, tensors below 2^31 bytes.
 bool gemm_conv_eligible(const GemmArgs& a);
 hipError_t launch_gemm_conv(const GemmArgs& a, hipStream_t s);
+// The weight gradient of the same convolution: a.A = dY [K, lda], a.B the NHWC tensor,
+// a.N = ksize^2 C (C a multiple of 64), a.K = output pixels, at most
+// a.splitk_max slices.
+bool gemm_conv_wgrad_eligible(const GemmArgs& a);
+hipError_t launch_gemm_conv_wgrad(const GemmArgs& a, hipStream_t s);
 // Rows per block of the column sums that launch_gemm writes for this
 // EPI_DGELU_BF16 product on K-contiguous operands: half the tile of the kernel
 // it runs (128, 64 or 32).

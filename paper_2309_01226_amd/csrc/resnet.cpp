@@ -5,13 +5,13 @@
 //
 // Every convolution is one MFMA GEMM over NHWC activations (rows = output
 // pixels, columns = channels): a 1 x 1 convolution multiplies the activation
-// matrix itself, a 3 x 3 gathers its input tap by tap inside the product (channel
-// counts that are multiples of 64; else, and for the 7 x 7 stem, through the im2col
-// matrix of its input),
-// a stride-2 1 x 1 projection the every-other-pixel subsample.  Its input
-// gradient is one GEMM against the transposed bf16 weight copy, gathered in the
-// same way (stride 1) or scattered back by col2im where the convolution is not 1 x 1; its weight gradient is
-// one GEMM over the pixels (K = N H W) on the row-major operands, split over K
+// matrix itself, a 3 x 3 or a stride-2 1 x 1 projection gathers its input tap by tap
+// inside the product (channel counts that are multiples of 64; else, and for the
+// 7 x 7 stem, through the im2col matrix of its input).  Its input gradient is one
+// GEMM against the transposed bf16 weight copy, gathered in the same way (3 x 3,
+// stride 1) or scattered back by col2im where the convolution is not 1 x 1; its
+// weight gradient is one GEMM over the pixels (K = N H W) on the row-major or
+// gathered operands, split over K
 // so that the few output tiles still fill the chip (pixel-contiguous copies of both
 // operands for the 256 x 256 kernel cost more than they gave: 12 blocks at batch 64,
 // 21.0 ms per step with them, 19.5 without).
@@ -401,24 +401,38 @@ sat_status conv_gemm(sat_model* M, const bf16* A, long lda, int w, long P, int c
   return gemm(M, a, LAY_K, LAY_K, EPI_F32, tk);
 }
 
-// The 3 x 3 convolution of block b without its im2col matrix: forward c2 = conv(a1,
-// w2), or, for stride 1, the input gradient da = conv^T(dY, w2), gathered tap by
-// tap.  Returns false when the shapes need the im2col path.
-bool conv3(sat_model* M, const RBlock& b, bool fwd, const bf16* A, float* out, sat_status* st) {
-  const ParamDesc& p = M->params[b.w2];
-  if (!fwd && b.stride != 1) return false;
-  GemmArgs a = fwd ? gargs(A, 0, shadow(M, b.w2), 9L * b.mid, (int)b.Pout, b.mid, 9 * b.mid, out, b.mid)
-                   : gargs(A, 0, shadow_t(M, b.w2), p.trows, (int)b.Pin, b.mid, 9 * b.mid, out, b.mid);
-  a.cv = fwd ? ConvTaps{b.H, b.W, b.mid, b.Ho, b.Wo, 3, b.stride, -1, 1, b.mid}
-             : ConvTaps{b.Ho, b.Wo, b.mid, b.H, b.W, 3, 1, 1, -1, (long)b.mid * p.trows};
-  if (!gemm_conv_eligible(a)) return false;
-  Timed t(M, fwd ? TK_QKV_FWD : TK_ALL_GEMM, 2.0 * a.M * a.N * (double)a.K);
+enum Conv { CONV2, DOWN };  // a block's 3 x 3 convolution, its 1 x 1 projection
+
+// A convolution of block b with stride or window, gathered inside the product
+// instead of through an im2col matrix: forward (A = its input, out), input
+// gradient (A = dY; 3 x 3 with stride 1 only) or weight gradient (A = dY, X = its
+// input).  Returns false when the shapes need the im2col path.
+enum ConvPass { FWD, DGRAD, WGRAD };
+bool conv_gather(sat_model* M, const RBlock& b, Conv which, ConvPass pass, const bf16* A, const bf16* X, float* out,
+                 sat_status* st) {
+  if (pass == DGRAD && (which != CONV2 || b.stride != 1)) return false;
+  const int w = which == CONV2 ? b.w2 : b.wd, k = which == CONV2 ? 3 : 1;
+  const int C = which == CONV2 ? b.mid : b.cin, cout = which == CONV2 ? b.mid : b.cout;
+  const ParamDesc& p = M->params[w];
+  GemmArgs a;
+  if (pass == FWD) {
+    a = gargs(A, 0, shadow(M, w), (long)k * k * C, (int)b.Pout, cout, k * k * C, out, cout);
+  } else if (pass == DGRAD) {
+    a = gargs(A, 0, shadow_t(M, w), p.trows, (int)b.Pin, C, k * k * cout, out, C);
+  } else {
+    a = gargs(A, cout, X, 0, cout, k * k * C, (int)b.Pout, out, k * k * C);
+  }
+  a.cv = pass == DGRAD ? ConvTaps{b.Ho, b.Wo, cout, b.H, b.W, k, 1, k / 2, -1, (long)C * p.trows}
+                       : ConvTaps{b.H, b.W, C, b.Ho, b.Wo, k, b.stride, -(k / 2), 1, C};
+  a.splitk_max = pass == WGRAD ? kSplitMax : 0;
   a.splitk_ws = M->splitk_ws;
   a.splitk_ws_elems = M->splitk_ws_elems;
-  const hipError_t e = launch_gemm_conv(a, M->stream);
+  if (pass == WGRAD ? !gemm_conv_wgrad_eligible(a) : !gemm_conv_eligible(a)) return false;
+  Timed t(M, pass == FWD && which == CONV2 ? TK_QKV_FWD : TK_ALL_GEMM, 2.0 * a.M * a.N * (double)a.K);
+  const hipError_t e = pass == WGRAD ? launch_gemm_conv_wgrad(a, M->stream) : launch_gemm_conv(a, M->stream);
   *st = SAT_OK;
   if (e != hipSuccess) {
-    sat_set_error("conv3: %s", hipGetErrorString(e));
+    sat_set_error("convolution of block %d: %s", b.idx, hipGetErrorString(e));
     *st = SAT_EHIP;
   }
   return true;
@@ -476,7 +490,7 @@ sat_status sat_resnet_forward(sat_model* M, const void* inputs, const int32_t* l
     SAT_HIP(launch_bn_apply(b.c1, b.Pin, b.mid, b.n1.mean, b.n1.rstd, gam(M, b.n1), bet(M, b.n1), 1,
                             b.a1, nullptr, s));
     sat_status st = SAT_OK;
-    if (!conv3(M, b, true, b.a1, b.c2, &st)) {
+    if (!conv_gather(M, b, CONV2, FWD, b.a1, nullptr, b.c2, &st)) {
       SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
                             s));
       TRY(conv_gemm(M, R.col, 9L * b.mid, b.w2, b.Pout, b.mid, 9 * b.mid, b.c2, TK_QKV_FWD));
@@ -488,13 +502,14 @@ sat_status sat_resnet_forward(sat_model* M, const void* inputs, const int32_t* l
     TRY(conv_gemm(M, b.a2, b.mid, b.w3, b.Pout, b.cout, b.mid, b.c3));
     SAT_HIP(launch_bn_stats(b.c3, b.Pout, b.cout, eps, R.part, b.n3.mean, b.n3.rstd, s));
     if (b.proj) {
-      const bf16* sub = R.xb[i];
-      if (b.stride != 1) {
+      if (b.stride == 1) {
+        TRY(conv_gemm(M, R.xb[i], b.cin, b.wd, b.Pout, b.cout, b.cin, b.cd));
+      } else if (!conv_gather(M, b, DOWN, FWD, R.xb[i], nullptr, b.cd, &st)) {
         SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho,
                               b.Wo, s));
-        sub = R.col;
+        TRY(conv_gemm(M, R.col, b.cin, b.wd, b.Pout, b.cout, b.cin, b.cd));
       }
-      TRY(conv_gemm(M, sub, b.cin, b.wd, b.Pout, b.cout, b.cin, b.cd));
+      TRY(st);
       SAT_HIP(launch_bn_stats(b.cd, b.Pout, b.cout, eps, R.part, b.nd.mean, b.nd.rstd, s));
       SAT_HIP(launch_bn_add_relu(b.c3, b.n3.mean, b.n3.rstd, gam(M, b.n3), bet(M, b.n3), b.cd,
                                  b.nd.mean, b.nd.rstd, gam(M, b.nd), bet(M, b.nd), b.Pout, b.cout,
@@ -558,14 +573,17 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
     // conv2 (3 x 3, the block's stride): input gradient gathered from dY (stride 1)
     // or through col2im, weight gradient against the im2col matrix of a1
     sat_status st = SAT_OK;
-    if (!conv3(M, b, false, R.dc, R.da, &st)) {
+    if (!conv_gather(M, b, CONV2, DGRAD, R.dc, nullptr, R.da, &st)) {
       TRY(dgrad(M, R.dc, b.mid, b.w2, b.Pout, 9 * b.mid, R.dcol, nullptr));
       SAT_HIP(launch_col2im(R.dcol, 9L * b.mid, R.da, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
                             0, s));
     }
     TRY(st);
-    SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo, s));
-    TRY(rwgrad(M, R.dc, b.mid, R.col, 9L * b.mid, 9 * b.mid, b.Pout, grad(M, b.w2)));
+    if (!conv_gather(M, b, CONV2, WGRAD, R.dc, b.a1, grad(M, b.w2), &st)) {
+      SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo, s));
+      TRY(rwgrad(M, R.dc, b.mid, R.col, 9L * b.mid, 9 * b.mid, b.Pout, grad(M, b.w2)));
+    }
+    TRY(st);
     SAT_HIP(launch_bn_bwd(R.da, 1, b.a1, b.c1, b.n1.mean, b.n1.rstd, gam(M, b.n1), b.Pin, b.mid,
                           R.part, grad(M, b.n1.g), grad(M, b.n1.g + 1), R.dc, s));
     // conv1 (1 x 1) and the shortcut; the input gradient only when something
@@ -579,8 +597,11 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
           TRY(dgrad(M, R.dcd, b.cout, b.wd, b.Pout, b.cin, R.dsub, nullptr));
           SAT_HIP(launch_stride2_add(R.dsub, R.N, b.Ho, b.Wo, b.cin, b.H, b.W, dx, s));
         }
-        SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho, b.Wo, s));
-        TRY(rwgrad(M, R.dcd, b.cout, R.col, b.cin, b.cin, b.Pout, grad(M, b.wd)));
+        if (!conv_gather(M, b, DOWN, WGRAD, R.dcd, R.xb[i], grad(M, b.wd), &st)) {
+          SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho, b.Wo, s));
+          TRY(rwgrad(M, R.dcd, b.cout, R.col, b.cin, b.cin, b.Pout, grad(M, b.wd)));
+        }
+        TRY(st);
       } else {
         if (need_dx) TRY(dgrad(M, R.dcd, b.cout, b.wd, b.Pout, b.cin, dx, dx));
         TRY(rwgrad(M, R.dcd, b.cout, R.xb[i], b.cin, b.cin, b.Pout, grad(M, b.wd)));
