@@ -807,7 +807,7 @@ namespace {
 // Estimated time (us) of an [M, N] product of depth K in S slices on tiles of
 // bt x bt, from measured products (random operands, 0.5 to 300 GFLOP):
 //  * 256: rounds of one tile per CU; a K-tile of 64 takes 1.5 us, a tile's
-//    prologue and epilogue 6.5 us (1.75 and 8 with an M/N-contiguous operand);
+//    prologue and epilogue 6.5 us (1.6 with an M/N-contiguous operand);
 //  * 128: two tiles share a CU; 0.39 us per K-tile and 4.5 us per tile of a CU,
 //    0.62 and 5 us for a CU that has one;
 //  * 64: 0.215 us per K-tile and 0.6 us per tile of a CU (1.8 past 16 tiles, where
@@ -817,7 +817,7 @@ double gemm_estimate(int bt, bool mn, long M, long N, long K, int S) {
   const double kt = (double)((sat_cdiv(K, S) + 63) / 64);
   const long n = ((long)sat_cdiv(M, bt) * sat_cdiv(N, bt) * S + 255) / 256;
   const double red = S > 1 ? 4.0 + (S + 1.0) * M * N * 4.0 / 6e6 : 0.0;
-  if (bt == 256) return n * (mn ? 1.75 * kt + 8.0 : 1.5 * kt + 6.5) + red;
+  if (bt == 256) return n * ((mn ? 1.6 : 1.5) * kt + 6.5) + red;
   if (bt == 128) return (n == 1 ? 0.62 * kt + 5.0 : n * (0.39 * kt + 4.5)) + red;
   return 3.0 + n * ((n > 16 ? 1.8 : 0.6) + 0.215 * kt) + red;
 }
@@ -885,7 +885,7 @@ GemmPlan gemm_plan(const GemmArgs& a, int alay, int blay, int epi) {
     } else {
       S256 = 1;
     }
-  } else if (may_split && !kl && a.K >= 1024 && tile_vec(a, alay, blay)) {
+  } else if (may_split && !kl && !a.no_tail_split && a.K >= 1024 && tile_vec(a, alay, blay)) {
     const long fit = a.splitk_ws_elems / std::max(1L, (long)a.M * a.N);
     const int smax = (int)std::min<long>(std::min<long>(a.splitk_max > 0 ? a.splitk_max : 16, a.K / 512), fit);
     slices(128, smax);

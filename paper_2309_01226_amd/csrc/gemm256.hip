@@ -84,6 +84,11 @@ constexpr int OPE = BT * BK;          // bf16 elements of one operand tile
 // one that the steady-state loop issues to keep its wait counts constant)
 // reads zeros and touches no memory.
 
+// M/N-contiguous operands lie [64 k][256 rows] (512 bytes per k-row) and are read
+// with the transposing LDS read; chunk c (of 32) of k-row k is stored at c ^ 4 (k % 4), so
+// that the 4 k-rows x 4 chunks that 32 lanes read at once are on distinct banks.
+
+template <int LAY>
 struct Loader {
   static constexpr int NI = (BT * BK * 2 / 1024) / 4;  // copy instructions per wave
   uint32_t off[NI];  // byte offsets relative to (tile row 0, k0)
@@ -92,69 +97,73 @@ struct Loader {
     const int lane = threadIdx.x & 63;
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int row = 8 * (4 * i + wave) + lane / 8;
-      const int c = (lane % 8) ^ swz_k(row);
-      off[i] = row < nrows ? (uint32_t)(((long)row * ld + 8 * c) * 2) : OOB;
-      kof[i] = 8 * c;
+      if (LAY == LAY_K) {
+        const int row = 8 * (4 * i + wave) + lane / 8;
+        const int c = (lane % 8) ^ swz_k(row);
+        off[i] = row < nrows ? (uint32_t)(((long)row * ld + 8 * c) * 2) : OOB;
+        kof[i] = 8 * c;
+      } else {
+        const int k = 2 * (4 * i + wave) + lane / 32;
+        const int row = 8 * ((lane % 32) ^ (4 * (k & 3)));
+        off[i] = row < nrows ? (uint32_t)(((long)k * ld + row) * 2) : OOB;
+        kof[i] = k;
+      }
     }
   }
   template <int I0 = 0, int I1 = NI>
-  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, int k0, int K, bf16* dst,
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, int k0, int K, long ld, bf16* dst,
                                         int wave) const {
+    const uint32_t so = LAY == LAY_K ? (uint32_t)(k0 * 2) : (uint32_t)((long)k0 * ld * 2);
 #pragma unroll
     for (int i = I0; i < I1; ++i) {
       const uint32_t o = (k0 + kof[i] < K) ? off[i] : OOB;
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds(dst + (4 * i + wave) * 512), 16, o,
-                                               (uint32_t)(k0 * 2), 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds(dst + (4 * i + wave) * 512), 16, o, so, 0, 0);
     }
   }
 };
 
-// Fragment addressing of one operand inside a stage, for the wave's 128-row
-// (or column) half `w0` (0 or 128).  frag(sub, ks) is the 32 x 16 MFMA operand
+// The transposing LDS read through a restrict-qualified pointer: its alias-scope
+// information keeps the compiler from making it wait for the LDS copies in flight,
+// which land in other slots.
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
+__device__ __forceinline__ bf16x4 ds_read_tr(const lds_bf16x4* __restrict__ p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4bf16(const_cast<lds_bf16x4*>(p));
+}
+
+// Fragment addressing of one operand inside a slot, for the wave's 128-row
+// (or column) half `w0` (0 or 128).  read(sub, ks) is the 32 x 16 MFMA operand
 // of rows w0 + 32 sub .. + 31, k = 16 ks .. + 15.
+template <int LAY>
 struct Frags {
-  static constexpr int KS = BK / 16;
-  int o[KS];  // element offsets of k-step ks
+  static constexpr int KS = LAY == LAY_K ? BK / 16 : 1;
+  int o[KS];  // element offsets (K-contiguous: of k-step ks)
   __device__ __forceinline__ void init(int w0) {
     const int lane = threadIdx.x & 63;
-    const int r = lane & 31;
+    if constexpr (LAY == LAY_K) {
+      const int r = lane & 31;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) o[ks] = (w0 + r) * BK + 8 * ((2 * ks + (lane >> 5)) ^ swz_k(r));
+      for (int ks = 0; ks < KS; ++ks) o[ks] = (w0 + r) * BK + 8 * ((2 * ks + (lane >> 5)) ^ swz_k(r));
+    } else {
+      // lane group G = lane / 16 hands in k-rows 8 (G / 2) + e of rows 16 (G % 2) + 4 q
+      // (lane 4 e + q) and receives four k values of one row
+      const int G = lane >> 4, ll = lane & 15;
+      const int k = 8 * (G >> 1) + (ll >> 2);
+      const int c = w0 / 8 + 2 * (G & 1) + ((ll >> 1) & 1);
+      o[0] = k * BT + 8 * (c ^ (4 * (k & 3))) + 4 * (ll & 1);
+    }
   }
   __device__ __forceinline__ bf16x8 read(const bf16* tile, int sub, int ks) const {
-    return *reinterpret_cast<const bf16x8*>(tile + o[ks] + sub * 32 * BK);
+    if constexpr (LAY == LAY_K) {
+      return *reinterpret_cast<const bf16x8*>(tile + o[ks] + sub * 32 * BK);
+    } else {
+      // rows + 32: chunk + 4, a field of its own under the XOR; k + 4: the same k % 4
+      const bf16* q = tile + (o[0] ^ (sub << 5)) + ks * 16 * BT;
+      const bf16x4 lo = ds_read_tr((const lds_bf16x4*)lds(q));
+      const bf16x4 hi = ds_read_tr((const lds_bf16x4*)lds(q + 4 * BT));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
   }
 };
-
-__device__ __forceinline__ void read_step(bf16x8 (&fa)[4], bf16x8 (&fb)[4], const Frags& FA,
-                                          const Frags& FB, const bf16* sa, const bf16* sb, int ks) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i) fa[i] = FA.read(sa, i, ks);
-#pragma unroll
-  for (int j = 0; j < 4; ++j) fb[j] = FB.read(sb, j, ks);
-}
-
-__device__ __forceinline__ void mfma_step(floatx16 (&acc)[4][4], const bf16x8 (&fa)[4],
-                                          const bf16x8 (&fb)[4]) {
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
-}
-
-// Scheduling templates for one k-step of 16 MFMAs: one DS read after each of
-// the first ND MFMAs, and one copy after each of the first NV.
-template <int ND, int NV>
-__device__ __forceinline__ void interleave() {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if (i < NV) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    if (i < ND) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  }
-}
 
 template <int EPI, int GE>
 __device__ __forceinline__ void store4(const GemmArgs& p, long row, int col, floatx4 x) {
@@ -569,8 +578,9 @@ __device__ __forceinline__ void tile_origin(int M, int N, int bid, int& m0, int&
 // this even spacing measured 3 - 5% faster on the GPT-J shapes.
 
 // Fragment q (0 - 7) of a k-step in the order the MFMAs use it: a0, b0 - b3, a1 - a3.
-__device__ __forceinline__ void read_q(bf16x8 (&fa)[4], bf16x8 (&fb)[4], const Frags& FA,
-                                       const Frags& FB, const bf16* sa, const bf16* sb, int ks,
+template <int AL, int BL>
+__device__ __forceinline__ void read_q(bf16x8 (&fa)[4], bf16x8 (&fb)[4], const Frags<AL>& FA,
+                                       const Frags<BL>& FB, const bf16* sa, const bf16* sb, int ks,
                                        int q) {
   if (q == 0) fa[0] = FA.read(sa, 0, ks);
   else if (q <= 4) fb[q - 1] = FB.read(sb, q - 1, ks);
@@ -580,10 +590,10 @@ __device__ __forceinline__ void read_q(bf16x8 (&fa)[4], bf16x8 (&fb)[4], const F
 // One k-step: 16 MFMAs on (ca, cb); after MFMA i, fragment read i / 2 of the
 // next k-step (odd i) and copy i / 4 (i % 4 == 2).  The scheduling barrier
 // after every MFMA pins this order.
-template <typename CopyF>
+template <int AL, int BL, typename CopyF>
 __device__ __forceinline__ void kstep_ring(floatx16 (&acc)[4][4], const bf16x8 (&ca)[4],
                                            const bf16x8 (&cb)[4], bf16x8 (&na)[4], bf16x8 (&nb)[4],
-                                           const Frags& FA, const Frags& FB, const bf16* sa,
+                                           const Frags<AL>& FA, const Frags<BL>& FB, const bf16* sa,
                                            const bf16* sb, int ks, CopyF copy) {
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
@@ -595,9 +605,10 @@ __device__ __forceinline__ void kstep_ring(floatx16 (&acc)[4][4], const bf16x8 (
   }
 }
 
-template <int EPI, int GE>
+template <int AL, int BL, int EPI, int GE>
 __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
-  static_assert(5 * OPE * 2 <= 163840 && BK == 64 && Loader::NI == 8, "LDS budget / copies");
+  constexpr int NI = Loader<LAY_K>::NI;
+  static_assert(5 * OPE * 2 <= 163840 && BK == 64 && NI == 8, "LDS budget / copies");
   __shared__ __attribute__((aligned(1024))) bf16 smem[5 * OPE];
 
   const int M = p.M, N = p.N;
@@ -619,13 +630,15 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
   const int wm = wave >> 1, wn = wave & 1;
 
   __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.A + (long)m0 * p.lda + kb), (short)0, 0x7FFFFFFF, 0x00020000);
+      (void*)(p.A + (AL == LAY_K ? (long)m0 * p.lda + kb : (long)kb * p.lda + m0)), (short)0, 0x7FFFFFFF, 0x00020000);
   __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.B + (long)n0 * p.ldb + kb), (short)0, 0x7FFFFFFF, 0x00020000);
-  Loader la, lb;
+      (void*)(p.B + (BL == LAY_K ? (long)n0 * p.ldb + kb : (long)kb * p.ldb + n0)), (short)0, 0x7FFFFFFF, 0x00020000);
+  Loader<AL> la;
+  Loader<BL> lb;
   la.init(p.lda, M - m0, wave);
   lb.init(p.ldb, N - n0, wave);
-  Frags FA, FB;
+  Frags<AL> FA;
+  Frags<BL> FB;
   FA.init(wm * 128);
   FB.init(wn * 128);
 
@@ -643,12 +656,12 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
   // k offset of tile t; tiles past the last one copy zeros (every chunk at or past K)
   auto kof = [&](int t) { return t < nk ? t * BK : K; };
   // tile 0 resident; A_1 and the first half of B_1 in flight
-  la.issue(rsA, 0, K, sA(0), wave);
-  lb.issue(rsB, 0, K, sB(0), wave);
+  la.issue(rsA, 0, K, p.lda, sA(0), wave);
+  lb.issue(rsB, 0, K, p.ldb, sB(0), wave);
   wait_vm_lgkm0<0>();
   cta_barrier();
-  la.issue(rsA, kof(1), K, sA(1), wave);
-  lb.issue<0, 4>(rsB, kof(1), K, sB(1), wave);
+  la.issue(rsA, kof(1), K, p.lda, sA(1), wave);
+  lb.template issue<0, 4>(rsB, kof(1), K, p.ldb, sB(1), wave);
   bf16x8 f0a[4], f0b[4], f1a[4], f1b[4];
 #pragma unroll
   for (int q = 0; q < 8; ++q) read_q(f0a, f0b, FA, FB, sA(0), sB(0), 0, q);
@@ -662,36 +675,36 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
     __builtin_amdgcn_sched_barrier(0);
     kstep_ring(acc, f0a, f0b, f1a, f1b, FA, FB, a, b, 1, [&](int c) {
       switch (c) {
-        case 0: lb.issue<4, 5>(rsB, k1, K, b1, wave); break;
-        case 1: lb.issue<5, 6>(rsB, k1, K, b1, wave); break;
-        case 2: lb.issue<6, 7>(rsB, k1, K, b1, wave); break;
-        default: lb.issue<7, 8>(rsB, k1, K, b1, wave); break;
+        case 0: lb.template issue<4, 5>(rsB, k1, K, p.ldb, b1, wave); break;
+        case 1: lb.template issue<5, 6>(rsB, k1, K, p.ldb, b1, wave); break;
+        case 2: lb.template issue<6, 7>(rsB, k1, K, p.ldb, b1, wave); break;
+        default: lb.template issue<7, 8>(rsB, k1, K, p.ldb, b1, wave); break;
       }
     });
     kstep_ring(acc, f1a, f1b, f0a, f0b, FA, FB, a, b, 2, [&](int c) {
       switch (c) {
-        case 0: la.issue<0, 1>(rsA, k2, K, a2, wave); break;
-        case 1: la.issue<1, 2>(rsA, k2, K, a2, wave); break;
-        case 2: la.issue<2, 3>(rsA, k2, K, a2, wave); break;
-        default: la.issue<3, 4>(rsA, k2, K, a2, wave); break;
+        case 0: la.template issue<0, 1>(rsA, k2, K, p.lda, a2, wave); break;
+        case 1: la.template issue<1, 2>(rsA, k2, K, p.lda, a2, wave); break;
+        case 2: la.template issue<2, 3>(rsA, k2, K, p.lda, a2, wave); break;
+        default: la.template issue<3, 4>(rsA, k2, K, p.lda, a2, wave); break;
       }
     });
     kstep_ring(acc, f0a, f0b, f1a, f1b, FA, FB, a, b, 3, [&](int c) {
       switch (c) {
-        case 0: la.issue<4, 5>(rsA, k2, K, a2, wave); break;
-        case 1: la.issue<5, 6>(rsA, k2, K, a2, wave); break;
-        case 2: la.issue<6, 7>(rsA, k2, K, a2, wave); break;
-        default: la.issue<7, 8>(rsA, k2, K, a2, wave); break;
+        case 0: la.template issue<4, 5>(rsA, k2, K, p.lda, a2, wave); break;
+        case 1: la.template issue<5, 6>(rsA, k2, K, p.lda, a2, wave); break;
+        case 2: la.template issue<6, 7>(rsA, k2, K, p.lda, a2, wave); break;
+        default: la.template issue<7, 8>(rsA, k2, K, p.lda, a2, wave); break;
       }
     });
-    wait_vm_lgkm0<Loader::NI>();  // A_{t+1}, B_{t+1} resident; reads of tile t done
+    wait_vm_lgkm0<NI>();  // A_{t+1}, B_{t+1} resident; reads of tile t done
     cta_barrier();                // ... in every wave: A_t's and B_t's slots are free
     kstep_ring(acc, f1a, f1b, f0a, f0b, FA, FB, sA(t + 1), b1, 0, [&](int c) {
       switch (c) {
-        case 0: lb.issue<0, 1>(rsB, k2, K, b2, wave); break;
-        case 1: lb.issue<1, 2>(rsB, k2, K, b2, wave); break;
-        case 2: lb.issue<2, 3>(rsB, k2, K, b2, wave); break;
-        default: lb.issue<3, 4>(rsB, k2, K, b2, wave); break;
+        case 0: lb.template issue<0, 1>(rsB, k2, K, p.ldb, b2, wave); break;
+        case 1: lb.template issue<1, 2>(rsB, k2, K, p.ldb, b2, wave); break;
+        case 2: lb.template issue<2, 3>(rsB, k2, K, p.ldb, b2, wave); break;
+        default: lb.template issue<3, 4>(rsB, k2, K, p.ldb, b2, wave); break;
       }
     });
   }
@@ -712,224 +725,17 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
   }
 }
 
-// An M/N-contiguous operand tile (64 k-rows of 256 contiguous m or n) staged
-// through registers and written to LDS in the K-contiguous layout, so that
-// its fragments are read with plain 16-byte LDS reads like a K-contiguous
-// operand's (the transposing LDS read costs more LDS time than the MFMAs
-// leave).  Lane (c, g) loads the 8 x 8 block of k-rows 8g .. 8g + 7 and
-// columns 8c .. 8c + 7 (one 16-byte load per k-row), transposes it with byte
-// permutes and writes it as eight 16-byte pieces: row 8c + e, logical chunk g
-// (swizzled like the copied K-contiguous tiles).  Lane assignment:
-// c = 8 wave + 2 (lane >> 4) + ((lane >> 3) & 1), g = lane & 7, so that one
-// load instruction reads eight whole 128-byte lines (8 lanes per k-row), and
-// the 16 lanes of a quarter-wave write 16 different (chunk, row parity) bank
-// groups: of the two c in a quarter-wave, the odd one writes the two rows of
-// each pair in the opposite order.
-struct RegStage {
-  static constexpr int NL = 8;  // loads per lane per K-tile
-  uint32_t off;                 // byte offset of (k-row 8g, column 8c), or OOB past M / N
-  int kr;                       // 8g
-  uint32_t sel0, sel1;          // v_perm selectors of even / odd writes
-  uint32_t wa[4];               // LDS element offset of write 2s (write 2s + 1: ^ 64)
-  u32x4 r[8];                   // r[i]: k-row 8g + i, columns 8c .. 8c + 7
-  __device__ __forceinline__ void init(long ld, int nrows) {
-    const int t = threadIdx.x, lane = t & 63;
-    const int c = 8 * (t >> 6) + 2 * (lane >> 4) + ((lane >> 3) & 1), g = lane & 7;
-    const int cp = c & 1;
-    kr = 8 * g;
-    off = 8 * c < nrows ? (uint32_t)(((long)kr * ld + 8 * c) * 2) : OOB;
-    // element h of a pair of bf16 from k-rows 2t (low half) and 2t + 1 (high)
-    sel0 = cp ? 0x07060302u : 0x05040100u;  // writes 2s: element cp of dword s
-    sel1 = cp ? 0x05040100u : 0x07060302u;  // writes 2s + 1: element 1 - cp
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      wa[q] = (uint32_t)(512 * c + 128 * q + 64 * cp + 8 * (g ^ ((4 * cp + q) & 7)));
-  }
-  template <int I0 = 0, int I1 = NL>
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int k0, int K, long ld) {
-#pragma unroll
-    for (int i = I0; i < I1; ++i) {
-      const uint32_t o = (k0 + kr + i < K) ? off : OOB;
-      r[i] = __builtin_bit_cast(
-          u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, o, (uint32_t)((long)(k0 + i) * ld * 2), 0));
-    }
-  }
-  __device__ __forceinline__ void store(bf16* tile) const {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const int q = j >> 1;
-      const uint32_t sel = (j & 1) ? sel1 : sel0;
-      u32x4 v;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(r[2 * e + 1][q], r[2 * e][q], sel);
-      *reinterpret_cast<u32x4*>(tile + ((j & 1) ? (wa[q] ^ 64u) : wa[q])) = v;
-    }
-  }
-};
-
-// Scheduling template for one k-step of 16 MFMAs: after MFMA i, one DS read
-// if i < ND, one DS write if i < NW, one VMEM instruction if i < NV.
-template <int ND, int NW, int NV>
-__device__ __forceinline__ void interleave3() {
-#pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-    if (i < NV) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
-    if (i < NW) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-    if (i < ND) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-  }
-}
-
-// GEMM with at least one M/N-contiguous operand: those operands are staged
-// through registers (RegStage), a K-contiguous one is copied straight into
-// LDS; two LDS stages, both operands in the K-contiguous layout.  Per K-tile
-// kt, the staged operands of tile kt + 1 are written into the stage that tile
-// kt - 1 released, and the registers are then reloaded with tile kt + 2:
-//  * one staged operand: write in k-step 0, loads in k-step 1, and the copies
-//    of the other operand's tile kt + 2 after the barrier;
-//  * two: A written in k-step 0, B in k-step 1; A's loads over k-steps 0 - 1,
-//    B's over k-steps 2 - 3, so that the address unit sees four loads per
-//    k-step instead of sixteen at once.
-template <int AL, int BL, int EPI, int GE>
-__global__ __launch_bounds__(NT, 1) void gemm256_rs_kernel(GemmArgs p) {
-  constexpr bool RA = AL == LAY_MN, RB = BL == LAY_MN;
-  constexpr int NR = (RA ? 1 : 0) + (RB ? 1 : 0);
-  constexpr int NI = Loader::NI;  // copies per wave, or loads per lane, per operand tile
-  static_assert(NR >= 1 && NI == RegStage::NL, "staged operand count");
-  __shared__ __attribute__((aligned(1024))) bf16 smem[4 * OPE];
-
-  const int M = p.M, N = p.N, K = p.K;
-  int m0, n0;
-  tile_origin(M, N, xcd_order_id(), m0, n0);
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave >> 1, wn = wave & 1;
-  __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.A + (RA ? (long)m0 : (long)m0 * p.lda)), (short)0, 0x7FFFFFFF, 0x00020000);
-  __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.B + (RB ? (long)n0 : (long)n0 * p.ldb)), (short)0, 0x7FFFFFFF, 0x00020000);
-  Loader la, lb;
-  RegStage ra, rb;
-  if constexpr (RA) ra.init(p.lda, M - m0); else la.init(p.lda, M - m0, wave);
-  if constexpr (RB) rb.init(p.ldb, N - n0); else lb.init(p.ldb, N - n0, wave);
-  Frags FA, FB;
-  FA.init(wm * 128);
-  FB.init(wn * 128);
-
-  floatx16 acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-  auto copy = [&](int k0, bf16* st) {
-    if constexpr (!RA) la.issue(rsA, k0, K, st, wave);
-    if constexpr (!RB) lb.issue(rsB, k0, K, st + OPE, wave);
-  };
-  const int nk = (K + BK - 1) / BK;
-  // tile 0 and the registers of tile 1; the operations of tile 1 (NI per
-  // operand) are the last issued, so waiting down to 2 NI leaves tile 0 resident
-  if constexpr (RA) ra.load(rsA, 0, K, p.lda);
-  if constexpr (RB) rb.load(rsB, 0, K, p.ldb);
-  copy(0, smem);
-  if constexpr (RA) ra.store(smem);
-  if constexpr (RB) rb.store(smem + OPE);
-  if constexpr (RA) ra.load(rsA, BK, K, p.lda);
-  if constexpr (RB) rb.load(rsB, BK, K, p.ldb);
-  copy(BK, smem + 2 * OPE);
-  wait_vm_lgkm0<2 * NI>();
-  cta_barrier();
-
-  bf16x8 f0a[4], f0b[4], f1a[4], f1b[4];
-  read_step(f0a, f0b, FA, FB, smem, smem + OPE, 0);
-  for (int kt = 0; kt + 1 < nk; ++kt) {
-    bf16* cur = smem + (kt & 1) * 2 * OPE;
-    bf16* nxt = smem + ((kt + 1) & 1) * 2 * OPE;
-    const int k2 = (kt + 2) * BK;
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f0a, f0b);
-    read_step(f1a, f1b, FA, FB, cur, cur + OPE, 1);
-    if constexpr (NR == 2) {
-      ra.store(nxt);
-      ra.template load<0, NI / 2>(rsA, k2, K, p.lda);
-      interleave3<8, 8, NI / 2>();
-    } else {
-      if constexpr (RA) ra.store(nxt);
-      else rb.store(nxt + OPE);
-      interleave3<8, 8, 0>();
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f1a, f1b);
-    read_step(f0a, f0b, FA, FB, cur, cur + OPE, 2);
-    if constexpr (NR == 2) {
-      rb.store(nxt + OPE);
-      ra.template load<NI / 2, NI>(rsA, k2, K, p.lda);
-      interleave3<8, 8, NI / 2>();
-    } else {
-      if constexpr (RA) ra.load(rsA, k2, K, p.lda);
-      else rb.load(rsB, k2, K, p.ldb);
-      interleave3<8, 0, NI>();
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f0a, f0b);
-    read_step(f1a, f1b, FA, FB, cur, cur + OPE, 3);
-    if constexpr (NR == 2) {
-      rb.template load<0, NI / 2>(rsB, k2, K, p.ldb);
-      interleave3<8, 0, NI / 2>();
-    } else {
-      interleave3<8, 0, 0>();
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    // this wave's copies of tile kt + 1 (issued before the register loads of
-    // tile kt + 2), its LDS writes and reads; then every other wave's
-    wait_vm_lgkm0<NR * NI>();
-    cta_barrier();
-    copy(k2, cur);
-    if constexpr (NR == 2) rb.template load<NI / 2, NI>(rsB, k2, K, p.ldb);
-    read_step(f0a, f0b, FA, FB, nxt, nxt + OPE, 0);
-    mfma_step(acc, f1a, f1b);
-    interleave3<8, 0, NR == 2 ? NI / 2 : NI>();
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  {
-    const bf16* cur = smem + ((nk - 1) & 1) * 2 * OPE;
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f0a, f0b);
-    read_step(f1a, f1b, FA, FB, cur, cur + OPE, 1);
-    interleave<8, 0>();
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f1a, f1b);
-    read_step(f0a, f0b, FA, FB, cur, cur + OPE, 2);
-    interleave<8, 0>();
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f0a, f0b);
-    read_step(f1a, f1b, FA, FB, cur, cur + OPE, 3);
-    interleave<8, 0>();
-    __builtin_amdgcn_sched_barrier(0);
-    mfma_step(acc, f1a, f1b);
-  }
-  wait_vm_lgkm0<0>();  // the register loads and copies past the last tile
-  __syncthreads();
-  epilogue<EPI, GE>(p, acc, reinterpret_cast<float*>(smem), m0, n0, wave, lane);
-}
-
 template <int AL, int BL, int EPI>
 hipError_t launch_e(const GemmArgs& a, hipStream_t s) {
   const int slices = (EPI == EPI_F32 && a.splitk > 1) ? a.splitk : 1;
   dim3 grid((unsigned)(sat_cdiv(a.M, BT) * sat_cdiv(a.N, BT) * slices));
-  const bool ge = (EPI == EPI_BF16 || EPI == EPI_DGELU_BF16) && a.gelu_erf;
-  if constexpr (EPI == EPI_ADAMW) {
-    static_assert(AL == LAY_K && BL == LAY_K, "optimizer epilogue: K-contiguous operands");
-    hipLaunchKernelGGL((gemm256_kernel<EPI, 0>), grid, dim3(NT), 0, s, a);
-  } else if constexpr (AL == LAY_K && BL == LAY_K) {
-    if (ge) hipLaunchKernelGGL((gemm256_kernel<EPI, 1>), grid, dim3(NT), 0, s, a);
-    else hipLaunchKernelGGL((gemm256_kernel<EPI, 0>), grid, dim3(NT), 0, s, a);
-  } else {
-    if (ge) hipLaunchKernelGGL((gemm256_rs_kernel<AL, BL, EPI, 1>), grid, dim3(NT), 0, s, a);
-    else hipLaunchKernelGGL((gemm256_rs_kernel<AL, BL, EPI, 0>), grid, dim3(NT), 0, s, a);
+  if constexpr (EPI == EPI_BF16 || EPI == EPI_DGELU_BF16) {
+    if (a.gelu_erf) {
+      hipLaunchKernelGGL((gemm256_kernel<AL, BL, EPI, 1>), grid, dim3(NT), 0, s, a);
+      return hipGetLastError();
+    }
   }
+  hipLaunchKernelGGL((gemm256_kernel<AL, BL, EPI, 0>), grid, dim3(NT), 0, s, a);
   return hipGetLastError();
 }
 
@@ -941,7 +747,7 @@ hipError_t launch_l(const GemmArgs& a, int epi, hipStream_t s) {
     case EPI_BF16: return launch_e<AL, BL, EPI_BF16>(a, s);
     case EPI_DGELU_BF16: return launch_e<AL, BL, EPI_DGELU_BF16>(a, s);
     case EPI_ADAMW:
-      if constexpr (AL == LAY_K && BL == LAY_K) return launch_e<AL, BL, EPI_ADAMW>(a, s);
+      if constexpr (AL == BL) return launch_e<AL, BL, EPI_ADAMW>(a, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -979,10 +785,10 @@ bool gemm256_eligible(const GemmArgs& a, int alay, int blay, int epi) {
                     : (a.ldb < r8(a.N) || ((long)a.K + 256) * a.ldb * 2 >= lim))
     return false;
   if (epi == EPI_ADAMW) {
-    // K-contiguous operands; 4-column vectors of W and 8-row pieces of its
+    // operands of one layout; 4-column vectors of W and 8-row pieces of its
     // transposed copy; the gradient itself only if requested
     auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-    return alay == LAY_K && blay == LAY_K && a.N % 8 == 0 && a16(a.opt_p) && a16(a.opt_m) &&
+    return alay == blay && a.N % 8 == 0 && a16(a.opt_p) && a16(a.opt_m) &&
            a16(a.opt_v) && al(a.opt_sh, 8) && a16(a.opt_sht) && a.opt_trows % 8 == 0 &&
            a.opt_trows >= a.M && (a.out == nullptr || (a16(a.out) && a.ldo % 4 == 0));
   }

@@ -95,7 +95,7 @@ struct GemmArgs {
   // + n] (cdiv(M, R) rows; launch_colsum_partials then adds them in order).
   float* colsum_part;
   // Keeps launch_gemm from splitting the rows of a mostly empty last round
-  // (gemm_tail_split): a weight gradient whose AdamW step may instead be
+  // (gemm_tail_split), or any product with an M/N-contiguous operand: a weight gradient whose AdamW step may instead be
   // fused into this kernel's epilogue must sum in the same order either way.
   int no_tail_split;
   ConvTaps cv;  // launch_gemm_conv only

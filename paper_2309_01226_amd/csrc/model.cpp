@@ -376,15 +376,14 @@ size_t carve(sat_model* M, char* base) {
   M->dqkv = c.take<bf16>(T * D.qkv_ld);
   M->du = gptj ? nullptr : c.take<bf16>(T * m);
   M->dout = c.take<bf16>(T * d);
-  // Token-contiguous copies of the weight-gradient operands only where a product
-  // needs them: the fused AdamW epilogue exists for K-contiguous operands, and
-  // the blocks' copies are shared by all of a block's products.
   bool fused_block = false, fused_head = false;
   for (const auto& p : M->params) {
     if (p.fused_opt && p.group >= 0) (p.group == D.L ? fused_head : fused_block) = true;
   }
   M->trans_blocks = T % 8 == 0 && fused_block;
-  M->trans_head = R % 8 == 0 && fused_head;
+  // the head's product on its row-major operands must stay below 2^31 bytes of
+  // each (buffer offsets)
+  M->trans_head = R % 8 == 0 && fused_head && (R + 256L) * std::max(D.Vp, (int)d) * 2 >= (1L << 31);
   {
     long na = 0, nb = 0;
     if (M->trans_blocks) {

@@ -230,47 +230,51 @@ sat_status sat_run_forward(sat_model* M, const void* inputs, const int32_t* labe
 // pidx: the weight's parameter index.  When its AdamW step is fused, the
 // product's epilogue applies the step to the weight (and writes the gradient
 // only if the model keeps gradients).
-// The product on token-contiguous operands yT [Mr, T] and xT [N, T], on
-// stream st (the model's, or the weight-gradient stream).
+// The product on operands of layout `lay` (LAY_K: token-contiguous copies [Mr, T] and
+// [N, T]; LAY_MN: the row-major tensors), on stream st (the model's, or the
+// weight-gradient stream).
+static sat_status wgrad_run(sat_model* M, hipStream_t st, int lay, const bf16* y, long ldy, const bf16* x,
+                            long ldx, int Mr, int N, int T, int pidx, int tk = TK_ALL_GEMM) {
+  const ParamDesc& P = M->params[pidx];
+  GemmArgs w = gargs(y, ldy, x, ldx, Mr, N, T, grad(M, pidx), P.cols);
+  if (P.fused_opt) {
+    if (M->opt_fused) {
+      if (!M->opt_keep_grads) w.out = nullptr;
+      w.opt_p = M->master + P.off;
+      w.opt_m = M->mom + P.off;
+      w.opt_v = M->vel + P.off;
+      w.opt_sh = M->shadow + P.off;
+      w.opt_sht = M->shadow_t + P.toff;
+      w.opt_trows = P.trows;
+      w.opt_c = M->adamw_c;
+      if (!gemm256_eligible(w, lay, lay, EPI_ADAMW)) {
+        sat_set_error("internal: fused optimizer step of %s not eligible for the 256 x 256 kernel",
+                      P.name.c_str());
+        return SAT_EINVAL;
+      }
+      return gemm(M, w, lay, lay, EPI_ADAMW, tk, st);
+    }
+    // the same sums as the fused epilogue's (nothing split), so that the separate
+    // AdamW pass gives the fused step's parameters
+    w.no_tail_split = 1;
+  }
+  if (lay == LAY_K) w.no_tail_split = 1;
+  return gemm(M, w, lay, lay, EPI_F32, tk, st);
+}
 static sat_status wgrad_t(sat_model* M, hipStream_t st, const bf16* yT, const bf16* xT, int Mr,
                           int N, int T, int pidx, int tk = TK_ALL_GEMM) {
-  const ParamDesc& P = M->params[pidx];
-  GemmArgs w = gargs(yT, T, xT, T, Mr, N, T, grad(M, pidx), P.cols);
-  if (M->opt_fused && P.fused_opt) {
-    if (!M->opt_keep_grads) w.out = nullptr;
-    w.opt_p = M->master + P.off;
-    w.opt_m = M->mom + P.off;
-    w.opt_v = M->vel + P.off;
-    w.opt_sh = M->shadow + P.off;
-    w.opt_sht = M->shadow_t + P.toff;
-    w.opt_trows = P.trows;
-    w.opt_c = M->adamw_c;
-    if (!gemm256_eligible(w, LAY_K, LAY_K, EPI_ADAMW)) {
-      sat_set_error("internal: fused optimizer step of %s not eligible for the 256 x 256 kernel",
-                    P.name.c_str());
-      return SAT_EINVAL;
-    }
-    return gemm(M, w, LAY_K, LAY_K, EPI_ADAMW, tk, st);
-  }
-  // the same sums as the fused epilogue's (no row split of the last round),
-  // so that the separate AdamW pass gives the fused step's parameters
-  w.no_tail_split = 1;
-  return gemm(M, w, LAY_K, LAY_K, EPI_F32, tk, st);
+  return wgrad_run(M, st, LAY_K, yT, T, xT, T, Mr, N, T, pidx, tk);
 }
 
 static sat_status wgrad(sat_model* M, bool trans, bool y_ready, const bf16* Y, long ldy,
                         int ycols, const bf16* X, long ldx, int Mr, int N, int T, int pidx,
                         int tk = TK_ALL_GEMM) {
-  const ParamDesc& P = M->params[pidx];
-  float* out = grad(M, pidx);
-  const long ldo = P.cols;
   if (trans) {
     if (!y_ready) SAT_HIP(launch_transpose_bf16(Y, ldy, M->tA, T, T, ycols, M->stream));
     SAT_HIP(launch_transpose_bf16(X, ldx, M->tB, T, T, N, M->stream));
     return wgrad_t(M, M->stream, M->tA, M->tB, Mr, N, T, pidx, tk);
   }
-  GemmArgs w = gargs(Y, ldy, X, ldx, Mr, N, T, out, ldo);
-  return gemm(M, w, LAY_MN, LAY_MN, EPI_F32, tk);
+  return wgrad_run(M, M->stream, LAY_MN, Y, ldy, X, ldx, Mr, N, T, pidx, tk);
 }
 
 // The fc1 bias gradient is the column sum of the fc2 input-gradient product's
