@@ -19,8 +19,10 @@
 // blocks (the score and dP tiles are recomputed in both).
 //
 // This file serves head dims 16, 32 (first-generation kernels, whose output
-// may be split into head-dim slices) and 128 (the pipelined *_fast kernels);
-// head dims 64 and 80 run in attn_small.hip and 256 in attn256.hip.
+// may be split into head-dim slices) and the calls of 128 that attn_small.hip does
+// not take: outputs aligned to less than 8 bytes, a scale <= 0 (the pipelined *_fast
+// kernels); head dims 64, 80 and all other calls of 128 run in attn_small.hip and 256
+// in attn256.hip.
 #include "common.h"
 #include "kernels.h"
 
@@ -1122,8 +1124,8 @@ struct AttnCfg {
 };
 
 // Head dims 16 and 32: the first-generation kernels; 128: the pipelined
-// ones.  64, 80 and 256 run only in their own files' kernels (attn_small.hip,
-// attn256.hip), which the callers below pick first.
+// ones, where attn_small.hip refuses the call.  64, 80 and 256 run only in their own
+// files' kernels (attn_small.hip, attn256.hip), which the callers below pick first.
 template <int DH>
 hipError_t fwd_launch(const AttnArgs& a, hipStream_t s) {
   static_assert(DH == 16 || DH == 32 || DH == 128, "head dim served by attn_small / attn256");
@@ -1172,7 +1174,7 @@ hipError_t launch_attention_fwd(const AttnArgs& a, hipStream_t s) {
   switch (a.dh) {
     case 16: return fwd_launch<16>(a, s);
     case 32: return fwd_launch<32>(a, s);
-    case 128: return fwd_launch<128>(a, s);
+    case 128: return attn_small_fwd_eligible(a) ? launch_attn_small_fwd(a, s) : fwd_launch<128>(a, s);
     case 64:
     case 80: return attn_small_fwd_eligible(a) ? launch_attn_small_fwd(a, s) : hipErrorInvalidValue;
     case 256: return attn256_fwd_eligible(a) ? launch_attn256_fwd(a, s) : hipErrorInvalidValue;
@@ -1188,7 +1190,9 @@ hipError_t launch_attention_bwd(const AttnBwdArgs& a, hipStream_t s) {
   switch (a.f.dh) {
     case 16: return bwd_launch<16>(a, s);
     case 32: return bwd_launch<32>(a, s);
-    case 128: return bwd_launch<128>(a, s);
+    case 128:  // attn_small writes dQ before it reads Q and dO again
+      return attn_small_bwd_eligible(a) && a.dq != a.f.q && a.dq != a.dout ? launch_attn_small_bwd(a, s)
+                                                                          : bwd_launch<128>(a, s);
     case 64:
     case 80: return attn_small_bwd_eligible(a) ? launch_attn_small_bwd(a, s) : hipErrorInvalidValue;
     case 256:

@@ -1,4 +1,4 @@
-// Attention forward and backward for 64- and 80-wide heads (GPT-2-style
+// Attention forward and backward for 64-, 80- and 128-wide heads (GPT-2-style
 // decoders, ViT-H/14), causal or bidirectional, on gfx950 MFMA
 // (v_mfma_f32_32x32x16_bf16, bf16 operands, fp32 accumulation).
 //
@@ -25,13 +25,22 @@
 // 17.6 / 52 us; 2 x 12 of 2048 x 80 causal 45 / 128 and 37 / 104; 8 x 12 of 1024 x 64
 // causal 31 / 84 and 28 / 76.
 //
+// 128-wide heads have twice the MFMA work per score of 64-wide ones, in twice the
+// registers: the row fragments are read four k-steps at a time, and the dK/dV kernel,
+// with 256 registers of operands and accumulators, runs one wave per SIMD whose two
+// sub-tiles of a block the compiler overlaps instead.  Against the kernels
+// that stage V and dO^T through register transposes (attention.hip), forward /
+// backward: 2 x 16 heads of 2048 causal 218 / 723 and 53 / 155 us; 32 x 12 of 512
+// causal 186 / 653 and 56 / 200; 7 x 16 of 1500 502 / 1617 and 151 / 517; 1 x 8 of 100
+// causal 10.6 / 34 and 8.9 / 18.
+//
 // Workgroup = 2 to 4 waves x 32 rows (queries for the forward and dQ kernels,
 // keys for the dK/dV kernel) of one (batch, head); the other operand streams
 // through LDS in blocks of 64 rows, two stages, copied HBM -> LDS with
 // buffer_load ... lds (no VGPR staging).
 //
 // Tile layout in LDS (R rows of a [rows][dh] bf16 block):
-//  * dims 0..63: R rows of 128 B, eight 16-byte chunks, chunk c of row r
+//  * each 64 dims (0..63; of 128-wide heads also 64..127): R rows of 128 B, eight 16-byte chunks, chunk c of row r
 //    stored at c ^ swz(r).  Row-fragment reads (16 lanes = 16 consecutive
 //    rows at one chunk) and transposing reads ds_read_b64_tr_b16 (32 lanes
 //    = 4 consecutive rows x 4 chunks) then both touch 16 distinct 16-byte
@@ -70,9 +79,11 @@ __device__ __forceinline__ lds_void* lds(const bf16* p) { return (lds_void*)(con
 
 template <int DH>
 struct Cfg {
-  static_assert(DH == 64 || DH == 80, "64- or 80-wide heads");
+  static_assert(DH == 64 || DH == 80 || DH == 128, "64-, 80- or 128-wide heads");
   static constexpr bool TAIL = DH == 80;
+  static constexpr int PARTS = DH / 64;      // 64-dim parts of a staged tile
   static constexpr int KS = DH / 16;         // k-steps over the head dims
+  static constexpr int RS = DH == 128 ? 4 : KS;  // k-steps whose row fragments are read together
   static constexpr int OT = (DH + 31) / 32;  // 32-dim output tiles
 };
 
@@ -138,13 +149,13 @@ template <int DH, int R, int NW>
 __device__ __forceinline__ void copy_tile(__amdgpu_buffer_rsrc_t rs, long ld, int nvalid, bf16* dst,
                                           int wave) {
   const int lane = threadIdx.x & 63;
-  constexpr int NM = R / 8;  // 1 KB instructions of the 64-dim part
+  constexpr int NM = R / 8 * Cfg<DH>::PARTS;  // 1 KB instructions of the 64-dim parts
 #pragma unroll
   for (int i = 0; i < (NM + NW - 1) / NW; ++i) {
     const int j = NW * i + wave;
     if (NM % NW == 0 || j < NM) {
-      const int row = 8 * j + (lane >> 3);
-      const int c = (lane & 7) ^ swz(row);
+      const int row = 8 * (j % (R / 8)) + (lane >> 3);
+      const int c = 8 * (j / (R / 8)) + ((lane & 7) ^ swz(row));
       const uint32_t o = row < nvalid ? (uint32_t)(((long)row * ld + 8 * c) * 2) : OOB;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, lds(dst + j * 512), 16, o, 0, 0, 0);
     }
@@ -163,9 +174,9 @@ __device__ __forceinline__ void copy_tile(__amdgpu_buffer_rsrc_t rs, long ld, in
 // Lane-dependent LDS offsets of the two kinds of tile read.
 template <int DH, int R>
 struct TileOfs {
-  int rf[4];   // row fragment, k-step c < 4: row lane % 32, dims 16 c + 8 g .. + 7
+  int rf[4];   // row fragment, k-step c % 4 of a 64-dim part: row lane % 32, dims 16 c + 8 g .. + 7
   int rft;     // row fragment of k-step 4 (80-wide heads)
-  int tr[2];   // transposed read, output tile ot < 2, 16-row step 0, low half
+  int tr[2];   // transposed read, output tile ot % 2 of a 64-dim part, 16-row step 0, low half
   int trt;     // transposed read of output tile 2 (80-wide heads)
   __device__ __forceinline__ void init(int lane) {
     const int g = lane >> 5, l31 = lane & 31;
@@ -186,18 +197,19 @@ struct TileOfs {
   }
   // Row fragment of k-step c for rows 32 u + lane % 32.
   __device__ __forceinline__ bf16x8 row(const bf16* tile, int u, int c) const {
-    const int o = c < 4 ? rf[c & 3] + 32 * u * 64 : rft + 32 * u * 8;
+    const int o = c < 4 * Cfg<DH>::PARTS ? rf[c & 3] + (c >> 2) * R * 64 + 32 * u * 64 : rft + 32 * u * 8;
     return *reinterpret_cast<const bf16x8*>(tile + o);
   }
   // Transposed operand (rows = head dims 32 ot + lane % 32, k = 16 tile rows
   // 16 kk .. + 15 in the accumulator permutation) of output tile ot.
   __device__ __forceinline__ bf16x8 trans(const bf16* tile, int kk, int ot) const {
     bf16x4 lo, hi;
-    if (ot < 2) {
-      const int o = tr[ot & 1] + 16 * kk * 64;
-      lo = ds_read_tr((const lds_bf16x4*)lds(tile + o));
+    if (ot < 2 * Cfg<DH>::PARTS) {
+      const int part = (ot >> 1) * R * 64 + 16 * kk * 64;
+      const int o = tr[ot & 1];
+      lo = ds_read_tr((const lds_bf16x4*)lds(tile + o + part));
       // rows + 8 flip bit 1 of swz, i.e. chunk bit 1
-      hi = ds_read_tr((const lds_bf16x4*)lds(tile + ((o ^ 16) + 8 * 64)));
+      hi = ds_read_tr((const lds_bf16x4*)lds(tile + (o ^ 16) + 8 * 64 + part));
     } else {
       const int o = trt + 16 * kk * 8;
       lo = ds_read_tr((const lds_bf16x4*)lds(tile + o));
@@ -260,18 +272,19 @@ __device__ __forceinline__ void fwd_block(FwdState<DH>& st, const TileOfs<DH, KB
                                           const bf16* Vs, float sc, bool two, int lim_rel) {
   using C = Cfg<DH>;
   floatx16 s0 = zero16(), s1 = zero16();
-  {
-    bf16x8 k0[C::KS], k1[C::KS];
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) {
-      k0[c] = to.row(Ks, 0, c);
-      k1[c] = to.row(Ks, 1, c);
+  for (int c0 = 0; c0 < C::KS; c0 += C::RS) {
+    bf16x8 k0[C::RS], k1[C::RS];
+#pragma unroll
+    for (int c = 0; c < C::RS; ++c) {
+      k0[c] = to.row(Ks, 0, c0 + c);
+      k1[c] = to.row(Ks, 1, c0 + c);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) {
-      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.qf[c], s0, 0, 0, 0);
-      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.qf[c], s1, 0, 0, 0);
+    for (int c = 0; c < C::RS; ++c) {
+      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.qf[c0 + c], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.qf[c0 + c], s1, 0, 0, 0);
     }
   }
   bf16x8 vf[PF ? PF : 1][C::OT];
@@ -427,18 +440,19 @@ __device__ __forceinline__ void dkdv_sub(DkvState<DH>& st, const TileOfs<DH, KB>
                                          int g, float sc, int lim_q, int lim_k) {
   using C = Cfg<DH>;
   floatx16 x = zero16(), y = zero16();
-  {
-    bf16x8 k0[C::KS], k1[C::KS];
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) {
-      k0[c] = to.row(Qs, u, c);
-      k1[c] = to.row(dOs, u, c);
+  for (int c0 = 0; c0 < C::KS; c0 += C::RS) {
+    bf16x8 k0[C::RS], k1[C::RS];
+#pragma unroll
+    for (int c = 0; c < C::RS; ++c) {
+      k0[c] = to.row(Qs, u, c0 + c);
+      k1[c] = to.row(dOs, u, c0 + c);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) {
-      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.kf[c], x, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.vf[c], y, 0, 0, 0);
+    for (int c = 0; c < C::RS; ++c) {
+      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.kf[c0 + c], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.vf[c0 + c], y, 0, 0, 0);
     }
   }
   bf16x8 pb[2], db[2];
@@ -468,7 +482,7 @@ __device__ __forceinline__ void dkdv_sub(DkvState<DH>& st, const TileOfs<DH, KB>
 }
 
 template <int DH, int NW>
-__global__ __launch_bounds__(64 * NW, 2) void attn_small_dkdv_kernel(AttnBwdArgs a, int group) {
+__global__ __launch_bounds__(64 * NW, DH == 128 ? 1 : 2) void attn_small_dkdv_kernel(AttnBwdArgs a, int group) {
   using C = Cfg<DH>;
   constexpr int BQ = KB, WGR = NW * WR;
   constexpr int QT = BQ * DH;
@@ -564,7 +578,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_small_dkdv_kernel(AttnBwdArgs
     const float* l2s = reinterpret_cast<const float*>(Qs + 2 * QT);
     if (j + 1 < nqb) fetch(j + 1);
 #pragma unroll
-    for (int u = 0; u < 2; ++u) { dkdv_sub<DH, false>(st, to, Qs, Qs + QT, l2s, l2s + BQ, u, g, sc, 0, 0); __builtin_amdgcn_sched_barrier(0); }
+    for (int u = 0; u < 2; ++u) { dkdv_sub<DH, false>(st, to, Qs, Qs + QT, l2s, l2s + BQ, u, g, sc, 0, 0); if (DH != 128) __builtin_amdgcn_sched_barrier(0); }
     next(j);
   }
   for (; j < nqb; ++j) {
@@ -598,18 +612,19 @@ __device__ __forceinline__ void dq_sub(DqState<DH>& st, const TileOfs<DH, KB>& t
                                        const bf16* Vs, int u, float sc, int lim_rel) {
   using C = Cfg<DH>;
   floatx16 x = zero16(), y = zero16();
-  {
-    bf16x8 k0[C::KS], k1[C::KS];
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) {
-      k0[c] = to.row(Ks, u, c);
-      k1[c] = to.row(Vs, u, c);
+  for (int c0 = 0; c0 < C::KS; c0 += C::RS) {
+    bf16x8 k0[C::RS], k1[C::RS];
+#pragma unroll
+    for (int c = 0; c < C::RS; ++c) {
+      k0[c] = to.row(Ks, u, c0 + c);
+      k1[c] = to.row(Vs, u, c0 + c);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int c = 0; c < C::KS; ++c) {
-      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.qf[c], x, 0, 0, 0);
-      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.of[c], y, 0, 0, 0);
+    for (int c = 0; c < C::RS; ++c) {
+      x = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0[c], st.qf[c0 + c], x, 0, 0, 0);
+      y = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1[c], st.of[c0 + c], y, 0, 0, 0);
     }
   }
   bf16x8 kt[2][C::OT];
@@ -741,7 +756,7 @@ bool rows_fit(long ld) { return 128 * ld * 2 < (1L << 30); }
 }  // namespace
 
 bool attn_small_fwd_eligible(const AttnArgs& a) {
-  return (a.dh == 64 || a.dh == 80) && a.scale > 0.f && ok16(a.q, a.ldq) && ok16(a.k, a.ldk) && ok16(a.v, a.ldv) &&
+  return (a.dh == 64 || a.dh == 80 || a.dh == 128) && a.scale > 0.f && ok16(a.q, a.ldq) && ok16(a.k, a.ldk) && ok16(a.v, a.ldv) &&
          ok8(a.o, a.ldo) && rows_fit(a.ldq) && rows_fit(a.ldk) && rows_fit(a.ldv);
 }
 
@@ -765,17 +780,20 @@ bool attn_small_bwd_eligible(const AttnBwdArgs& a) {
 
 hipError_t launch_attn_small_fwd(const AttnArgs& a, hipStream_t s) {
   if (a.dh == 64) SMALL_LAUNCH(attn_small_fwd_kernel, 64, a, a, true);
-  else SMALL_LAUNCH(attn_small_fwd_kernel, 80, a, a, true);
+  else if (a.dh == 80) SMALL_LAUNCH(attn_small_fwd_kernel, 80, a, a, true);
+  else SMALL_LAUNCH(attn_small_fwd_kernel, 128, a, a, true);
   return hipGetLastError();
 }
 
 // dQ (which also writes delta), then dK / dV.
 hipError_t launch_attn_small_bwd(const AttnBwdArgs& a, hipStream_t s) {
   if (a.f.dh == 64) SMALL_LAUNCH(attn_small_dq_kernel, 64, a, a.f, false);
-  else SMALL_LAUNCH(attn_small_dq_kernel, 80, a, a.f, false);
+  else if (a.f.dh == 80) SMALL_LAUNCH(attn_small_dq_kernel, 80, a, a.f, false);
+  else SMALL_LAUNCH(attn_small_dq_kernel, 128, a, a.f, false);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (a.f.dh == 64) SMALL_LAUNCH(attn_small_dkdv_kernel, 64, a, a.f, false);
-  else SMALL_LAUNCH(attn_small_dkdv_kernel, 80, a, a.f, false);
+  else if (a.f.dh == 80) SMALL_LAUNCH(attn_small_dkdv_kernel, 80, a, a.f, false);
+  else SMALL_LAUNCH(attn_small_dkdv_kernel, 128, a, a.f, false);
   return hipGetLastError();
 }

@@ -160,6 +160,36 @@ def test_attention_small_heads_grid(B, H, S, dh, causal):
     test_attention_fwd_bwd(B, H, S, dh, causal)
 
 
+# 128-wide heads: edges of the 64-key blocks and 32-row wave tiles, two to four waves per workgroup,
+# grouped heads; with o and dq 4-byte aligned (rows of d + 2) the general kernels run.
+@pytest.mark.parametrize("B,H,S,causal", [(1, 1, 1, True), (1, 2, 64, False), (2, 1, 65, True), (66, 1, 257, False),
+                                          (13, 15, 33, True), (25, 4, 255, True)])
+@pytest.mark.parametrize("pad", [0, 2])
+def test_attention_128_wide(B, H, S, causal, pad):
+    flush(f"attention 128 B={B} H={H} S={S} causal={causal} pad={pad}")
+    rng = np.random.default_rng(S + H)
+    dh, d = 128, 128 * H
+    buf, q, k, v = _qkv(rng, B, H, S, dh)
+    qkv = to_dev_bf16(buf)
+    o = torch.empty(B * S, d + pad, device="cuda", dtype=torch.bfloat16)
+    lse = torch.empty(B * H * S, device="cuda")
+    dq, dkv = torch.empty_like(o), torch.empty(2, B * S, d, device="cuda", dtype=torch.bfloat16)
+    do = bf16_round(rng.normal(size=(B * S, d)))
+    kw = dict(ldq=3 * d, ldk=3 * d, ldv=3 * d, ldo=d + pad)
+    K = ops()
+    K.attention_fwd(qkv, qkv[:, d:], qkv[:, 2 * d:], o, lse, B, H, S, dh, causal, dh ** -0.5, **kw)
+    K.attention_bwd(qkv, qkv[:, d:], qkv[:, 2 * d:], o, lse, to_dev_bf16(do), dq, dkv[0], dkv[1], B, H, S, dh, causal,
+                    dh ** -0.5, lddo=d, lddq=d + pad, lddk=d, lddv=d, **kw)
+    torch.cuda.synchronize()
+    ro, rlse, probs = O.attention(q, k, v, causal)
+    assert rel(host(o)[:, :d], _merge(ro)) < 1e-2
+    assert np.max(np.abs(host(lse).reshape(B, H, S) - rlse)) < 1e-4 * max(1.0, np.abs(rlse).max())
+    ref = O.attention_bwd(do.reshape(B, S, H, dh).transpose(0, 2, 1, 3), q, k, v, probs)
+    floor = 1e-3 * np.linalg.norm(do) * np.linalg.norm(buf[:, d:2 * d]) / math.sqrt(B * S)  # as above: one visible key
+    for got, r in zip((host(dq)[:, :d], *host(dkv)), ref):
+        assert np.linalg.norm(got - _merge(r)) <= 2e-2 * max(np.linalg.norm(r), floor)
+
+
 # Attention at the full per-layer shapes the step launches (GPT-J, GPT-2-small,
 # ViT-H/14, a grid member at batch 16), checked on sampled heads (the first
 # and the last (batch, head) plus one in between) against the oracle.
