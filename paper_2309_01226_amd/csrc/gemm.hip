@@ -885,7 +885,7 @@ GemmPlan gemm_plan(const GemmArgs& a, int alay, int blay, int epi) {
     } else {
       S256 = 1;
     }
-  } else if (may_split && !kl && !a.no_tail_split && a.K >= 1024 && tile_vec(a, alay, blay)) {
+  } else if (may_split && !kl && a.K >= 1024 && tile_vec(a, alay, blay)) {
     const long fit = a.splitk_ws_elems / std::max(1L, (long)a.M * a.N);
     const int smax = (int)std::min<long>(std::min<long>(a.splitk_max > 0 ? a.splitk_max : 16, a.K / 512), fit);
     slices(128, smax);

@@ -86,7 +86,7 @@ struct GemmArgs {
   // to fill the chip as split-K plus a reduction (gemm_splitk below).
   float* splitk_ws;
   long splitk_ws_elems;
-  // Most K slices the split-K plan may use (0: 16).  Products with very few
+  // Most K slices the split-K plan may use (0: 16; 1: none).  Products with very few
   // output tiles and very long K (the convolution weight gradients, K =
   // pixels) fill the chip only with more.
   int splitk_max;
@@ -95,8 +95,9 @@ struct GemmArgs {
   // + n] (cdiv(M, R) rows; launch_colsum_partials then adds them in order).
   float* colsum_part;
   // Keeps launch_gemm from splitting the rows of a mostly empty last round
-  // (gemm_tail_split), or any product with an M/N-contiguous operand: a weight gradient whose AdamW step may instead be
-  // fused into this kernel's epilogue must sum in the same order either way.
+  // (gemm_tail_split): a weight gradient whose AdamW step may instead be fused into
+  // this kernel's epilogue must sum in the same order either way (and with
+  // splitk_max 1, so that nothing else splits it).
   int no_tail_split;
   ConvTaps cv;  // launch_gemm_conv only
 };

@@ -257,6 +257,7 @@ static sat_status wgrad_run(sat_model* M, hipStream_t st, int lay, const bf16* y
     // the same sums as the fused epilogue's (nothing split), so that the separate
     // AdamW pass gives the fused step's parameters
     w.no_tail_split = 1;
+    w.splitk_max = 1;
   }
   if (lay == LAY_K) w.no_tail_split = 1;
   return gemm(M, w, lay, lay, EPI_F32, tk, st);
