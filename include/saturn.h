@@ -192,14 +192,14 @@ sat_status sat_model_stats(const sat_model* m, int64_t* n_params, int64_t* n_tra
  *   (with the AdamW steps fused into them) run on a second stream that the
  *   library creates on the first such backward (default priority; destroyed
  *   with the model), beside the input-gradient chain of the
- *   blocks below; they read token-contiguous copies of their operands in two
+ *   blocks below; consecutive blocks keep their gradients in two
  *   alternating sets, and the step joins that stream back into the model's
  *   stream before the backward ends, so a caller that synchronizes the
  *   model's stream sees the whole step.  Results are bitwise those with 0
  *   (the same kernels on the same operands).  Applies to models with a block
- *   weight whose AdamW step can be fused (SAT_OPT_FUSED_ADAMW: wide models)
- *   and batch * seq_len % 8 == 0; the others' products read the row-major
- *   tensors on the model's stream (otherwise ignored).
+ *   weight whose AdamW step can be fused (SAT_OPT_FUSED_ADAMW: wide models,
+ *   batch * seq_len % 8 == 0) and activations under 2 GiB each; the others' products run on the
+ *   model's stream (otherwise ignored).
  * value is 0 or 1; the setting applies from the next train step.
  * Errors: SAT_EINVAL (null model, unknown option or value), SAT_ESTATE. */
 typedef enum {

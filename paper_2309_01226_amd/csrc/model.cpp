@@ -371,19 +371,18 @@ size_t carve(sat_model* M, char* base) {
   }
   // backward workspace
   M->dh = c.take<float>(T * d);
-  M->dh_bf = c.take<bf16>(T * d);
   M->dA = c.take<float>(T * d);
-  M->dqkv = c.take<bf16>(T * D.qkv_ld);
-  M->du = gptj ? nullptr : c.take<bf16>(T * m);
   M->dout = c.take<bf16>(T * d);
   bool fused_block = false, fused_head = false;
   for (const auto& p : M->params) {
     if (p.fused_opt && p.group >= 0) (p.group == D.L ? fused_head : fused_block) = true;
   }
-  M->trans_blocks = T % 8 == 0 && fused_block;
-  // the head's product on its row-major operands must stay below 2^31 bytes of
-  // each (buffer offsets)
-  M->trans_head = R % 8 == 0 && fused_head && (R + 256L) * std::max(D.Vp, (int)d) * 2 >= (1L << 31);
+  // a product on its row-major operands must stay below 2^31 bytes of each (buffer offsets)
+  auto too_long = [](long rows, long cols) { return (rows + 256L) * cols * 2 >= (1L << 31); };
+  const bool long_block = too_long(T, std::max<long>(std::max<long>(d, D.qkv_ld), m));
+  M->two_sets = fused_block && !long_block;
+  M->trans_blocks = T % 8 == 0 && fused_block && long_block;
+  M->trans_head = R % 8 == 0 && fused_head && too_long(R, std::max<long>(D.Vp, d));
   {
     long na = 0, nb = 0;
     if (M->trans_blocks) {
@@ -397,22 +396,17 @@ size_t carve(sat_model* M, char* base) {
     M->tA = na > 0 ? c.take<bf16>(na) : nullptr;
     M->tB = nb > 0 ? c.take<bf16>(nb) : nullptr;
   }
-  // operands of the blocks' weight-gradient products on the side stream (two
-  // sets), and that stream's split-K workspace
+  // the blocks' gradients, and the side stream's split-K workspace
   for (int i = 0; i < 2; ++i) {
     WgradSet& W = M->wset[i];
-    memset(&W, 0, sizeof W);
-    if (!M->trans_blocks) continue;
-    W.dy1 = c.take<bf16>(T * d);
-    W.g = c.take<bf16>(T * m);
-    W.o = c.take<bf16>(T * d);
-    W.a = c.take<bf16>(T * d);
-    W.qkv = c.take<bf16>(T * D.qkv_ld);
-    if (!gptj) {
-      W.dy2 = c.take<bf16>(T * d);
-      W.c = c.take<bf16>(T * d);
-      W.du = c.take<bf16>(T * m);
+    if (i == 1 && !M->two_sets) {
+      W = M->wset[0];
+      break;
     }
+    W.dy1 = c.take<bf16>(T * d);
+    W.dy2 = gptj ? nullptr : M->two_sets ? c.take<bf16>(T * d) : W.dy1;  // on one stream dy1 is read before
+    W.du = gptj ? nullptr : c.take<bf16>(T * m);
+    W.qkv = c.take<bf16>(T * D.qkv_ld);
   }
   M->splitk_ws2 = M->splitk_ws_elems > 0 ? c.take<float>((size_t)M->splitk_ws_elems) : nullptr;
   M->delta = c.take<float>((size_t)D.B * D.H * D.S);

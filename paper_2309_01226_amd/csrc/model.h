@@ -80,15 +80,13 @@ struct TimingRec {
   double flops;
 };
 
-// Token-contiguous copies of the operands of one block's weight-gradient
-// products, read by those products on the weight-gradient stream (two sets,
-// used by alternate blocks).  dy1: dY of fc2 (and of the out-projection in
-// the parallel GPT-J block); dy2: dY of the out-projection in the sequential
-// block (the residual gradient after the second LayerNorm's backward);
-// g, o, a, c: inputs of fc2, out-projection, QKV, fc1; du: dY of fc1; qkv: dY
-// of the QKV (GPT-J: QKV + fc1) product.
+// bf16 gradients of one block, which its input- and weight-gradient products read.  dy1:
+// dY of fc2 (and of the out-projection in the parallel GPT-J block); dy2: dY of
+// the out-projection in the sequential block (the residual gradient after the
+// second LayerNorm's backward); du: dY of fc1; qkv: dY of the QKV (GPT-J:
+// QKV + fc1) product.
 struct WgradSet {
-  bf16 *dy1, *dy2, *g, *o, *a, *c, *du, *qkv;
+  bf16 *dy1, *dy2, *du, *qkv;
 };
 
 struct sat_model {
@@ -104,7 +102,7 @@ struct sat_model {
   hipEvent_t ev_join;     // side -> model stream: every product done
   bool side_pending[2];
   bool opt_overlap;
-  WgradSet wset[2];
+  WgradSet wset[2];  // block l's is wset[l % 2]; one set twice without the weight-gradient stream
   float* splitk_ws2;      // split-K workspace of the side stream
   int device;
   char* arena;
@@ -161,24 +159,25 @@ struct sat_model {
   bf16* dzpatch;
   // backward workspace
   float* dh;
-  bf16* dh_bf;
   float* dA;
-  bf16* dqkv;
-  bf16* du;
   bf16* dout;
-  // Token-contiguous (transposed) copies of the operands of the weight-gradient
-  // products dW = dY^T X: tA holds dY^T, tB holds X^T.  They serve models with a
-  // weight whose AdamW step is fused into its product (fused_opt: at least 256
-  // tiles of 256 x 256), when the token count is a multiple of 8.  The other
-  // models' products read the row-major tensors through the tile kernels'
-  // transposing LDS reads, on the model's stream: without the copies, two
-  // streams gain nothing (GPT-2-small: 14.65 ms per step with copies and the second
-  // stream, 13.98 without either; 8 ViT-H blocks 25.7 and 24.6 ms; the tiny
-  // decoder 0.43 and 0.24 ms).
+  // Models with a weight whose AdamW step is fused into its weight-gradient product
+  // (fused_opt: at least 256 tiles of 256 x 256) run the blocks' weight-gradient
+  // products on the second stream, with two operand sets, so that one block's
+  // products run beside the next one's chain.  All products read row-major tensors:
+  // through the kernels' transposing LDS reads they cost at most 6 % more than
+  // token-contiguous copies would let them, and the copies cost more than that (28 GPT-J
+  // blocks on two streams: with copies 160.1 ms per step, without 158.5; recomputing
+  // activations 187.1 and 183.6; one block 12.29 and 12.25).  Narrower models use one
+  // stream: 8 ViT-H blocks, copies and two streams 25.7 ms, neither 24.6.
+  bool two_sets;
+  // Token-contiguous copies dY^T and X^T for the weight-gradient products whose
+  // row-major operands exceed 2^31 bytes (32-bit buffer offsets), on the model's
+  // stream, when the token count is a multiple of 8.
   bf16* tA;
   bf16* tB;
-  bool trans_blocks;  // tA / tB (and the two operand sets) serve the blocks
-  bool trans_head;    // ... and tA / tB the head
+  bool trans_blocks;  // tA / tB serve the blocks
+  bool trans_head;    // ... the head
   // split-K workspace of the fp32-output products with too few tiles
   float* splitk_ws;
   long splitk_ws_elems;

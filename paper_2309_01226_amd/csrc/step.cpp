@@ -230,9 +230,9 @@ sat_status sat_run_forward(sat_model* M, const void* inputs, const int32_t* labe
 // pidx: the weight's parameter index.  When its AdamW step is fused, the
 // product's epilogue applies the step to the weight (and writes the gradient
 // only if the model keeps gradients).
-// The product on operands of layout `lay` (LAY_K: token-contiguous copies [Mr, T] and
-// [N, T]; LAY_MN: the row-major tensors), on stream st (the model's, or the
-// weight-gradient stream).
+// wgrad_run: the product on operands of layout `lay` (LAY_K: token-contiguous copies
+// [Mr, T] and [N, T]; LAY_MN: the row-major tensors), on stream st (the model's, or
+// the weight-gradient stream).
 static sat_status wgrad_run(sat_model* M, hipStream_t st, int lay, const bf16* y, long ldy, const bf16* x,
                             long ldx, int Mr, int N, int T, int pidx, int tk = TK_ALL_GEMM) {
   const ParamDesc& P = M->params[pidx];
@@ -267,15 +267,15 @@ static sat_status wgrad_t(sat_model* M, hipStream_t st, const bf16* yT, const bf
   return wgrad_run(M, st, LAY_K, yT, T, xT, T, Mr, N, T, pidx, tk);
 }
 
-static sat_status wgrad(sat_model* M, bool trans, bool y_ready, const bf16* Y, long ldy,
+static sat_status wgrad(sat_model* M, hipStream_t st, bool trans, bool y_ready, const bf16* Y, long ldy,
                         int ycols, const bf16* X, long ldx, int Mr, int N, int T, int pidx,
                         int tk = TK_ALL_GEMM) {
   if (trans) {
-    if (!y_ready) SAT_HIP(launch_transpose_bf16(Y, ldy, M->tA, T, T, ycols, M->stream));
-    SAT_HIP(launch_transpose_bf16(X, ldx, M->tB, T, T, N, M->stream));
-    return wgrad_t(M, M->stream, M->tA, M->tB, Mr, N, T, pidx, tk);
+    if (!y_ready) SAT_HIP(launch_transpose_bf16(Y, ldy, M->tA, T, T, ycols, st));
+    SAT_HIP(launch_transpose_bf16(X, ldx, M->tB, T, T, N, st));
+    return wgrad_t(M, st, M->tA, M->tB, Mr, N, T, pidx, tk);
   }
-  return wgrad_run(M, M->stream, LAY_MN, Y, ldy, X, ldx, Mr, N, T, pidx, tk);
+  return wgrad_run(M, st, LAY_MN, Y, ldy, X, ldx, Mr, N, T, pidx, tk);
 }
 
 // The fc1 bias gradient is the column sum of the fc2 input-gradient product's
@@ -294,7 +294,7 @@ static int with_colsums(sat_model* M, GemmArgs& a) {
 }
 
 // Weight-gradient stream.  fork: what the model's stream has enqueued so far
-// (the operand copies) precedes what the side stream enqueues next.  reuse:
+// (the operands) precedes what the side stream enqueues next.  reuse:
 // before the model's stream rewrites operand set i, the products that read it
 // are done.  done: marks the end of the products of set i.  join: the model's
 // stream waits for everything on the side stream.
@@ -321,11 +321,11 @@ static sat_status side_join(sat_model* M) {
 }
 
 // LayerNorm backward into the residual gradient dh, which it also rounds into
-// dh_bf, the bf16 copy the next products read.  dbias (may be null): the bias
+// out_bf, the bf16 copy the next products read (null: none does).  dbias (may be null): the bias
 // gradient of the residual product below, the column sums of the updated dh,
 // reduced in the same pass.
 static sat_status ln_bwd(sat_model* M, const float* dy, const float* x, long row_stride,
-                         int gidx, const float* mean, const float* rstd, int rows,
+                         int gidx, const float* mean, const float* rstd, int rows, bf16* out_bf,
                          float* dbias = nullptr) {
   const int d = M->D.d;
   const int np_ = ln_bwd_parts(rows, d);
@@ -335,7 +335,7 @@ static sat_status ln_bwd(sat_model* M, const float* dy, const float* x, long row
   {
     Timed tm(M, TK_LN_BWD, ln_bwd_bytes(rows, d, true));
     SAT_HIP(launch_layernorm_bwd(dy, d, x, d, row_stride, master(M, gidx), mean, rstd, M->dh, d, pg,
-                                 pbb, rows, d, np_, M->stream, M->dh_bf, d, po));
+                                 pbb, rows, d, np_, M->stream, out_bf, d, po));
   }
   SAT_HIP(launch_ln_bwd_colsums(pg, np_, d, grad(M, gidx), grad(M, gidx + 1), M->stream, dbias));
   return SAT_OK;
@@ -375,7 +375,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
     // zero tail, so the extra products vanish and the 16-byte path applies.
     GemmArgs g = gargs(M->dz, D.Vp, shadow_t(M, hb + 2), D.Vp, R, d, D.Vp, M->dA, d);
     TRY(gemm(M, g, LAY_K, LAY_K, EPI_F32));
-    TRY(wgrad(M, M->trans_head, false, M->dz, D.Vp, D.Vp, M->f, d, D.V, d, R, hb + 2));
+    TRY(wgrad(M, s, M->trans_head, false, M->dz, D.Vp, D.Vp, M->f, d, D.V, d, R, hb + 2));
     if (D.arch != SAT_GPT2)
       SAT_HIP(launch_colsum_bf16(M->dz, D.Vp, R, D.V, M->part, R < 256 ? R : 256,
                                  grad(M, hb + 3), s));
@@ -388,29 +388,38 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
     float* pg = M->part;
     float* pbb = M->part + (size_t)np_ * d;
     float* dbias_top = fc2_bias_grad(M, D.L - 1);
+    bf16* dy_top = M->wset[(D.L - 1) & 1].dy1;
     float* po = dbias_top ? M->part + (size_t)2 * np_ * d : nullptr;
     {
       Timed tm(M, TK_LN_BWD, ln_bwd_bytes(R, d, rstride == 1));
       SAT_HIP(launch_layernorm_bwd(M->dA, d, M->h_in[D.L], d, rstride, master(M, hb + 0),
                                    M->meanf, M->rstdf, M->dh, d, pg, pbb, R, d, np_, s,
-                                   rstride == 1 ? M->dh_bf : nullptr, d, po));
+                                   rstride == 1 ? dy_top : nullptr, d, po));
     }
     if (rstride != 1)  // ViT: only the CLS rows of dh were written
-      SAT_HIP(launch_f32_to_bf16(M->dh, d, M->dh_bf, d, T, d, s));
+      SAT_HIP(launch_f32_to_bf16(M->dh, d, dy_top, d, T, d, s));
     SAT_HIP(launch_ln_bwd_colsums(pg, np_, d, grad(M, hb + 0), grad(M, hb + 1), s, dbias_top));
   }
 
   // ---- blocks L-1 .. k
-  // With the weight-gradient stream, block l's operand copies go to set l % 2
-  // on the model's stream and its weight-gradient products run on the side
-  // stream; every input-gradient product of a weight is enqueued before the
-  // fork that releases the weight's (AdamW-fused) weight-gradient product.
-  const bool ov = M->opt_overlap && M->trans_blocks && D.k < D.L;
+  // Block l keeps its gradients (dy1, dy2, du, qkv) in set l % 2.  With the
+  // weight-gradient stream, its weight-gradient products read them, and the saved
+  // activations, on the side stream, where they lie; every input-gradient product
+  // of a weight is enqueued before the fork that releases the weight's
+  // (AdamW-fused) weight-gradient product.  Block l's last LayerNorm writes the first
+  // tensor of the other set: before it, block l + 1's products are waited for,
+  // under checkpointing before the recomputation that rewrites the activations they read.
+  const bool ov = M->opt_overlap && M->two_sets && D.k < D.L;
   if (ov) TRY(sat_side_ensure(M));
   for (int l = D.L - 1; l >= D.k; --l) {
-    if (ov) TRY(side_reuse(M, l & 1));
-    WgradSet& W = M->wset[l & 1];
-    if (D.ckpt) TRY(block_forward(M, l, true));
+    const WgradSet& W = M->wset[l & 1];
+    bf16* next_dy1 = l > D.k ? M->wset[(l - 1) & 1].dy1 : nullptr;
+    if (D.ckpt) {
+      if (ov) TRY(side_reuse(M, (l + 1) & 1));
+      TRY(block_forward(M, l, true));
+    }
+    const bool tr = M->trans_blocks;
+    hipStream_t ws = ov ? M->side : s;  // of the weight-gradient products
     const LayerActs& A = sat_layer_acts(M, l);
     const int pb = block_base(M, l);
     AttnBwdArgs ab;
@@ -430,20 +439,19 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
     ab.dout = M->dout;
     ab.lddo = d;
     ab.delta = M->delta;
-    ab.dq = M->dqkv;
-    ab.dk = M->dqkv + d;
-    ab.dv = M->dqkv + 2 * d;
+    ab.dq = W.qkv;
+    ab.dk = W.qkv + d;
+    ab.dv = W.qkv + 2 * d;
     ab.lddq = ab.lddk = ab.lddv = D.qkv_ld;
     const double attn_bwd_flops =
         8.0 * D.B * D.H * (double)D.S * D.S * D.dh * (ab.f.causal ? 0.5 : 1.0);
 
-    // dh_bf: the bf16 copy of dh, written by the LayerNorm backward that last
+    // dy1: the bf16 copy of dh, written by the LayerNorm backward that last
     // updated dh (the head's, or the block above's)
     if (gptj) {
-      const bool tr = M->trans_blocks;
       if (!bias_in_ln_bwd(M))
         SAT_HIP(launch_colsum_f32(M->dh, d, T, d, M->part, npT, grad(M, pb + J_FC2B), s));
-      GemmArgs du = gargs(M->dh_bf, d, shadow_t(M, pb + J_FC2W), d, T, m, d, M->dqkv + 3 * d, D.qkv_ld);
+      GemmArgs du = gargs(W.dy1, d, shadow_t(M, pb + J_FC2W), d, T, m, d, W.qkv + 3 * d, D.qkv_ld);
       du.aux = A.qkv + 3 * d;
       du.ldaux = D.qkv_ld;
       du.gelu_erf = 0;
@@ -451,47 +459,33 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       TRY(gemm(M, du, LAY_K, LAY_K, EPI_DGELU_BF16));
       if (fc1b_parts)
         SAT_HIP(launch_colsum_partials(M->part, fc1b_parts, m, grad(M, pb + J_FC1B), s));
-      GemmArgs go = gargs(M->dh_bf, d, shadow_t(M, pb + J_PROJW), d, T, d, d, M->dout, d);
+      GemmArgs go = gargs(W.dy1, d, shadow_t(M, pb + J_PROJW), d, T, d, d, M->dout, d);
       TRY(gemm(M, go, LAY_K, LAY_K, EPI_BF16));
-      if (ov) {
-        SAT_HIP(launch_transpose_bf16(M->dh_bf, d, W.dy1, T, T, d, s));
-        SAT_HIP(launch_transpose_bf16(A.g, m, W.g, T, T, m, s));
-        SAT_HIP(launch_transpose_bf16(A.o, d, W.o, T, T, d, s));
-        TRY(side_fork(M));
-        TRY(wgrad_t(M, M->side, W.dy1, W.g, d, m, T, pb + J_FC2W));
-        TRY(wgrad_t(M, M->side, W.dy1, W.o, d, d, T, pb + J_PROJW));
-      } else {
-        TRY(wgrad(M, tr, false, M->dh_bf, d, d, A.g, m, d, m, T, pb + J_FC2W));
-        TRY(wgrad(M, tr, true, M->dh_bf, d, d, A.o, d, d, d, T, pb + J_PROJW));
-      }
+      if (ov) TRY(side_fork(M));
+      TRY(wgrad(M, ws, tr, false, W.dy1, d, d, A.g, m, d, m, T, pb + J_FC2W));
+      TRY(wgrad(M, ws, tr, true, W.dy1, d, d, A.o, d, d, d, T, pb + J_PROJW));
       {
         Timed tm(M, TK_ATTN_BWD, attn_bwd_flops);
         SAT_HIP(launch_attention_bwd(ab, s));
       }
-      SAT_HIP(launch_rotary(M->dqkv, D.qkv_ld, D.B, D.S, D.H, D.dh, D.rd, 1, s, M->rope_cs));
-      GemmArgs ga = gargs(M->dqkv, D.qkv_ld, shadow_t(M, pb + J_QKVW), D.qkv_ld, T, d, D.qkv_ld,
+      SAT_HIP(launch_rotary(W.qkv, D.qkv_ld, D.B, D.S, D.H, D.dh, D.rd, 1, s, M->rope_cs));
+      GemmArgs ga = gargs(W.qkv, D.qkv_ld, shadow_t(M, pb + J_QKVW), D.qkv_ld, T, d, D.qkv_ld,
                           M->dA, d);
       TRY(gemm(M, ga, LAY_K, LAY_K, EPI_F32));
-      if (ov) {
-        SAT_HIP(launch_transpose_bf16(M->dqkv, D.qkv_ld, W.qkv, T, T, D.qkv_ld, s));
-        SAT_HIP(launch_transpose_bf16(A.a, d, W.a, T, T, d, s));
-        TRY(side_fork(M));
-        TRY(wgrad_t(M, M->side, W.qkv, W.a, D.qkv_ld, d, T, pb + J_QKVW, TK_QKV_WGRAD));
-        TRY(side_done(M, l & 1));
-      } else {
-        TRY(wgrad(M, tr, false, M->dqkv, D.qkv_ld, D.qkv_ld, A.a, d, D.qkv_ld, d, T, pb + J_QKVW,
-                  TK_QKV_WGRAD));
-      }
+      if (ov) TRY(side_fork(M));
+      TRY(wgrad(M, ws, tr, false, W.qkv, D.qkv_ld, D.qkv_ld, A.a, d, D.qkv_ld, d, T, pb + J_QKVW,
+                TK_QKV_WGRAD));
+      if (ov) TRY(side_done(M, l & 1));
       if (!fc1b_parts)
-        SAT_HIP(launch_colsum_bf16(M->dqkv + 3 * d, D.qkv_ld, T, m, M->part, npT,
+        SAT_HIP(launch_colsum_bf16(W.qkv + 3 * d, D.qkv_ld, T, m, M->part, npT,
                                    grad(M, pb + J_FC1B), s));
-      TRY(ln_bwd(M, M->dA, M->h_in[l], 1, pb + J_LN1G, A.mean1, A.rstd1, T,
+      if (ov && next_dy1) TRY(side_reuse(M, (l - 1) & 1));
+      TRY(ln_bwd(M, M->dA, M->h_in[l], 1, pb + J_LN1G, A.mean1, A.rstd1, T, next_dy1,
                  fc2_bias_grad(M, l - 1)));
     } else {
-      const bool tr = M->trans_blocks;
       if (!bias_in_ln_bwd(M))
         SAT_HIP(launch_colsum_f32(M->dh, d, T, d, M->part, npT, grad(M, pb + B_FC2B), s));
-      GemmArgs du = gargs(M->dh_bf, d, shadow_t(M, pb + B_FC2W), d, T, m, d, M->du, m);
+      GemmArgs du = gargs(W.dy1, d, shadow_t(M, pb + B_FC2W), d, T, m, d, W.du, m);
       du.aux = A.u;
       du.ldaux = m;
       du.gelu_erf = gelu_erf;
@@ -499,54 +493,33 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       TRY(gemm(M, du, LAY_K, LAY_K, EPI_DGELU_BF16));
       if (fc1b_parts)
         SAT_HIP(launch_colsum_partials(M->part, fc1b_parts, m, grad(M, pb + B_FC1B), s));
-      GemmArgs gc = gargs(M->du, m, shadow_t(M, pb + B_FC1W), m, T, d, m, M->dA, d);
+      GemmArgs gc = gargs(W.du, m, shadow_t(M, pb + B_FC1W), m, T, d, m, M->dA, d);
       TRY(gemm(M, gc, LAY_K, LAY_K, EPI_F32));
-      if (ov) {
-        SAT_HIP(launch_transpose_bf16(M->dh_bf, d, W.dy1, T, T, d, s));
-        SAT_HIP(launch_transpose_bf16(A.g, m, W.g, T, T, m, s));
-        SAT_HIP(launch_transpose_bf16(M->du, m, W.du, T, T, m, s));
-        SAT_HIP(launch_transpose_bf16(A.c, d, W.c, T, T, d, s));
-        TRY(side_fork(M));
-        TRY(wgrad_t(M, M->side, W.dy1, W.g, d, m, T, pb + B_FC2W));
-        TRY(wgrad_t(M, M->side, W.du, W.c, m, d, T, pb + B_FC1W));
-      } else {
-        TRY(wgrad(M, tr, false, M->dh_bf, d, d, A.g, m, d, m, T, pb + B_FC2W));
-        TRY(wgrad(M, tr, false, M->du, m, m, A.c, d, m, d, T, pb + B_FC1W));
-      }
+      if (ov) TRY(side_fork(M));
+      TRY(wgrad(M, ws, tr, false, W.dy1, d, d, A.g, m, d, m, T, pb + B_FC2W));
+      TRY(wgrad(M, ws, tr, false, W.du, m, m, A.c, d, m, d, T, pb + B_FC1W));
       if (!fc1b_parts)
-        SAT_HIP(launch_colsum_bf16(M->du, m, T, m, M->part, npT, grad(M, pb + B_FC1B), s));
-      TRY(ln_bwd(M, M->dA, A.h_mid, 1, pb + B_LN2G, A.mean2, A.rstd2, T,
+        SAT_HIP(launch_colsum_bf16(W.du, m, T, m, M->part, npT, grad(M, pb + B_FC1B), s));
+      TRY(ln_bwd(M, M->dA, A.h_mid, 1, pb + B_LN2G, A.mean2, A.rstd2, T, W.dy2,
                  bias_in_ln_bwd(M) ? grad(M, pb + B_PROJB) : nullptr));
       if (!bias_in_ln_bwd(M))
         SAT_HIP(launch_colsum_f32(M->dh, d, T, d, M->part, npT, grad(M, pb + B_PROJB), s));
-      GemmArgs go = gargs(M->dh_bf, d, shadow_t(M, pb + B_PROJW), d, T, d, d, M->dout, d);
+      GemmArgs go = gargs(W.dy2, d, shadow_t(M, pb + B_PROJW), d, T, d, d, M->dout, d);
       TRY(gemm(M, go, LAY_K, LAY_K, EPI_BF16));
-      if (ov) {
-        SAT_HIP(launch_transpose_bf16(M->dh_bf, d, W.dy2, T, T, d, s));
-        SAT_HIP(launch_transpose_bf16(A.o, d, W.o, T, T, d, s));
-        TRY(side_fork(M));
-        TRY(wgrad_t(M, M->side, W.dy2, W.o, d, d, T, pb + B_PROJW));
-      } else {
-        TRY(wgrad(M, tr, false, M->dh_bf, d, d, A.o, d, d, d, T, pb + B_PROJW));
-      }
+      if (ov) TRY(side_fork(M));
+      TRY(wgrad(M, ws, tr, false, W.dy2, d, d, A.o, d, d, d, T, pb + B_PROJW));
       {
         Timed tm(M, TK_ATTN_BWD, attn_bwd_flops);
         SAT_HIP(launch_attention_bwd(ab, s));
       }
-      GemmArgs ga = gargs(M->dqkv, 3 * d, shadow_t(M, pb + B_QKVW), 3 * d, T, d, 3 * d, M->dA, d);
+      GemmArgs ga = gargs(W.qkv, 3 * d, shadow_t(M, pb + B_QKVW), 3 * d, T, d, 3 * d, M->dA, d);
       TRY(gemm(M, ga, LAY_K, LAY_K, EPI_F32));
-      if (ov) {
-        SAT_HIP(launch_transpose_bf16(M->dqkv, 3 * d, W.qkv, T, T, 3 * d, s));
-        SAT_HIP(launch_transpose_bf16(A.a, d, W.a, T, T, d, s));
-        TRY(side_fork(M));
-        TRY(wgrad_t(M, M->side, W.qkv, W.a, 3 * d, d, T, pb + B_QKVW, TK_QKV_WGRAD));
-        TRY(side_done(M, l & 1));
-      } else {
-        TRY(wgrad(M, tr, false, M->dqkv, 3 * d, 3 * d, A.a, d, 3 * d, d, T, pb + B_QKVW,
-                  TK_QKV_WGRAD));
-      }
-      SAT_HIP(launch_colsum_bf16(M->dqkv, 3 * d, T, 3 * d, M->part, npT, grad(M, pb + B_QKVB), s));
-      TRY(ln_bwd(M, M->dA, M->h_in[l], 1, pb + B_LN1G, A.mean1, A.rstd1, T,
+      if (ov) TRY(side_fork(M));
+      TRY(wgrad(M, ws, tr, false, W.qkv, 3 * d, 3 * d, A.a, d, 3 * d, d, T, pb + B_QKVW, TK_QKV_WGRAD));
+      if (ov) TRY(side_done(M, l & 1));
+      SAT_HIP(launch_colsum_bf16(W.qkv, 3 * d, T, 3 * d, M->part, npT, grad(M, pb + B_QKVB), s));
+      if (ov && next_dy1) TRY(side_reuse(M, (l - 1) & 1));
+      TRY(ln_bwd(M, M->dA, M->h_in[l], 1, pb + B_LN1G, A.mean1, A.rstd1, T, next_dy1,
                  fc2_bias_grad(M, l - 1)));
     }
   }

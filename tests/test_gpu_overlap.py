@@ -37,6 +37,11 @@ CASES = {
                       seq_len=64, batch=2, lr=1e-3, frozen_layers=1),
     "gptj_wide_ckpt": dict(arch="gptj", n_layers=2, d_model=2048, n_heads=8, d_mlp=8192, vocab=64,
                            seq_len=64, batch=2, rotary_dim=16, lr=1e-3, checkpoint=1),
+    # each of the two gradient sets used twice
+    "gpt2_wide_deep": dict(arch="gpt2", n_layers=4, d_model=2048, n_heads=16, d_mlp=8192, vocab=64,
+                           seq_len=72, batch=3, lr=1e-3),
+    "gptj_wide_deep": dict(arch="gptj", n_layers=4, d_model=2048, n_heads=8, d_mlp=8192, vocab=64,
+                           seq_len=512, batch=2, rotary_dim=16, lr=1e-3),
     # every block weight's AdamW step fused into its weight-gradient product
     "gptj_fused": dict(arch="gptj", n_layers=2, d_model=2048, n_heads=8, d_mlp=8192, vocab=8200,
                        seq_len=2048, batch=2, rotary_dim=64, lr=1e-3),
