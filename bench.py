@@ -663,7 +663,7 @@ def main():
     if w_n and resnet:
         achieved = w_fl / w_n / (w_ms / w_n * 1e-3) / 1e12
         out["roofline"] = {
-            "kernel": "3x3 convolution forward products (im2col operand x weight, fp32 out), "
+            "kernel": "3x3 convolution forward products (operand gathered in the product, fp32 out), "
                       "mean over the 50 per step",
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS, "traffic": None,
@@ -675,10 +675,10 @@ def main():
         opt_bytes = 28.0 * ncols * kw["d_model"] if fused else 0.0
         serial_us = (w_fl / w_n / (PEAK_BF16_TFLOPS * 1e12) + opt_bytes / (PEAK_HBM_GBS * 1e9)) * 1e6
         out["roofline"] = {
-            "kernel": (f"gemm256_kernel<4, 0> (AdamW epilogue): weight gradient of the fused QKV + fc1 weight "
+            "kernel": (f"gemm256_kernel<1, 1, 4, 0> (AdamW epilogue): weight gradient of the fused QKV + fc1 weight "
                        f"({ncols} x {kw['d_model']} x {m.rows()} tokens) with that weight's AdamW step"
                        if fused else
-                       f"gemm256_kernel<0, 0>: weight gradient of the fused QKV + fc1 weight "
+                       f"gemm256_kernel<1, 1, 0, 0>: weight gradient of the fused QKV + fc1 weight "
                        f"({ncols} x {kw['d_model']} x {m.rows()} tokens)"),
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS,
@@ -703,7 +703,7 @@ def main():
     if q_n:
         achieved = q_fl / q_n / (q_ms / q_n * 1e-3) / 1e12
         out["roofline_qkv_fwd"] = {
-            "kernel": "gemm256_kernel<2, 0> (bf16 epilogue, GELU on the fc1 columns): fused QKV + fc1 forward "
+            "kernel": "gemm256_kernel<0, 0, 2, 0> (bf16 epilogue, GELU on the fc1 columns): fused QKV + fc1 forward "
                       f"({m.rows()} x {ncols} x {kw['d_model']})",
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS,
