@@ -107,11 +107,14 @@ __device__ __forceinline__ float halves_max(float x) {
 __device__ __forceinline__ float halves_sum(float x) { return x + __shfl_xor(x, 32, 64); }
 
 // Maximum of three.  fmaxf first quiets each operand (v_max x, x), since the
-// compiler cannot know that an MFMA result is no signaling NaN; this does not.
+// compiler cannot know that an MFMA result is no signaling NaN; the maximum that hands
+// NaN on does not, and becomes one v_maximum3.  (As inline asm the same
+// instruction read its operands 2 wait states after the MFMA that writes them, which
+// needs 12: the compiler keeps them apart only for instructions that it knows.)
+// A NaN score leaves its query's maximum where it was; that query's sum, output and
+// log-sum-exp are NaN whatever the maximum.
 __device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
+  return __builtin_elementwise_maximum(__builtin_elementwise_maximum(a, b), c);
 }
 
 // Which head and which block of its rows a workgroup takes.  Workgroups are dealt

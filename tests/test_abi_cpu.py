@@ -149,3 +149,12 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
         L.lib()
     with pytest.raises(ImportError):
         L.call("sat_model_destroy", None)
+
+
+def test_no_inline_assembly():
+    """Kernels use compiler builtins only: the compiler keeps the wait states that an MFMA's
+    result and a load need before they are read, but does not look into inline assembly."""
+    csrc = os.path.join(ROOT, "paper_2309_01226_amd", "csrc")
+    for f in sorted(os.listdir(csrc)):
+        src = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(csrc, f)).read(), flags=re.S)
+        assert not re.search(r"\b(?:__)?asm(?:__)?\b", src), f

@@ -190,6 +190,40 @@ def test_attention_128_wide(B, H, S, causal, pad):
         assert np.linalg.norm(got - _merge(r)) <= 2e-2 * max(np.linalg.norm(r), floor)
 
 
+# Scores whose maximum rises from one 64-key block to the next, by less than the slack of 8 (base
+# 2) below which the running maximum stays, by just more, and by more than fp32 holds (2^128: a
+# maximum that missed the largest score overflows), or falls; the largest key of a block
+# sits at every one of the 64 positions in turn, over (block, head).  Whole blocks, and with the
+# causal mask the diagonal's.
+@pytest.mark.parametrize("dh", [64, 80, 128])
+@pytest.mark.parametrize("rise", [5.0, 9.0, 150.0, -150.0])
+@pytest.mark.parametrize("S,causal", [(576, False), (575, True)])
+def test_attention_rising_maximum(dh, rise, S, causal):
+    flush(f"attention rising maximum dh={dh} rise={rise} S={S} causal={causal}")
+    rng = np.random.default_rng(dh + S)
+    B, H, d = 1, 8, 8 * dh
+    scale = 1.0 / math.sqrt(dh)
+    x = 0.25 * rng.normal(size=(3, H, S, dh))
+    # queries and the blocks' largest keys along (1, ..., 1), every fifth query against it
+    x[0] += np.where(np.arange(S) % 5 == 4, -1.0, 1.0)[:, None]
+    for h in range(H):
+        for j in range((S + 63) // 64):
+            key = min(64 * j + (8 * j + h) % 64, S - 1)
+            x[1, h, key] += (j + 1) * rise * math.log(2.0) / (scale * dh)
+    x = bf16_round(x)
+    q, k, v = x[:, None]
+    qkv = to_dev_bf16(np.concatenate([_merge(t) for t in (q, k, v)], axis=1))
+    o = torch.empty(S, d, device="cuda", dtype=torch.bfloat16)
+    lse = torch.empty(H * S, device="cuda")
+    ops().attention_fwd(qkv, qkv[:, d:], qkv[:, 2 * d:], o, lse, B, H, S, dh, causal, scale,
+                        ldq=3 * d, ldk=3 * d, ldv=3 * d, ldo=d)
+    torch.cuda.synchronize()
+    ro, rlse, _ = O.attention(q, k, v, causal)
+    assert np.isfinite(host(o)).all() and np.isfinite(host(lse)).all()
+    assert rel(host(o), _merge(ro)) < 1e-2
+    assert np.max(np.abs(host(lse).reshape(B, H, S) - rlse)) < 1e-4 * max(1.0, np.abs(rlse).max())
+
+
 # Attention at the full per-layer shapes the step launches (GPT-J, GPT-2-small,
 # ViT-H/14, a grid member at batch 16), checked on sampled heads (the first
 # and the last (batch, head) plus one in between) against the oracle.
