@@ -318,15 +318,16 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& p, floatx16 (&acc)
   }
 }
 
-// Whether the epilogue's 4-column vectors are aligned in every array it touches.
-template <int EPI>
+// Whether the epilogue's 4-column vectors are aligned in every array it touches, and a
+// tile's rows of the residual / pre-activation stay within 32-bit buffer offsets.
+template <int BT, int EPI>
 __device__ __forceinline__ bool epilogue_vec(const GemmArgs& p) {
   auto al = [](const void* q, int b) { return (reinterpret_cast<uintptr_t>(q) & (b - 1)) == 0; };
   bool ok = p.ldo % 4 == 0 && al(p.out, (EPI == EPI_F32 || EPI == EPI_RESID_F32) ? 16 : 8);
-  if (EPI == EPI_RESID_F32) ok = ok && p.ldr % 4 == 0 && al(p.resid, 16);
+  if (EPI == EPI_RESID_F32) ok = ok && p.ldr % 4 == 0 && al(p.resid, 16) && p.ldr < (1L << 31) / (BT * 4);
   if (EPI == EPI_BF16 && p.out2 != nullptr)
     ok = ok && p.ldo2 % 4 == 0 && p.gelu_col0 % 4 == 0 && al(p.out2, 8);
-  if (EPI == EPI_DGELU_BF16) ok = ok && p.ldaux % 4 == 0 && al(p.aux, 8);
+  if (EPI == EPI_DGELU_BF16) ok = ok && p.ldaux % 4 == 0 && al(p.aux, 8) && p.ldaux < (1L << 31) / (BT * 2);
   return ok;
 }
 
@@ -407,7 +408,7 @@ __global__ __launch_bounds__(NT) void gemm_kernel_simple(GemmArgs p) {
   }
   __syncthreads();
 
-  gemm_epilogue<BT, EPI, GE>(p, acc, smem, m0, n0, wave, lane, epilogue_vec<EPI>(p));
+  gemm_epilogue<BT, EPI, GE>(p, acc, smem, m0, n0, wave, lane, epilogue_vec<BT, EPI>(p));
 }
 
 // ------------------------------------------------------------------------
@@ -714,7 +715,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_tile_kernel(GemmArgs p) {
   }
   wait_vm_lgkm0<0>();  // the zero-filling copies past the last tile
   __syncthreads();
-  gemm_epilogue<BT, EPI, GE>(p, acc, smem, m0, n0, wave, lane, epilogue_vec<EPI>(p));
+  gemm_epilogue<BT, EPI, GE>(p, acc, smem, m0, n0, wave, lane, epilogue_vec<BT, EPI>(p));
 }
 
 template <int BT, int ALAY, int BLAY, int EPI, int GE>

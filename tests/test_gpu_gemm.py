@@ -284,3 +284,29 @@ def test_gemm_splitk_mn_layouts(a_layout, b_layout):
     torch.cuda.synchronize()
     assert rel(host(out), R + O.gemm(A, B)) < 2e-6
     assert int(torch.isfinite(ws).sum().item()) >= 2 * M * N
+
+
+# A residual / pre-activation whose rows of one tile span 2 GiB (and 4 GiB) or more: the same
+# result as from a compact one, with 128 x 128 tiles and with 64 x 64.
+@pytest.mark.parametrize("M,N,K", [(128, 25600, 4096), (64, 64, 64)])
+@pytest.mark.parametrize("epi", [1, 3])
+@pytest.mark.parametrize("span", [1, 2])
+def test_gemm_epilogue_operand_spans_2gib(M, N, K, epi, span):
+    from paper_2309_01226_amd import ops
+    flush(f"gemm epilogue operand past 2 GiB M={M} N={N} K={K} epi={epi} span={span}")
+    g = torch.Generator("cuda").manual_seed(M + epi)
+    A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    B = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    dt = torch.float32 if epi == 1 else torch.bfloat16
+    X = torch.randn(M, N, generator=g, device="cuda").to(dt)
+    ld = (span * (1 << 31) // ((M - 1) * X.element_size()) + 67) // 4 * 4
+    wide = torch.empty(M * ld, device="cuda", dtype=dt).view(M, ld)
+    wide[:, :N] = X
+    res = []
+    for x, l in ((X, N), (wide, ld)):
+        out = torch.empty(M, N, device="cuda", dtype=dt)
+        kw = dict(resid=x, ldr=l) if epi == 1 else dict(aux=x, ldaux=l)
+        ops.gemm(A, B, M, N, K, out, lda=K, ldb=K, epilogue=epi, **kw)
+        res.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(res[0], res[1])
