@@ -757,10 +757,11 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 // piece would mix in values past K, so K must be a multiple of 8; along M / N a
 // partial piece only feeds output rows / columns that are never stored, so it
 // suffices that the rows are long enough (ld >= M or N rounded up to 8) to stay
-// in bounds.
+// in bounds.  A tile's rows (128, or 64 k-rows) must stay within 32-bit buffer offsets.
 bool tile_vec(const GemmArgs& a, int alay, int blay) {
   auto r8 = [](long x) { return (x + 7) / 8 * 8; };
-  return aligned16(a.A) && aligned16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0 &&
+  auto fits = [](long ld, int lay) { return ld < (1L << 31) / (lay == LAY_K ? 2 * 128 : 2 * BK); };
+  return aligned16(a.A) && aligned16(a.B) && a.lda % 8 == 0 && a.ldb % 8 == 0 && fits(a.lda, alay) && fits(a.ldb, blay) &&
          (alay == LAY_K ? a.K % 8 == 0 : a.lda >= r8(a.M)) &&
          (blay == LAY_K ? a.K % 8 == 0 : a.ldb >= r8(a.N));
 }

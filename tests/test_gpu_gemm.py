@@ -310,3 +310,27 @@ def test_gemm_epilogue_operand_spans_2gib(M, N, K, epi, span):
         res.append(out)
     torch.cuda.synchronize()
     assert torch.equal(res[0], res[1])
+
+
+# An operand whose rows (or k-rows) of one tile span 2 GiB or more.
+@pytest.mark.parametrize("M,N,K", [(128, 25600, 4096), (64, 64, 64)])
+@pytest.mark.parametrize("layout", [0, 1])
+def test_gemm_operand_spans_2gib(M, N, K, layout):
+    from paper_2309_01226_amd import ops
+    flush(f"gemm operand past 2 GiB M={M} N={N} K={K} layout={layout}")
+    if layout == 1:
+        K = 64
+    g = torch.Generator("cuda").manual_seed(M + layout)
+    A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
+    B = torch.randn(N, K, generator=g, device="cuda").bfloat16()
+    S = A if layout == 0 else A.t().contiguous()
+    ld = ((1 << 31) // ((S.shape[0] - 1) * 2) + 71) // 8 * 8
+    wide = torch.empty(S.shape[0] * ld, device="cuda", dtype=torch.bfloat16).view(S.shape[0], ld)
+    wide[:, :S.shape[1]] = S
+    res = []
+    for x, l in ((S, S.shape[1]), (wide, ld)):
+        out = torch.empty(M, N, device="cuda")
+        ops.gemm(x, B, M, N, K, out, lda=l, ldb=K, a_layout=layout)
+        res.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(res[0], res[1])
