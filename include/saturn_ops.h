@@ -139,7 +139,8 @@ sat_status sat_op_adamw(float* p, const float* g, float* m, float* v, void* shad
 
 /* Token embedding forward h[t] = wte[tok[t]] (+ wpe[t % S]) and its
  * deterministic backward dwte[v] = sum over t with tok[t] == v of dh[t] in
- * increasing t, written for every v < V (zero rows for absent tokens).  Past
+ * increasing t, written for every v < V (zero rows for absent tokens; a token
+ * outside [0, V) adds to no row of the backward).  Past
  * 16384 positions the sum is formed per chunk of 16384 positions, in order,
  * and the chunks' sums are added in order.
  * work: int32 scratch of min(T, 16384) entries.  Backward limit: V < 65536

@@ -117,8 +117,9 @@ __global__ void embed_fwd_kernel(const int32_t* __restrict__ tok, const float* _
   *reinterpret_cast<float4*>(h + (long)t * d + c) = v;
 }
 
-// Sorts the keys (token << 15 | position) of T <= 16384 tokens: a stable radix
-// sort by the token's low `bits` bits, four at a time, in LDS (one workgroup; the
+// Sorts the keys (token << 15 | position) of T <= 16384 tokens, every token outside
+// [0, V) as V, so that it belongs to no row: a stable radix
+// sort by the token's `bits` bits (those of V), four at a time, in LDS (one workgroup; the
 // positions start in order, so equal tokens keep theirs).  A thread owns
 // ceil(T / TH) consecutive keys and one column of 16 counters per pass; up to
 // 1024 tokens take one wave (64 tokens of 9 bits: 8.6 us with 1024 threads,
@@ -129,7 +130,7 @@ __global__ void embed_fwd_kernel(const int32_t* __restrict__ tok, const float* _
 constexpr int EMB_MAXT = 16384;
 template <int TH>
 __global__ __launch_bounds__(TH) void embed_sort_kernel(const int32_t* __restrict__ tok, int T,
-                                                        int32_t* __restrict__ sorted, int bits) {
+                                                        int32_t* __restrict__ sorted, int V, int bits) {
   constexpr int IMAX = 16;
   static_assert(IMAX * 1024 == EMB_MAXT, "keys per thread");
   __shared__ uint32_t key[IMAX * TH];
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(TH) void embed_sort_kernel(const int32_t* __restric
 #pragma unroll
   for (int j = 0; j < IMAX; ++j) {
     const int i = t * per + j;
-    k[j] = (j < per && i < T) ? (((uint32_t)tok[i] << 15) | (uint32_t)i) : 0xFFFFFFFFu;
+    k[j] = (j < per && i < T) ? (min((uint32_t)tok[i], (uint32_t)V) << 15 | (uint32_t)i) : 0xFFFFFFFFu;
   }
   const int mine = max(0, min(per, T - t * per));
   for (int shift = 15; shift < 15 + bits; shift += 4) {
@@ -693,14 +694,14 @@ hipError_t launch_embed_bwd(const int32_t* tok, const float* dh, float* dwte, in
                             int32_t* work, hipStream_t s) {
   if (T <= 0 || d % 4 || V <= 0 || V >= (1 << 16)) return hipErrorInvalidValue;
   int bits = 1;
-  while ((1 << bits) < V) ++bits;
+  while ((1 << bits) <= V) ++bits;
   const dim3 grid(sat_cdiv(V, EMB_ROWS), sat_cdiv(d, 1024));
   for (int t0 = 0; t0 < T; t0 += EMB_MAXT) {
     const int n = T - t0 < EMB_MAXT ? T - t0 : EMB_MAXT;
     if (n <= 1024)
-      hipLaunchKernelGGL(embed_sort_kernel<64>, dim3(1), dim3(64), 0, s, tok + t0, n, work, bits);
+      hipLaunchKernelGGL(embed_sort_kernel<64>, dim3(1), dim3(64), 0, s, tok + t0, n, work, V, bits);
     else
-      hipLaunchKernelGGL(embed_sort_kernel<1024>, dim3(1), dim3(1024), 0, s, tok + t0, n, work, bits);
+      hipLaunchKernelGGL(embed_sort_kernel<1024>, dim3(1), dim3(1024), 0, s, tok + t0, n, work, V, bits);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const float* dhc = dh + (long)t0 * d;

@@ -383,6 +383,24 @@ def test_embedding_bwd_skewed(T, d, V):
     assert np.array_equal(host(dw), ref)
 
 
+# Tokens outside [0, V) (a padding id, an id of a larger vocabulary, one whose low bits name a row)
+# belong to no row.  V a power of two, and not.
+@pytest.mark.parametrize("V", [256, 4096, 512, 1000])
+@pytest.mark.parametrize("T", [300, 3000])
+def test_embedding_bwd_tokens_out_of_range(T, V):
+    flush(f"embedding out of range T={T} V={V}")
+    rng = np.random.default_rng(T + V)
+    tok = rng.integers(0, V, T).astype(np.int32)
+    tok[::5] = np.resize(np.array([-1, V, V + 5, 8 * V + 5, (1 << 17) + 3, -(1 << 31)], np.int64), tok[::5].shape)
+    dh = rng.normal(size=(T, 8)).astype(np.float32)
+    dw = torch.full((V, 8), 7.0, device="cuda")
+    ops().embed_bwd(torch.as_tensor(tok).cuda(), to_dev_f32(dh), dw, T, 8, V)
+    ok = (tok >= 0) & (tok < V)
+    ref = np.zeros((V, 8), np.float32)
+    np.add.at(ref, tok[ok], dh[ok])
+    assert np.array_equal(host(dw), ref)
+
+
 def test_colsum():
     rng = np.random.default_rng(2)
     X = rng.normal(size=(1000, 333)).astype(np.float32)
