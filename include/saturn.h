@@ -198,8 +198,8 @@ sat_status sat_model_stats(const sat_model* m, int64_t* n_params, int64_t* n_tra
  *   model's stream sees the whole step.  Results are bitwise those with 0
  *   (the same kernels on the same operands).  Applies to models with a block
  *   weight whose AdamW step can be fused (SAT_OPT_FUSED_ADAMW: wide models,
- *   batch * seq_len % 8 == 0) and activations under 2 GiB each; the others' products run on the
- *   model's stream (otherwise ignored).
+ *   batch * seq_len % 8 == 0); narrower models run these products on the
+ *   model's stream whatever the option says.
  * value is 0 or 1; the setting applies from the next train step.
  * Errors: SAT_EINVAL (null model, unknown option or value), SAT_ESTATE. */
 typedef enum {

@@ -94,6 +94,10 @@ sat_status sat_side_ensure(sat_model* m) {
   return SAT_OK;
 }
 
+// For the tests, not declared in the headers: whether the model has run products on a
+// weight-gradient stream.
+extern "C" int sat_test_side_stream(const sat_model* m) { return m->side != nullptr; }
+
 extern "C" sat_status sat_model_create(const sat_config* cfg, void* arena, size_t arena_bytes,
                                        void* hip_stream, sat_model** out) {
   sat_status st = sat_validate_config(cfg);

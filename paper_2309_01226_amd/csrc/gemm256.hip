@@ -112,10 +112,12 @@ struct Loader {
       }
     }
   }
+  // rs: the operand at (tile row 0, k = 0) when K-contiguous, else at (tile row 0,
+  // k = k0): whole columns of k-rows may span more than a 32-bit offset.
   template <int I0 = 0, int I1 = NI>
-  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, int k0, int K, long ld, bf16* dst,
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rs, int k0, int K, bf16* dst,
                                         int wave) const {
-    const uint32_t so = LAY == LAY_K ? (uint32_t)(k0 * 2) : (uint32_t)((long)k0 * ld * 2);
+    const uint32_t so = LAY == LAY_K ? (uint32_t)(k0 * 2) : 0u;
 #pragma unroll
     for (int i = I0; i < I1; ++i) {
       const uint32_t o = (k0 + kof[i] < K) ? off[i] : OOB;
@@ -631,10 +633,15 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
 
-  __amdgpu_buffer_rsrc_t rsA = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.A + (AL == LAY_K ? (long)m0 * p.lda + kb : (long)kb * p.lda + m0)), (short)0, 0x7FFFFFFF, 0x00020000);
-  __amdgpu_buffer_rsrc_t rsB = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(p.B + (BL == LAY_K ? (long)n0 * p.ldb + kb : (long)kb * p.ldb + n0)), (short)0, 0x7FFFFFFF, 0x00020000);
+  // an operand's resource for the K-tile at k0 (K-contiguous: for all of them)
+  auto rsA = [&](int k0) {
+    const bf16* q = p.A + (AL == LAY_K ? (long)m0 * p.lda + kb : (long)(kb + k0) * p.lda + m0);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)q, (short)0, 0x7FFFFFFF, 0x00020000);
+  };
+  auto rsB = [&](int k0) {
+    const bf16* q = p.B + (BL == LAY_K ? (long)n0 * p.ldb + kb : (long)(kb + k0) * p.ldb + n0);
+    return __builtin_amdgcn_make_buffer_rsrc((void*)q, (short)0, 0x7FFFFFFF, 0x00020000);
+  };
   Loader<AL> la;
   Loader<BL> lb;
   la.init(p.lda, M - m0, wave);
@@ -658,12 +665,13 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
   // k offset of tile t; tiles past the last one copy zeros (every chunk at or past K)
   auto kof = [&](int t) { return t < nk ? t * BK : K; };
   // tile 0 resident; A_1 and the first half of B_1 in flight
-  la.issue(rsA, 0, K, p.lda, sA(0), wave);
-  lb.issue(rsB, 0, K, p.ldb, sB(0), wave);
+  la.issue(rsA(0), 0, K, sA(0), wave);
+  lb.issue(rsB(0), 0, K, sB(0), wave);
   wait_vm_lgkm0<0>();
   cta_barrier();
-  la.issue(rsA, kof(1), K, p.lda, sA(1), wave);
-  lb.template issue<0, 4>(rsB, kof(1), K, p.ldb, sB(1), wave);
+  la.issue(rsA(kof(1)), kof(1), K, sA(1), wave);
+  __amdgpu_buffer_rsrc_t rB1 = rsB(kof(1));  // of B_{t+1}
+  lb.template issue<0, 4>(rB1, kof(1), K, sB(1), wave);
   bf16x8 f0a[4], f0b[4], f1a[4], f1b[4];
 #pragma unroll
   for (int q = 0; q < 8; ++q) read_q(f0a, f0b, FA, FB, sA(0), sB(0), 0, q);
@@ -674,41 +682,43 @@ __global__ __launch_bounds__(NT, 1) void gemm256_kernel(GemmArgs p) {
     bf16* a2 = sA(t + 2);
     bf16* b2 = sB(t + 2);
     const int k1 = kof(t + 1), k2 = kof(t + 2);
+    const __amdgpu_buffer_rsrc_t rA2 = rsA(k2), rB2 = rsB(k2);
     __builtin_amdgcn_sched_barrier(0);
     kstep_ring(acc, f0a, f0b, f1a, f1b, FA, FB, a, b, 1, [&](int c) {
       switch (c) {
-        case 0: lb.template issue<4, 5>(rsB, k1, K, p.ldb, b1, wave); break;
-        case 1: lb.template issue<5, 6>(rsB, k1, K, p.ldb, b1, wave); break;
-        case 2: lb.template issue<6, 7>(rsB, k1, K, p.ldb, b1, wave); break;
-        default: lb.template issue<7, 8>(rsB, k1, K, p.ldb, b1, wave); break;
+        case 0: lb.template issue<4, 5>(rB1, k1, K, b1, wave); break;
+        case 1: lb.template issue<5, 6>(rB1, k1, K, b1, wave); break;
+        case 2: lb.template issue<6, 7>(rB1, k1, K, b1, wave); break;
+        default: lb.template issue<7, 8>(rB1, k1, K, b1, wave); break;
       }
     });
     kstep_ring(acc, f1a, f1b, f0a, f0b, FA, FB, a, b, 2, [&](int c) {
       switch (c) {
-        case 0: la.template issue<0, 1>(rsA, k2, K, p.lda, a2, wave); break;
-        case 1: la.template issue<1, 2>(rsA, k2, K, p.lda, a2, wave); break;
-        case 2: la.template issue<2, 3>(rsA, k2, K, p.lda, a2, wave); break;
-        default: la.template issue<3, 4>(rsA, k2, K, p.lda, a2, wave); break;
+        case 0: la.template issue<0, 1>(rA2, k2, K, a2, wave); break;
+        case 1: la.template issue<1, 2>(rA2, k2, K, a2, wave); break;
+        case 2: la.template issue<2, 3>(rA2, k2, K, a2, wave); break;
+        default: la.template issue<3, 4>(rA2, k2, K, a2, wave); break;
       }
     });
     kstep_ring(acc, f0a, f0b, f1a, f1b, FA, FB, a, b, 3, [&](int c) {
       switch (c) {
-        case 0: la.template issue<4, 5>(rsA, k2, K, p.lda, a2, wave); break;
-        case 1: la.template issue<5, 6>(rsA, k2, K, p.lda, a2, wave); break;
-        case 2: la.template issue<6, 7>(rsA, k2, K, p.lda, a2, wave); break;
-        default: la.template issue<7, 8>(rsA, k2, K, p.lda, a2, wave); break;
+        case 0: la.template issue<4, 5>(rA2, k2, K, a2, wave); break;
+        case 1: la.template issue<5, 6>(rA2, k2, K, a2, wave); break;
+        case 2: la.template issue<6, 7>(rA2, k2, K, a2, wave); break;
+        default: la.template issue<7, 8>(rA2, k2, K, a2, wave); break;
       }
     });
     wait_vm_lgkm0<NI>();  // A_{t+1}, B_{t+1} resident; reads of tile t done
     cta_barrier();                // ... in every wave: A_t's and B_t's slots are free
     kstep_ring(acc, f1a, f1b, f0a, f0b, FA, FB, sA(t + 1), b1, 0, [&](int c) {
       switch (c) {
-        case 0: lb.template issue<0, 1>(rsB, k2, K, p.ldb, b2, wave); break;
-        case 1: lb.template issue<1, 2>(rsB, k2, K, p.ldb, b2, wave); break;
-        case 2: lb.template issue<2, 3>(rsB, k2, K, p.ldb, b2, wave); break;
-        default: lb.template issue<3, 4>(rsB, k2, K, p.ldb, b2, wave); break;
+        case 0: lb.template issue<0, 1>(rB2, k2, K, b2, wave); break;
+        case 1: lb.template issue<1, 2>(rB2, k2, K, b2, wave); break;
+        case 2: lb.template issue<2, 3>(rB2, k2, K, b2, wave); break;
+        default: lb.template issue<3, 4>(rB2, k2, K, b2, wave); break;
       }
     });
+    rB1 = rB2;
   }
   wait_vm_lgkm0<0>();  // the zero-filling copies past the last tile
   __syncthreads();
@@ -778,13 +788,14 @@ bool gemm256_eligible(const GemmArgs& a, int alay, int blay, int epi) {
   }
   auto r8 = [](long x) { return (x + 7) / 8 * 8; };
   const long lim = 1L << 31;
-  // operands: 16-byte copies, 32-bit buffer offsets
+  // operands: 16-byte copies, 32-bit buffer offsets (of the whole row of K-contiguous
+  // operands, of a K-tile's 64 k-rows of M/N-contiguous ones)
   if (!al(a.A, 16) || !al(a.B, 16) || a.lda % 8 || a.ldb % 8) return false;
   if (alay == LAY_K ? (a.K % 8 || (long)BT * a.lda * 2 + 2L * a.K >= lim)
-                    : (a.lda < r8(a.M) || ((long)a.K + 256) * a.lda * 2 >= lim))
+                    : (a.lda < r8(a.M) || (long)BK * a.lda * 2 >= lim))
     return false;
   if (blay == LAY_K ? (a.K % 8 || (long)BT * a.ldb * 2 + 2L * a.K >= lim)
-                    : (a.ldb < r8(a.N) || ((long)a.K + 256) * a.ldb * 2 >= lim))
+                    : (a.ldb < r8(a.N) || (long)BK * a.ldb * 2 >= lim))
     return false;
   if (epi == EPI_ADAMW) {
     // operands of one layout; 4-column vectors of W and 8-row pieces of its

@@ -95,9 +95,7 @@ struct GemmArgs {
   // + n] (cdiv(M, R) rows; launch_colsum_partials then adds them in order).
   float* colsum_part;
   // Keeps launch_gemm from splitting the rows of a mostly empty last round
-  // (gemm_tail_split): a weight gradient whose AdamW step may instead be fused into
-  // this kernel's epilogue must sum in the same order either way (and with
-  // splitk_max 1, so that nothing else splits it).
+  // (gemm_tail_split): models that sum every row of a product in one order.
   int no_tail_split;
   ConvTaps cv;  // launch_gemm_conv only
 };

@@ -208,11 +208,12 @@ void sat_build_params(const sat_config& c, const Dims& D, std::vector<ParamDesc>
 
 namespace {
 
-// Whether the weight-gradient product of a [rows, cols] weight (K = k
-// token-contiguous rows) runs in the 256 x 256 kernel, so that its AdamW step
-// can be fused into the product's epilogue: enough tiles for every CU, whole
-// 8-column vectors, and the transposed copy in pieces of 8 rows.  The operand
-// and parameter sections are 256-byte aligned by construction.
+// Whether the AdamW step of a [rows, cols] weight is fused into the epilogue of its
+// weight-gradient product (over k tokens, in the 256 x 256 kernel): enough tiles for
+// every CU, whole 8-column vectors, and the transposed copy in pieces of 8 rows.
+// Token counts that are no multiple of 8 keep the separate pass (the row-major operands
+// themselves would allow them).  The operand and parameter sections are 256-byte
+// aligned by construction.
 bool fused_opt_ok(long rows, long cols, long trows, long k) {
   return k % 8 == 0 && cols % 8 == 0 && trows % 8 == 0 && trows >= rows &&
          ((rows + 255) / 256) * ((cols + 255) / 256) >= 256;
@@ -373,29 +374,8 @@ size_t carve(sat_model* M, char* base) {
   M->dh = c.take<float>(T * d);
   M->dA = c.take<float>(T * d);
   M->dout = c.take<bf16>(T * d);
-  bool fused_block = false, fused_head = false;
-  for (const auto& p : M->params) {
-    if (p.fused_opt && p.group >= 0) (p.group == D.L ? fused_head : fused_block) = true;
-  }
-  // a product on its row-major operands must stay below 2^31 bytes of each (buffer offsets)
-  auto too_long = [](long rows, long cols) { return (rows + 256L) * cols * 2 >= (1L << 31); };
-  const bool long_block = too_long(T, std::max<long>(std::max<long>(d, D.qkv_ld), m));
-  M->two_sets = fused_block && !long_block;
-  M->trans_blocks = T % 8 == 0 && fused_block && long_block;
-  M->trans_head = R % 8 == 0 && fused_head && too_long(R, std::max<long>(D.Vp, d));
-  {
-    long na = 0, nb = 0;
-    if (M->trans_blocks) {
-      na = std::max(na, (long)std::max<long>(std::max<long>(d, D.qkv_ld), m) * T);
-      nb = std::max(nb, std::max(d, m) * T);
-    }
-    if (M->trans_head) {
-      na = std::max(na, (long)D.Vp * R);
-      nb = std::max(nb, d * R);
-    }
-    M->tA = na > 0 ? c.take<bf16>(na) : nullptr;
-    M->tB = nb > 0 ? c.take<bf16>(nb) : nullptr;
-  }
+  M->two_sets = false;
+  for (const auto& p : M->params) M->two_sets = M->two_sets || (p.fused_opt && p.group >= 0 && p.group < D.L);
   // the blocks' gradients, and the side stream's split-K workspace
   for (int i = 0; i < 2; ++i) {
     WgradSet& W = M->wset[i];

@@ -171,13 +171,6 @@ struct sat_model {
   // activations 187.1 and 183.6; one block 12.29 and 12.25).  Narrower models use one
   // stream: 8 ViT-H blocks, copies and two streams 25.7 ms, neither 24.6.
   bool two_sets;
-  // Token-contiguous copies dY^T and X^T for the weight-gradient products whose
-  // row-major operands exceed 2^31 bytes (32-bit buffer offsets), on the model's
-  // stream, when the token count is a multiple of 8.
-  bf16* tA;
-  bf16* tB;
-  bool trans_blocks;  // tA / tB serve the blocks
-  bool trans_head;    // ... the head
   // split-K workspace of the fp32-output products with too few tiles
   float* splitk_ws;
   long splitk_ws_elems;

@@ -222,21 +222,15 @@ sat_status sat_run_forward(sat_model* M, const void* inputs, const int32_t* labe
   return SAT_OK;
 }
 
-// dW[Mr, N] = sum over the T rows of Y[t, m] X[t, n] (Y, X bf16 row-major).
-// With token-contiguous scratch (trans), both operands are first transposed
-// into it (ycols >= Mr: the transposed width of Y, a multiple of 8), so the
-// product reads K-contiguous operands; y_ready: tA already holds Y^T.  Without,
-// the product reads the row-major operands.
-// pidx: the weight's parameter index.  When its AdamW step is fused, the
-// product's epilogue applies the step to the weight (and writes the gradient
-// only if the model keeps gradients).
-// wgrad_run: the product on operands of layout `lay` (LAY_K: token-contiguous copies
-// [Mr, T] and [N, T]; LAY_MN: the row-major tensors), on stream st (the model's, or
-// the weight-gradient stream).
-static sat_status wgrad_run(sat_model* M, hipStream_t st, int lay, const bf16* y, long ldy, const bf16* x,
-                            long ldx, int Mr, int N, int T, int pidx, int tk = TK_ALL_GEMM) {
+// dW[Mr, N] = sum over the T rows of Y[t, m] X[t, n] (Y, X bf16 row-major, read where
+// they lie), on stream st (the model's, or the weight-gradient stream).  pidx: the
+// weight's parameter index.  When its AdamW step is fused, the product's epilogue
+// applies the step to the weight (and writes the gradient only if the model keeps
+// gradients).
+static sat_status wgrad(sat_model* M, hipStream_t st, const bf16* Y, long ldy, const bf16* X, long ldx,
+                        int Mr, int N, int T, int pidx, int tk = TK_ALL_GEMM) {
   const ParamDesc& P = M->params[pidx];
-  GemmArgs w = gargs(y, ldy, x, ldx, Mr, N, T, grad(M, pidx), P.cols);
+  GemmArgs w = gargs(Y, ldy, X, ldx, Mr, N, T, grad(M, pidx), P.cols);
   if (P.fused_opt) {
     if (M->opt_fused) {
       if (!M->opt_keep_grads) w.out = nullptr;
@@ -247,35 +241,18 @@ static sat_status wgrad_run(sat_model* M, hipStream_t st, int lay, const bf16* y
       w.opt_sht = M->shadow_t + P.toff;
       w.opt_trows = P.trows;
       w.opt_c = M->adamw_c;
-      if (!gemm256_eligible(w, lay, lay, EPI_ADAMW)) {
+      if (!gemm256_eligible(w, LAY_MN, LAY_MN, EPI_ADAMW)) {
         sat_set_error("internal: fused optimizer step of %s not eligible for the 256 x 256 kernel",
                       P.name.c_str());
         return SAT_EINVAL;
       }
-      return gemm(M, w, lay, lay, EPI_ADAMW, tk, st);
+      return gemm(M, w, LAY_MN, LAY_MN, EPI_ADAMW, tk, st);
     }
     // the same sums as the fused epilogue's (nothing split), so that the separate
     // AdamW pass gives the fused step's parameters
-    w.no_tail_split = 1;
     w.splitk_max = 1;
   }
-  if (lay == LAY_K) w.no_tail_split = 1;
-  return gemm(M, w, lay, lay, EPI_F32, tk, st);
-}
-static sat_status wgrad_t(sat_model* M, hipStream_t st, const bf16* yT, const bf16* xT, int Mr,
-                          int N, int T, int pidx, int tk = TK_ALL_GEMM) {
-  return wgrad_run(M, st, LAY_K, yT, T, xT, T, Mr, N, T, pidx, tk);
-}
-
-static sat_status wgrad(sat_model* M, hipStream_t st, bool trans, bool y_ready, const bf16* Y, long ldy,
-                        int ycols, const bf16* X, long ldx, int Mr, int N, int T, int pidx,
-                        int tk = TK_ALL_GEMM) {
-  if (trans) {
-    if (!y_ready) SAT_HIP(launch_transpose_bf16(Y, ldy, M->tA, T, T, ycols, st));
-    SAT_HIP(launch_transpose_bf16(X, ldx, M->tB, T, T, N, st));
-    return wgrad_t(M, st, M->tA, M->tB, Mr, N, T, pidx, tk);
-  }
-  return wgrad_run(M, st, LAY_MN, Y, ldy, X, ldx, Mr, N, T, pidx, tk);
+  return gemm(M, w, LAY_MN, LAY_MN, EPI_F32, tk, st);
 }
 
 // The fc1 bias gradient is the column sum of the fc2 input-gradient product's
@@ -375,7 +352,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
     // zero tail, so the extra products vanish and the 16-byte path applies.
     GemmArgs g = gargs(M->dz, D.Vp, shadow_t(M, hb + 2), D.Vp, R, d, D.Vp, M->dA, d);
     TRY(gemm(M, g, LAY_K, LAY_K, EPI_F32));
-    TRY(wgrad(M, s, M->trans_head, false, M->dz, D.Vp, D.Vp, M->f, d, D.V, d, R, hb + 2));
+    TRY(wgrad(M, s, M->dz, D.Vp, M->f, d, D.V, d, R, hb + 2));
     if (D.arch != SAT_GPT2)
       SAT_HIP(launch_colsum_bf16(M->dz, D.Vp, R, D.V, M->part, R < 256 ? R : 256,
                                  grad(M, hb + 3), s));
@@ -418,7 +395,6 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       if (ov) TRY(side_reuse(M, (l + 1) & 1));
       TRY(block_forward(M, l, true));
     }
-    const bool tr = M->trans_blocks;
     hipStream_t ws = ov ? M->side : s;  // of the weight-gradient products
     const LayerActs& A = sat_layer_acts(M, l);
     const int pb = block_base(M, l);
@@ -462,8 +438,8 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       GemmArgs go = gargs(W.dy1, d, shadow_t(M, pb + J_PROJW), d, T, d, d, M->dout, d);
       TRY(gemm(M, go, LAY_K, LAY_K, EPI_BF16));
       if (ov) TRY(side_fork(M));
-      TRY(wgrad(M, ws, tr, false, W.dy1, d, d, A.g, m, d, m, T, pb + J_FC2W));
-      TRY(wgrad(M, ws, tr, true, W.dy1, d, d, A.o, d, d, d, T, pb + J_PROJW));
+      TRY(wgrad(M, ws, W.dy1, d, A.g, m, d, m, T, pb + J_FC2W));
+      TRY(wgrad(M, ws, W.dy1, d, A.o, d, d, d, T, pb + J_PROJW));
       {
         Timed tm(M, TK_ATTN_BWD, attn_bwd_flops);
         SAT_HIP(launch_attention_bwd(ab, s));
@@ -473,8 +449,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
                           M->dA, d);
       TRY(gemm(M, ga, LAY_K, LAY_K, EPI_F32));
       if (ov) TRY(side_fork(M));
-      TRY(wgrad(M, ws, tr, false, W.qkv, D.qkv_ld, D.qkv_ld, A.a, d, D.qkv_ld, d, T, pb + J_QKVW,
-                TK_QKV_WGRAD));
+      TRY(wgrad(M, ws, W.qkv, D.qkv_ld, A.a, d, D.qkv_ld, d, T, pb + J_QKVW, TK_QKV_WGRAD));
       if (ov) TRY(side_done(M, l & 1));
       if (!fc1b_parts)
         SAT_HIP(launch_colsum_bf16(W.qkv + 3 * d, D.qkv_ld, T, m, M->part, npT,
@@ -496,8 +471,8 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       GemmArgs gc = gargs(W.du, m, shadow_t(M, pb + B_FC1W), m, T, d, m, M->dA, d);
       TRY(gemm(M, gc, LAY_K, LAY_K, EPI_F32));
       if (ov) TRY(side_fork(M));
-      TRY(wgrad(M, ws, tr, false, W.dy1, d, d, A.g, m, d, m, T, pb + B_FC2W));
-      TRY(wgrad(M, ws, tr, false, W.du, m, m, A.c, d, m, d, T, pb + B_FC1W));
+      TRY(wgrad(M, ws, W.dy1, d, A.g, m, d, m, T, pb + B_FC2W));
+      TRY(wgrad(M, ws, W.du, m, A.c, d, m, d, T, pb + B_FC1W));
       if (!fc1b_parts)
         SAT_HIP(launch_colsum_bf16(W.du, m, T, m, M->part, npT, grad(M, pb + B_FC1B), s));
       TRY(ln_bwd(M, M->dA, A.h_mid, 1, pb + B_LN2G, A.mean2, A.rstd2, T, W.dy2,
@@ -507,7 +482,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       GemmArgs go = gargs(W.dy2, d, shadow_t(M, pb + B_PROJW), d, T, d, d, M->dout, d);
       TRY(gemm(M, go, LAY_K, LAY_K, EPI_BF16));
       if (ov) TRY(side_fork(M));
-      TRY(wgrad(M, ws, tr, false, W.dy2, d, d, A.o, d, d, d, T, pb + B_PROJW));
+      TRY(wgrad(M, ws, W.dy2, d, A.o, d, d, d, T, pb + B_PROJW));
       {
         Timed tm(M, TK_ATTN_BWD, attn_bwd_flops);
         SAT_HIP(launch_attention_bwd(ab, s));
@@ -515,7 +490,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       GemmArgs ga = gargs(W.qkv, 3 * d, shadow_t(M, pb + B_QKVW), 3 * d, T, d, 3 * d, M->dA, d);
       TRY(gemm(M, ga, LAY_K, LAY_K, EPI_F32));
       if (ov) TRY(side_fork(M));
-      TRY(wgrad(M, ws, tr, false, W.qkv, 3 * d, 3 * d, A.a, d, 3 * d, d, T, pb + B_QKVW, TK_QKV_WGRAD));
+      TRY(wgrad(M, ws, W.qkv, 3 * d, A.a, d, 3 * d, d, T, pb + B_QKVW, TK_QKV_WGRAD));
       if (ov) TRY(side_done(M, l & 1));
       SAT_HIP(launch_colsum_bf16(W.qkv, 3 * d, T, 3 * d, M->part, npT, grad(M, pb + B_QKVB), s));
       if (ov && next_dy1) TRY(side_reuse(M, (l - 1) & 1));
@@ -533,16 +508,8 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
       SAT_HIP(hipMemcpyAsync(grad(M, 2), grad(M, 3), (size_t)d * 4, hipMemcpyDeviceToDevice, s));
       SAT_HIP(launch_vit_patch_grad(M->dh, M->dzpatch, D.B, D.np, d, s));
       const int rows = D.B * D.np;
-      if (M->trans_blocks && rows % 8 == 0 && d % 8 == 0) {
-        // a reduction over every patch of the batch into a 1280 x 588 weight: on
-        // token-contiguous copies it runs split-K over the whole chip
-        SAT_HIP(launch_transpose_bf16(M->dzpatch, d, M->tA, rows, rows, d, s));
-        SAT_HIP(launch_transpose_bf16(M->patches, D.pdp, M->tB, rows, rows, D.pdp, s));
-        TRY(wgrad_t(M, s, M->tA, M->tB, d, D.pd, rows, 0));
-      } else {
-        GemmArgs wp = gargs(M->dzpatch, d, M->patches, D.pdp, d, D.pd, rows, grad(M, 0), D.pd);
-        TRY(gemm(M, wp, LAY_MN, LAY_MN, EPI_F32));
-      }
+      GemmArgs wp = gargs(M->dzpatch, d, M->patches, D.pdp, d, D.pd, rows, grad(M, 0), D.pd);
+      TRY(gemm(M, wp, LAY_MN, LAY_MN, EPI_F32));
       SAT_HIP(launch_colsum_bf16(M->dzpatch, d, rows, d, M->part, rows < 256 ? rows : 256,
                                  grad(M, 1), s));
     } else {

@@ -334,3 +334,19 @@ def test_gemm_operand_spans_2gib(M, N, K, layout):
         res.append(out)
     torch.cuda.synchronize()
     assert torch.equal(res[0], res[1])
+
+
+def test_gemm_mn_operand_past_2gib():
+    """An M/N-contiguous operand of more than 2 GiB (21504 k-rows of 50264) in the 256 x 256 kernel:
+    sampled rows against fp64."""
+    from paper_2309_01226_amd import ops
+    M, N, K, lda = 16390, 4096, 21504, 50264
+    flush(f"gemm M/N-contiguous operand of {2 * K * lda} bytes")
+    g = torch.Generator("cuda").manual_seed(4)
+    A = torch.randn(K, lda, generator=g, device="cuda", dtype=torch.bfloat16)
+    B = torch.randn(K, N, generator=g, device="cuda", dtype=torch.bfloat16)
+    out = torch.empty(M, N, device="cuda")
+    ops.gemm(A, B, M, N, K, out, lda=lda, ldb=N, a_layout=1, b_layout=1)
+    rows = torch.tensor([0, 1, 255, 256, 8191, 16383, 16384, 16389], device="cuda")
+    ref = A[:, rows].double().t() @ B.double()
+    assert rel(host(out[rows]), host(ref)) < 2e-6

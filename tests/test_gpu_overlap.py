@@ -10,6 +10,8 @@ pass, and with two models stepping on their own streams at once.  Step
 parity against the oracle runs with the overlap on (tests/test_gpu_step.py
 and the others use the default)."""
 
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -45,6 +47,9 @@ CASES = {
     # every block weight's AdamW step fused into its weight-gradient product
     "gptj_fused": dict(arch="gptj", n_layers=2, d_model=2048, n_heads=8, d_mlp=8192, vocab=8200,
                        seq_len=2048, batch=2, rotary_dim=64, lr=1e-3),
+    # 75776 tokens: the q | k | v | fc1 gradients of a block are 2.2 GB
+    "gptj_long": dict(arch="gptj", n_layers=2, d_model=2048, n_heads=8, d_mlp=8192, vocab=64,
+                      seq_len=1024, batch=74, rotary_dim=16, lr=1e-3),
 }
 
 
@@ -57,6 +62,14 @@ def _pair(kw, extra=None):
         a.set_option(k, v)
         b.set_option(k, v)
     return a, b
+
+
+def _side(m):
+    """Whether the model has run products on its second stream."""
+    from paper_2309_01226_amd import _lib
+    f = _lib.lib().sat_test_side_stream
+    f.argtypes = [C.c_void_p]
+    return bool(f(m.h))
 
 
 def _same(a, b, what):
@@ -80,6 +93,8 @@ def test_overlap_bitwise_equal(name):
         x, y = device_batch(kw, seed=5, step=step)
         la, lb = a.train_step(x, y), b.train_step(x, y)
         assert la == lb, (name, step, la, lb)
+    if kw["d_model"] >= 2048:
+        assert _side(a) and not _side(b)
     _same(a, b, name)
     a.close()
     b.close()
