@@ -32,16 +32,16 @@ extern "C" {
  * n >= bias_col0 as bias[n - bias_col0].  gelu_erf: 0 tanh form, 1 erf form.
  * splitk_ws (fp32 device scratch of splitk_ws_elems elements, may be NULL):
  * with it, an epilogue-0/1 product on layout-0 operands that has fewer than
- * 256 output tiles of 256 x 256 and K >= 1024 runs split-K: K slices
- * write fp32 partials there, then one reduction adds them in slice
+ * 256 output tiles of 256 x 256 and K >= 1024 runs split-K: K slices of at
+ * least 512 write fp32 partials there, then one reduction adds them in slice
  * order with bias and residual (unless smaller tiles that fill the chip unsplit
- * are estimated faster).  An epilogue-0/1 product with a layout-1 operand and
- * K >= 1024 may split into slices of at least 512 in the same way.  Such a product with more than 256 tiles
+ * are estimated faster).  Such a product with more than 256 tiles
  * whose last round of 256 tiles would run mostly empty instead runs its
  * first rows (whole rounds) unsplit and only the remaining rows split-K,
  * when that is estimated faster.  Results then differ from the unsplit
  * product by summation order only.  The scratch is used only when it holds
- * slices * (split rows) * N elements; the call makes no allocation. */
+ * slices * (split rows) * N elements; the call makes no allocation.  No other
+ * product touches it. */
 typedef struct {
   const void* A;
   const void* B;
@@ -64,6 +64,10 @@ typedef struct {
   int64_t splitk_ws_elems;
 } sat_gemm_desc;
 sat_status sat_op_gemm(const sat_gemm_desc* d, void* stream);
+/* The same, and an epilogue-0/1 product with a layout-1 operand and K >= 1024 may
+ * use splitk_ws too, in slices of at least 512.  Calls that may overlap
+ * (different streams, or different host threads) need a splitk_ws each. */
+sat_status sat_op_gemm_splitk(const sat_gemm_desc* d, void* stream);
 
 /* sat_op_gemm for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops and harnesses that forbid hipMalloc.
@@ -75,7 +79,7 @@ sat_status sat_op_gemm(const sat_gemm_desc* d, void* stream);
  * nothing.  A product whose split-K partials would exceed the scratch is
  * rejected with SAT_EINVAL before any launch, except one that would split
  * only the rows of its last round: that runs unsplit, with the result of
- * sat_op_gemm without a workspace.  So does a product with a layout-1 operand.  All calls on one device share
+ * sat_op_gemm without a workspace.  All calls on one device share
  * that device's scratch: calls whose products split K and that may overlap
  * (different streams, or different host threads) race and must be ordered
  * by the caller. */

@@ -95,6 +95,7 @@ SIGNATURES = {
     "sat_profile_batch": (C.c_int, [C.POINTER(sat_config), _VP, _VP, _VP]),
     "sat_model_timing_read": (C.c_int, [_VP, C.POINTER(C.c_double), C.POINTER(C.c_int64), C.POINTER(C.c_double)]),
     "sat_op_gemm": (C.c_int, [C.POINTER(sat_gemm_desc), _VP]),
+    "sat_op_gemm_splitk": (C.c_int, [C.POINTER(sat_gemm_desc), _VP]),
     "sat_op_gemm_noalloc": (C.c_int, [C.POINTER(sat_gemm_desc), _VP]),
     "sat_op_layernorm_fwd": (C.c_int, [_VP, _I64, _I64, _VP, _VP, _VP, _I64, _VP, _VP, _I32, _I32, _F32, _VP]),
     "sat_op_layernorm_bwd": (C.c_int, [_VP, _I64, _VP, _I64, _I64, _VP, _VP, _VP, _VP, _I64, _VP, _VP, _VP,

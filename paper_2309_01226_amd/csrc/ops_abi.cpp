@@ -59,14 +59,24 @@ static sat_status gemm_args(const sat_gemm_desc* d, GemmArgs* out, const char* f
   return SAT_OK;
 }
 
-extern "C" sat_status sat_op_gemm(const sat_gemm_desc* d, void* stream) {
+static sat_status run_gemm(const sat_gemm_desc* d, bool any_layout, void* stream, const char* fn) {
   GemmArgs a;
-  sat_status st = gemm_args(d, &a, "sat_op_gemm");
+  sat_status st = gemm_args(d, &a, fn);
   if (st != SAT_OK) return st;
-  a.splitk_ws = d->splitk_ws;
-  a.splitk_ws_elems = d->splitk_ws ? d->splitk_ws_elems : 0;
+  if (d->splitk_ws && (any_layout || (d->a_layout == 0 && d->b_layout == 0))) {
+    a.splitk_ws = d->splitk_ws;
+    a.splitk_ws_elems = d->splitk_ws_elems;
+  }
   SAT_HIP(launch_gemm(a, d->a_layout, d->b_layout, d->epilogue, S(stream)));
   return SAT_OK;
+}
+
+extern "C" sat_status sat_op_gemm(const sat_gemm_desc* d, void* stream) {
+  return run_gemm(d, false, stream, "sat_op_gemm");
+}
+
+extern "C" sat_status sat_op_gemm_splitk(const sat_gemm_desc* d, void* stream) {
+  return run_gemm(d, true, stream, "sat_op_gemm_splitk");
 }
 
 // ---- sat_op_gemm_noalloc: the split-K workspace in a file-scope device array

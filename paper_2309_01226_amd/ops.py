@@ -61,10 +61,11 @@ def gemm(A, B, M, N, K, out, *, lda, ldb, a_layout=LAY_K, b_layout=LAY_K, epilog
          ldo=None, bias=None, bias_col0=0, resid=None, ldr=None, out2=None, ldo2=0, gelu_col0=0,
          aux=None, ldaux=0, gelu_erf=0, splitk_ws=None):
     """C[m, n] = sum_k A(m, k) B(n, k) with the chosen epilogue (see saturn_ops.h);
-    splitk_ws: optional fp32 scratch that lets a small fp32-output product run split-K."""
+    splitk_ws: optional fp32 scratch that lets a small fp32-output product of either layout run
+    split-K; calls that may overlap on different streams need one each."""
     d = _gemm_desc(A, B, M, N, K, out, lda, ldb, a_layout, b_layout, epilogue, ldo, bias, bias_col0,
                    resid, ldr, out2, ldo2, gelu_col0, aux, ldaux, gelu_erf, splitk_ws)
-    _lib.call("sat_op_gemm", C.byref(d), _stream())
+    _lib.call("sat_op_gemm_splitk", C.byref(d), _stream())
     return out
 
 

@@ -123,6 +123,7 @@ def test_op_argument_checks_make_no_launch():
     L = B.lib()
     d = B.sat_gemm_desc()
     assert L.sat_op_gemm(C.byref(d), None) == -1          # null operands
+    assert L.sat_op_gemm_splitk(C.byref(d), None) == -1
     assert L.sat_op_adamw(None, None, None, None, None, 0, 0, 0, 0, 0, 0, 1, None) == -1
     assert L.sat_op_attention_fwd(C.c_void_p(16), C.c_void_p(16), C.c_void_p(16), 8, 8, 8,
                                   C.c_void_p(16), 8, C.c_void_p(16), 1, 1, 4, 48, 1,

@@ -2,6 +2,8 @@
 over all operand layouts and epilogues, at shapes that span several tiles with
 ragged edges, and the unaligned (scalar-load) path."""
 
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -284,6 +286,28 @@ def test_gemm_splitk_mn_layouts(a_layout, b_layout):
     torch.cuda.synchronize()
     assert rel(host(out), R + O.gemm(A, B)) < 2e-6
     assert int(torch.isfinite(ws).sum().item()) >= 2 * M * N
+
+
+@pytest.mark.parametrize("a_layout,b_layout", [(0, 1), (1, 1), (1, 0)])
+def test_gemm_leaves_workspace_to_layout_0(a_layout, b_layout):
+    """sat_op_gemm itself splits only products on layout-0 operands: with a layout-1 operand the
+    workspace stays untouched and the result is the one without it (and of sat_op_gemm_noalloc)."""
+    from paper_2309_01226_amd import _lib, ops
+    M, N, K = 264, 392, 4168
+    flush(f"gemm workspace untouched lay=({a_layout},{b_layout})")
+    rng = np.random.default_rng(29)
+    A, B, Ad, Bd, lda, ldb = _operands(rng, M, N, K, a_layout, b_layout)
+    ws = torch.full((16 * M * N,), float("nan"), device="cuda", dtype=torch.float32)
+    outs = [torch.empty(M, N, device="cuda") for _ in range(3)]
+    for out, w in zip(outs, (ws, None)):
+        d = ops._gemm_desc(Ad, Bd, M, N, K, out, lda, ldb, a_layout, b_layout, 0, None, None, 0, None, None, None, 0,
+                           0, None, 0, 0, w)
+        _lib.call("sat_op_gemm", ctypes.byref(d), ops._stream())
+    ops.gemm_noalloc(Ad, Bd, M, N, K, outs[2], lda=lda, ldb=ldb, a_layout=a_layout, b_layout=b_layout)
+    torch.cuda.synchronize()
+    assert torch.isnan(ws).all()
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    assert rel(host(outs[0]), O.gemm(A, B)) < 2e-6
 
 
 # A residual / pre-activation whose rows of one tile span 2 GiB (and 4 GiB) or more: the same
