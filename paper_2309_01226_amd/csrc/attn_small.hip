@@ -769,15 +769,17 @@ bool attn_small_bwd_eligible(const AttnBwdArgs& a) {
          ok8(a.dk, a.lddk) && ok8(a.dv, a.lddv);
 }
 
-#define SMALL_LAUNCH(KERNEL, DH, args, f, fwd)                                                          \
+// One kernel of a head width: `three` also instantiates it for three waves (the forward).
+#define SMALL_LAUNCH(KERNEL, DH, args, f, three)                                                   \
   do {                                                                                             \
     const int BH_ = (f).B * (f).H, hx_ = (BH_ + 7) / 8;                                            \
-    const int nw_ = waves_per_wg((f).S, BH_, fwd);                                                      \
+    const int nw_ = waves_per_wg((f).S, BH_, three);                                               \
     const long nb_ = sat_cdiv((f).S, nw_ * WR);                                                    \
-    const int group_ = (int)std::max(1L, std::min((long)hx_, l2_group((f).causal) / (4L * (f).S * DH)));       \
+    const int group_ =                                                                             \
+        (int)std::max(1L, std::min((long)hx_, l2_group((f).causal) / (4L * (f).S * DH)));          \
     const dim3 grid_((unsigned)(nb_ * (BH_ < 64 ? BH_ : 8 * hx_)));                                \
     if (nw_ == 2) hipLaunchKernelGGL((KERNEL<DH, 2>), grid_, dim3(128), 0, s, args, group_);       \
-    else if (nw_ == 3) hipLaunchKernelGGL((KERNEL<DH, 3>), grid_, dim3(192), 0, s, args, group_);  \
+    else if (three && nw_ == 3) hipLaunchKernelGGL((KERNEL<DH, three ? 3 : 4>), grid_, dim3(192), 0, s, args, group_); \
     else hipLaunchKernelGGL((KERNEL<DH, 4>), grid_, dim3(256), 0, s, args, group_);                \
   } while (0)
 

@@ -759,7 +759,7 @@ hipError_t launch_l(const GemmArgs& a, int epi, hipStream_t s) {
     case EPI_BF16: return launch_e<AL, BL, EPI_BF16>(a, s);
     case EPI_DGELU_BF16: return launch_e<AL, BL, EPI_DGELU_BF16>(a, s);
     case EPI_ADAMW:
-      if constexpr (AL == BL) return launch_e<AL, BL, EPI_ADAMW>(a, s);
+      if constexpr (AL == LAY_MN && BL == LAY_MN) return launch_e<AL, BL, EPI_ADAMW>(a, s);
       break;
   }
   return hipErrorInvalidValue;
@@ -798,10 +798,10 @@ bool gemm256_eligible(const GemmArgs& a, int alay, int blay, int epi) {
                     : (a.ldb < r8(a.N) || (long)BK * a.ldb * 2 >= lim))
     return false;
   if (epi == EPI_ADAMW) {
-    // operands of one layout; 4-column vectors of W and 8-row pieces of its
-    // transposed copy; the gradient itself only if requested
+    // row-major operands (a weight gradient's); 4-column vectors of W and 8-row pieces
+    // of its transposed copy; the gradient itself only if requested
     auto a16 = [](const void* q) { return (reinterpret_cast<uintptr_t>(q) & 15) == 0; };
-    return alay == blay && a.N % 8 == 0 && a16(a.opt_p) && a16(a.opt_m) &&
+    return alay == LAY_MN && blay == LAY_MN && a.N % 8 == 0 && a16(a.opt_p) && a16(a.opt_m) &&
            a16(a.opt_v) && al(a.opt_sh, 8) && a16(a.opt_sht) && a.opt_trows % 8 == 0 &&
            a.opt_trows >= a.M && (a.out == nullptr || (a16(a.out) && a.ldo % 4 == 0));
   }
