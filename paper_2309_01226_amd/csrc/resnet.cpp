@@ -76,7 +76,8 @@ struct ResNetPlan {
   float* stem_act = nullptr;
   uint8_t* pool_arg = nullptr;
   bf16* stem_wpad = nullptr;
-  bf16* col = nullptr;
+  bf16* col = nullptr;  // im2col matrix of the stem and of the convolutions that are not gathered
+  long col_elems = 0;
   bf16* feat = nullptr;
   // backward workspace
   float* g0 = nullptr;
@@ -84,6 +85,7 @@ struct ResNetPlan {
   float* gdo = nullptr;
   float* da = nullptr;
   float* dcol = nullptr;
+  long dcol_elems = 0;
   float* dsub = nullptr;
   bf16* dc = nullptr;
   bf16* dcd = nullptr;
@@ -92,6 +94,33 @@ struct ResNetPlan {
 };
 
 namespace {
+
+enum Conv { CONV2, DOWN };  // a block's 3 x 3 convolution, its 1 x 1 projection
+enum ConvPass { FWD, DGRAD, WGRAD };
+
+// A convolution of block b with stride or window as a product that gathers its
+// operand instead of reading an im2col matrix: forward (A = its input, out), input
+// gradient (A = dY; 3 x 3 with stride 1 only) or weight gradient (A = dY, X = its
+// input).  False when the shapes need the im2col path.
+bool conv_args(const sat_model* M, const RBlock& b, Conv which, ConvPass pass, const bf16* A, const bf16* X,
+               float* out, GemmArgs* g) {
+  if (pass == DGRAD && (which != CONV2 || b.stride != 1)) return false;
+  const int w = which == CONV2 ? b.w2 : b.wd, k = which == CONV2 ? 3 : 1;
+  const int C = which == CONV2 ? b.mid : b.cin, cout = which == CONV2 ? b.mid : b.cout;
+  const ParamDesc& p = M->params[w];
+  GemmArgs& a = *g;
+  if (pass == FWD) {
+    a = gargs(A, 0, shadow(M, w), (long)k * k * C, (int)b.Pout, cout, k * k * C, out, cout);
+  } else if (pass == DGRAD) {
+    a = gargs(A, 0, shadow_t(M, w), p.trows, (int)b.Pin, C, k * k * cout, out, C);
+  } else {
+    a = gargs(A, cout, X, 0, cout, k * k * C, (int)b.Pout, out, k * k * C);
+  }
+  a.cv = pass == DGRAD ? ConvTaps{b.Ho, b.Wo, cout, b.H, b.W, k, 1, k / 2, -1, (long)C * p.trows}
+                       : ConvTaps{b.H, b.W, C, b.Ho, b.Wo, k, b.stride, -(k / 2), 1, C};
+  a.splitk_max = pass == WGRAD ? kSplitMax : 0;
+  return pass == WGRAD ? gemm_conv_wgrad_eligible(a) : gemm_conv_eligible(a);
+}
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -315,14 +344,21 @@ void sat_resnet_carve(sat_model* M, SatCarver& c) {
       n->rstd = c.take<float>(C);
     }
     maxPC = std::max({maxPC, b.Pin * b.mid, b.Pout * b.cout, b.Pout * b.cin});
-    col = std::max(col, b.Pout * 9L * b.mid);
-    dcol = std::max(dcol, b.Pout * 9L * b.mid);
-    if (b.stride != 1) col = std::max(col, b.Pout * (long)b.cin);
+    // im2col matrices of what is not gathered (the buffers are all aligned: null stands for them)
+    auto gathered = [&](Conv which, ConvPass pass) {
+      GemmArgs a;
+      return conv_args(M, b, which, pass, nullptr, nullptr, nullptr, &a);
+    };
+    if (!gathered(CONV2, FWD) || !gathered(CONV2, WGRAD)) col = std::max(col, b.Pout * 9L * b.mid);
+    if (!gathered(CONV2, DGRAD)) dcol = std::max(dcol, b.Pout * 9L * b.mid);
+    if (b.proj && b.stride != 1 && (!gathered(DOWN, FWD) || !gathered(DOWN, WGRAD)))
+      col = std::max(col, b.Pout * (long)b.cin);
     bnp(b.Pin, b.mid);
     bnp(b.Pout, b.mid);
     bnp(b.Pout, b.cout);
   }
   R.col = c.take<bf16>(col);
+  R.col_elems = col;
   R.feat = c.take<bf16>((long)R.N * R.F);
   // head
   M->logits = c.take<float>((long)R.N * R.Vp);
@@ -336,6 +372,7 @@ void sat_resnet_carve(sat_model* M, SatCarver& c) {
   R.da = c.take<float>(maxPC);
   R.dsub = c.take<float>(maxPC);
   R.dcol = c.take<float>(std::max(dcol, 8L));
+  R.dcol_elems = dcol;
   R.dc = c.take<bf16>(maxPC);
   R.dcd = c.take<bf16>(maxPC);
   R.dfeat = c.take<float>((long)R.N * R.F);
@@ -401,33 +438,14 @@ sat_status conv_gemm(sat_model* M, const bf16* A, long lda, int w, long P, int c
   return gemm(M, a, LAY_K, LAY_K, EPI_F32, tk);
 }
 
-enum Conv { CONV2, DOWN };  // a block's 3 x 3 convolution, its 1 x 1 projection
-
-// A convolution of block b with stride or window, gathered inside the product
-// instead of through an im2col matrix: forward (A = its input, out), input
-// gradient (A = dY; 3 x 3 with stride 1 only) or weight gradient (A = dY, X = its
-// input).  Returns false when the shapes need the im2col path.
-enum ConvPass { FWD, DGRAD, WGRAD };
+// Runs the convolution gathered inside its product; false when its shapes need the
+// im2col path.
 bool conv_gather(sat_model* M, const RBlock& b, Conv which, ConvPass pass, const bf16* A, const bf16* X, float* out,
                  sat_status* st) {
-  if (pass == DGRAD && (which != CONV2 || b.stride != 1)) return false;
-  const int w = which == CONV2 ? b.w2 : b.wd, k = which == CONV2 ? 3 : 1;
-  const int C = which == CONV2 ? b.mid : b.cin, cout = which == CONV2 ? b.mid : b.cout;
-  const ParamDesc& p = M->params[w];
   GemmArgs a;
-  if (pass == FWD) {
-    a = gargs(A, 0, shadow(M, w), (long)k * k * C, (int)b.Pout, cout, k * k * C, out, cout);
-  } else if (pass == DGRAD) {
-    a = gargs(A, 0, shadow_t(M, w), p.trows, (int)b.Pin, C, k * k * cout, out, C);
-  } else {
-    a = gargs(A, cout, X, 0, cout, k * k * C, (int)b.Pout, out, k * k * C);
-  }
-  a.cv = pass == DGRAD ? ConvTaps{b.Ho, b.Wo, cout, b.H, b.W, k, 1, k / 2, -1, (long)C * p.trows}
-                       : ConvTaps{b.H, b.W, C, b.Ho, b.Wo, k, b.stride, -(k / 2), 1, C};
-  a.splitk_max = pass == WGRAD ? kSplitMax : 0;
+  if (!conv_args(M, b, which, pass, A, X, out, &a)) return false;
   a.splitk_ws = M->splitk_ws;
   a.splitk_ws_elems = M->splitk_ws_elems;
-  if (pass == WGRAD ? !gemm_conv_wgrad_eligible(a) : !gemm_conv_eligible(a)) return false;
   Timed t(M, pass == FWD && which == CONV2 ? TK_QKV_FWD : TK_ALL_GEMM, 2.0 * a.M * a.N * (double)a.K);
   const hipError_t e = pass == WGRAD ? launch_gemm_conv_wgrad(a, M->stream) : launch_gemm_conv(a, M->stream);
   *st = SAT_OK;
@@ -436,6 +454,14 @@ bool conv_gather(sat_model* M, const RBlock& b, Conv which, ConvPass pass, const
     *st = SAT_EHIP;
   }
   return true;
+}
+
+// The im2col matrices of those that are not gathered: buffers sized for them by the
+// same rule (conv_args), checked again here.
+sat_status need_elems(long have, long want) {
+  if (want <= have) return SAT_OK;
+  sat_set_error("internal: im2col matrix of %ld elements in a buffer of %ld", want, have);
+  return SAT_EINVAL;
 }
 
 // Weight gradient [cout, ncols] = dY^T X over P pixels (dY [P, cout] bf16; X
@@ -491,6 +517,7 @@ sat_status sat_resnet_forward(sat_model* M, const void* inputs, const int32_t* l
                             b.a1, nullptr, s));
     sat_status st = SAT_OK;
     if (!conv_gather(M, b, CONV2, FWD, b.a1, nullptr, b.c2, &st)) {
+      TRY(need_elems(R.col_elems, b.Pout * 9L * b.mid));
       SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
                             s));
       TRY(conv_gemm(M, R.col, 9L * b.mid, b.w2, b.Pout, b.mid, 9 * b.mid, b.c2, TK_QKV_FWD));
@@ -505,6 +532,7 @@ sat_status sat_resnet_forward(sat_model* M, const void* inputs, const int32_t* l
       if (b.stride == 1) {
         TRY(conv_gemm(M, R.xb[i], b.cin, b.wd, b.Pout, b.cout, b.cin, b.cd));
       } else if (!conv_gather(M, b, DOWN, FWD, R.xb[i], nullptr, b.cd, &st)) {
+        TRY(need_elems(R.col_elems, b.Pout * b.cin));
         SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho,
                               b.Wo, s));
         TRY(conv_gemm(M, R.col, b.cin, b.wd, b.Pout, b.cout, b.cin, b.cd));
@@ -571,15 +599,17 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
     SAT_HIP(launch_bn_bwd(R.da, 1, b.a2, b.c2, b.n2.mean, b.n2.rstd, gam(M, b.n2), b.Pout, b.mid,
                           R.part, grad(M, b.n2.g), grad(M, b.n2.g + 1), R.dc, s));
     // conv2 (3 x 3, the block's stride): input gradient gathered from dY (stride 1)
-    // or through col2im, weight gradient against the im2col matrix of a1
+    // or through col2im, weight gradient on gathered a1 or its im2col matrix
     sat_status st = SAT_OK;
     if (!conv_gather(M, b, CONV2, DGRAD, R.dc, nullptr, R.da, &st)) {
+      TRY(need_elems(R.dcol_elems, b.Pout * 9L * b.mid));
       TRY(dgrad(M, R.dc, b.mid, b.w2, b.Pout, 9 * b.mid, R.dcol, nullptr));
       SAT_HIP(launch_col2im(R.dcol, 9L * b.mid, R.da, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo,
                             0, s));
     }
     TRY(st);
     if (!conv_gather(M, b, CONV2, WGRAD, R.dc, b.a1, grad(M, b.w2), &st)) {
+      TRY(need_elems(R.col_elems, b.Pout * 9L * b.mid));
       SAT_HIP(launch_im2col(b.a1, R.col, 9L * b.mid, R.N, b.H, b.W, b.mid, 3, b.stride, 1, b.Ho, b.Wo, s));
       TRY(rwgrad(M, R.dc, b.mid, R.col, 9L * b.mid, 9 * b.mid, b.Pout, grad(M, b.w2)));
     }
@@ -598,6 +628,7 @@ sat_status sat_resnet_backward(sat_model* M, const void* inputs) {
           SAT_HIP(launch_stride2_add(R.dsub, R.N, b.Ho, b.Wo, b.cin, b.H, b.W, dx, s));
         }
         if (!conv_gather(M, b, DOWN, WGRAD, R.dcd, R.xb[i], grad(M, b.wd), &st)) {
+          TRY(need_elems(R.col_elems, b.Pout * b.cin));
           SAT_HIP(launch_im2col(R.xb[i], R.col, b.cin, R.N, b.H, b.W, b.cin, 1, b.stride, 0, b.Ho, b.Wo, s));
           TRY(rwgrad(M, R.dcd, b.cout, R.col, b.cin, b.cin, b.Pout, grad(M, b.wd)));
         }
