@@ -974,6 +974,12 @@ int gemm_colsum_rows(const GemmArgs& a) {
   return p.bt / 2;
 }
 
+int gemm_planned_tile(const GemmArgs& a, int alay, int blay, int epi, int* slices) {
+  const GemmPlan p = gemm_plan(a, alay, blay, epi);
+  *slices = p.S;
+  return p.bt == 256 || tile_vec(a, alay, blay) ? p.bt : -p.bt;
+}
+
 hipError_t launch_gemm(const GemmArgs& a, int alay, int blay, int epi, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   if (a.K <= 0) return hipErrorInvalidValue;

@@ -115,6 +115,9 @@ hipError_t launch_gemm_conv_wgrad(const GemmArgs& a, hipStream_t s);
 // EPI_DGELU_BF16 product on K-contiguous operands: half the tile of the kernel
 // it runs (128, 64 or 32).
 int gemm_colsum_rows(const GemmArgs& a);
+// The tile (256, 128 or 64; negative: of the gather kernel) and the K slices that
+// launch_gemm would run this product on, unless it splits the rows of a last round.
+int gemm_planned_tile(const GemmArgs& a, int alay, int blay, int epi, int* slices);
 // The 256 x 256 four-stage kernel (gemm256.hip) for large aligned problems;
 // launch_gemm dispatches to it when gemm256_eligible holds.
 bool gemm256_eligible(const GemmArgs& a, int alay, int blay, int epi);

@@ -79,6 +79,16 @@ extern "C" sat_status sat_op_gemm_splitk(const sat_gemm_desc* d, void* stream) {
   return run_gemm(d, true, stream, "sat_op_gemm_splitk");
 }
 
+// For the tests, not declared in the headers: the tile and K slices of sat_op_gemm_splitk
+// for this descriptor (gemm_planned_tile); 0 for a refused one.  Launches nothing.
+extern "C" int sat_test_gemm_tile(const sat_gemm_desc* d, int* slices) {
+  GemmArgs a;
+  if (gemm_args(d, &a, "sat_test_gemm_tile") != SAT_OK) return 0;
+  a.splitk_ws = d->splitk_ws;
+  a.splitk_ws_elems = d->splitk_ws ? d->splitk_ws_elems : 0;
+  return gemm_planned_tile(a, d->a_layout, d->b_layout, d->epilogue, slices);
+}
+
 // ---- sat_op_gemm_noalloc: the split-K workspace in a file-scope device array
 //
 // `scratch` is a host-side stand-in for the array in host code: its device

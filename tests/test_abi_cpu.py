@@ -159,3 +159,29 @@ def test_no_inline_assembly():
     for f in sorted(os.listdir(csrc)):
         src = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(os.path.join(csrc, f)).read(), flags=re.S)
         assert not re.search(r"\b(?:__)?asm(?:__)?\b", src), f
+
+
+def test_gemm_tiles_by_size():
+    """The tile that each size of product runs on (no GPU: the rule sees sizes, types and
+    alignment only); the GPU tests of the kernels rely on the first five."""
+    L = _lib()
+
+    def tile(M, N, K, epi=0, lay=0, ws=0, lda=None):
+        lda = lda or (M if lay else K)
+        d = L.sat_gemm_desc(A=1 << 20, B=1 << 20, M=M, N=N, K=K, lda=lda, ldb=N if lay else K, a_layout=lay,
+                            b_layout=lay, epilogue=epi, out=1 << 20, ldo=N, resid=1 << 20, ldr=N, aux=1 << 20, ldaux=N,
+                            splitk_ws=1 << 20 if ws else None, splitk_ws_elems=ws)
+        s = C.c_int()
+        return L.lib().sat_test_gemm_tile(C.byref(d), C.byref(s)), s.value
+
+    assert tile(2000, 2048, 512, epi=3) == (128, 1)   # test_gpu_step's gpt2_colsum64
+    assert tile(80, 256, 64, epi=3) == (64, 1)
+    assert tile(264, 392, 4168, epi=1, lay=1, ws=16 * 264 * 392)[0] == 64
+    assert tile(1000, 1288, 4168, epi=1, lay=1, ws=16 * 1000 * 1288)[0] == 128
+    assert tile(16390, 4096, 21504, lay=1, lda=50264)[0] == 256
+    assert tile(4096, 28672, 4096, epi=2) == (256, 1)
+    assert tile(64, 64, 63) == (-64, 1)               # K no multiple of 8: gathered
+    assert tile(64, 64, 64, lda=1 << 23) == (-64, 1)  # 128 rows span 2 GiB
+    assert tile(64, 64, 64, lda=(1 << 23) - 8) == (64, 1)
+    # no workspace, or one that is too small: unsplit
+    assert tile(1000, 1288, 4168, lay=1)[1] == 1 and tile(1000, 1288, 4168, lay=1, ws=1000)[1] == 1

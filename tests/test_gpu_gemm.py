@@ -9,7 +9,7 @@ import pytest
 import torch
 
 from oracle import ops as O
-from tests.gpu_util import bf16_round, flush, host, rel, to_dev_bf16, to_dev_f32
+from tests.gpu_util import bf16_round, flush, gemm_on, host, rel, to_dev_bf16, to_dev_f32
 
 pytestmark = pytest.mark.gpu
 
@@ -94,13 +94,15 @@ def test_gemm_epilogues(erf_form):
 
 @pytest.mark.parametrize("a_layout,b_layout", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("epi", [0, 1, 2, 3])
-def test_gemm_large_tiles_sampled(a_layout, b_layout, epi):
-    """Shapes large enough for the 256 x 256 four-stage path (>= 256 tiles),
-    with ragged M and N edges and a K tail, every epilogue; checked on 300
-    sampled rows (always including the last) against float64."""
-    from paper_2309_01226_amd import ops
-    M, N, K = 4100, 4104, 584
-    flush(f"gemm large lay=({a_layout},{b_layout}) epi={epi}")
+@pytest.mark.parametrize("M,N,K", [(4100, 4104, 584), (4104, 7944, 584)])
+def test_gemm_large_tiles_sampled(M, N, K, a_layout, b_layout, epi):
+    """Shapes of more than 256 tiles of 256 x 256, with ragged M and N edges and a K tail,
+    every epilogue: the 256 x 256 kernel, except that the smaller one's fp32 outputs (17 x 17
+    tiles, a last round of 33) run on 128 x 128, and its M-contiguous A (4100 is no
+    multiple of 8) in the gather kernel; checked on 300 sampled rows (always including
+    the last) against float64."""
+    flush(f"gemm large M={M} N={N} lay=({a_layout},{b_layout}) epi={epi}")
+    tile = 256 if N == 7944 else -128 if a_layout == 1 else 128 if epi < 2 else 256
     rng = np.random.default_rng(17 + a_layout + 2 * b_layout + 4 * epi)
     A, B, Ad, Bd, lda, ldb = _operands(rng, M, N, K, a_layout, b_layout)
     bias = rng.normal(size=N - 8)
@@ -112,19 +114,19 @@ def test_gemm_large_tiles_sampled(a_layout, b_layout, epi):
     kw = dict(lda=lda, ldb=ldb, a_layout=a_layout, b_layout=b_layout, epilogue=epi)
     if epi == 0:
         out = torch.empty(M, N, device="cuda", dtype=torch.float32)
-        ops.gemm(Ad, Bd, M, N, K, out, bias=to_dev_f32(bias), bias_col0=8, **kw)
+        gemm_on(tile, Ad, Bd, M, N, K, out, bias=to_dev_f32(bias), bias_col0=8, **kw)
         torch.cuda.synchronize()
         assert rel(host(out)[rows], pre) < 2e-6
     elif epi == 1:
         R = rng.normal(size=(M, N)).astype(np.float32)
         out = to_dev_f32(R)
-        ops.gemm(Ad, Bd, M, N, K, out, resid=out, bias=to_dev_f32(bias), bias_col0=8, **kw)
+        gemm_on(tile, Ad, Bd, M, N, K, out, resid=out, bias=to_dev_f32(bias), bias_col0=8, **kw)
         torch.cuda.synchronize()
         assert rel(host(out)[rows], R[rows] + pre) < 2e-6
     elif epi == 2:
         o1 = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
         o2 = torch.empty(M, N - 512, device="cuda", dtype=torch.bfloat16)
-        ops.gemm(Ad, Bd, M, N, K, o1, bias=to_dev_f32(bias), bias_col0=8, out2=o2, ldo2=N - 512,
+        gemm_on(tile, Ad, Bd, M, N, K, o1, bias=to_dev_f32(bias), bias_col0=8, out2=o2, ldo2=N - 512,
                  gelu_col0=512, **kw)
         torch.cuda.synchronize()
         assert rel(host(o1)[rows], pre) < 4e-3
@@ -132,7 +134,7 @@ def test_gemm_large_tiles_sampled(a_layout, b_layout, epi):
     else:
         U = bf16_round(rng.normal(size=(M, N)))
         o3 = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
-        ops.gemm(Ad, Bd, M, N, K, o3, aux=to_dev_bf16(U), ldaux=N, gelu_erf=1, **kw)
+        gemm_on(tile, Ad, Bd, M, N, K, o3, aux=to_dev_bf16(U), ldaux=N, gelu_erf=1, **kw)
         torch.cuda.synchronize()
         assert rel(host(o3)[rows], C * O.gelu_grad(U[rows], 1)) < 4e-3
 
@@ -222,14 +224,14 @@ def test_gemm_tail_split(M, N, K, resid):
 # tiles in M and N, a K tail, rows whose 4-column vectors are aligned and rows
 # where they are not (N odd, so every layout but (0, 0) is gathered), every
 # layout and epilogue.
-TILES = [(3001, 1288, 712), (1285, 520, 200), (2100, 1301, 328)]
+TILES = [(3001, 1288, 712, 64), (1285, 520, 200, 64), (2100, 1301, 328, 64), (3001, 2301, 1096, 128),
+         (1285, 5160, 1096, 128)]
 
 
 @pytest.mark.parametrize("a_layout,b_layout", [(0, 0), (0, 1), (1, 1), (1, 0)])
 @pytest.mark.parametrize("epi", [0, 1, 2, 3])
-@pytest.mark.parametrize("M,N,K", TILES)
-def test_gemm_tile_kernels(M, N, K, epi, a_layout, b_layout):
-    from paper_2309_01226_amd import ops
+@pytest.mark.parametrize("M,N,K,tile", TILES)
+def test_gemm_tile_kernels(M, N, K, tile, epi, a_layout, b_layout):
     flush(f"gemm tiles lay=({a_layout},{b_layout}) epi={epi} M={M} N={N} K={K}")
     rng = np.random.default_rng(M + epi + 4 * a_layout + 8 * b_layout)
     A = bf16_round(rng.normal(size=(M, K)))
@@ -252,37 +254,36 @@ def test_gemm_tile_kernels(M, N, K, epi, a_layout, b_layout):
     if epi < 2:
         R = rng.normal(size=(M, N)).astype(np.float32)
         out = to_dev_f32(R)
-        ops.gemm(Ad, Bd, M, N, K, out, resid=out if epi else None, bias=to_dev_f32(bias), bias_col0=8, **kw)
+        gemm_on(tile, Ad, Bd, M, N, K, out, resid=out if epi else None, bias=to_dev_f32(bias), bias_col0=8, **kw)
         torch.cuda.synchronize()
         assert rel(host(out), pre + (R if epi else 0.0)) < 2e-6
     elif epi == 2:
         o1 = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
         o2 = torch.empty(M, N - 72, device="cuda", dtype=torch.bfloat16)
-        ops.gemm(Ad, Bd, M, N, K, o1, bias=to_dev_f32(bias), bias_col0=8, out2=o2, ldo2=N - 72, gelu_col0=72, **kw)
+        gemm_on(tile, Ad, Bd, M, N, K, o1, bias=to_dev_f32(bias), bias_col0=8, out2=o2, ldo2=N - 72, gelu_col0=72, **kw)
         torch.cuda.synchronize()
         assert rel(host(o1), pre) < 4e-3
         assert rel(host(o2), O.gelu(pre[:, 72:], 0)) < 4e-3
     else:
         U = bf16_round(rng.normal(size=(M, N)))
         o3 = torch.empty(M, N, device="cuda", dtype=torch.bfloat16)
-        ops.gemm(Ad, Bd, M, N, K, o3, aux=to_dev_bf16(U), ldaux=N, gelu_erf=1, **kw)
+        gemm_on(tile, Ad, Bd, M, N, K, o3, aux=to_dev_bf16(U), ldaux=N, gelu_erf=1, **kw)
         torch.cuda.synchronize()
         assert rel(host(o3), C * O.gelu_grad(U, 1)) < 4e-3
 
 
 @pytest.mark.parametrize("a_layout,b_layout", [(0, 1), (1, 1), (1, 0)])
-def test_gemm_splitk_mn_layouts(a_layout, b_layout):
+@pytest.mark.parametrize("M,N,K,tile", [(264, 392, 4168, 64), (1000, 1288, 4168, 128)])
+def test_gemm_splitk_mn_layouts(M, N, K, tile, a_layout, b_layout):
     """An M/N-contiguous operand with a workspace: K slices, the last one short."""
-    from paper_2309_01226_amd import ops
-    M, N, K = 264, 392, 4168
-    flush(f"gemm split-K lay=({a_layout},{b_layout})")
+    flush(f"gemm split-K M={M} N={N} lay=({a_layout},{b_layout})")
     rng = np.random.default_rng(23)
     A, B, Ad, Bd, lda, ldb = _operands(rng, M, N, K, a_layout, b_layout)
     R = rng.normal(size=(M, N)).astype(np.float32)
     ws = torch.full((16 * M * N,), float("nan"), device="cuda", dtype=torch.float32)
     out = to_dev_f32(R)
-    ops.gemm(Ad, Bd, M, N, K, out, lda=lda, ldb=ldb, a_layout=a_layout, b_layout=b_layout, epilogue=1, resid=out,
-             splitk_ws=ws)
+    gemm_on(tile, Ad, Bd, M, N, K, out, lda=lda, ldb=ldb, a_layout=a_layout, b_layout=b_layout, epilogue=1, resid=out,
+            splitk_ws=ws)
     torch.cuda.synchronize()
     assert rel(host(out), R + O.gemm(A, B)) < 2e-6
     assert int(torch.isfinite(ws).sum().item()) >= 2 * M * N
@@ -312,11 +313,10 @@ def test_gemm_leaves_workspace_to_layout_0(a_layout, b_layout):
 
 # A residual / pre-activation whose rows of one tile span 2 GiB (and 4 GiB) or more: the same
 # result as from a compact one, with 128 x 128 tiles and with 64 x 64.
-@pytest.mark.parametrize("M,N,K", [(128, 25600, 4096), (64, 64, 64)])
+@pytest.mark.parametrize("M,N,K,tile", [(128, 25600, 4096, 128), (64, 64, 64, 64)])
 @pytest.mark.parametrize("epi", [1, 3])
 @pytest.mark.parametrize("span", [1, 2])
-def test_gemm_epilogue_operand_spans_2gib(M, N, K, epi, span):
-    from paper_2309_01226_amd import ops
+def test_gemm_epilogue_operand_spans_2gib(M, N, K, tile, epi, span):
     flush(f"gemm epilogue operand past 2 GiB M={M} N={N} K={K} epi={epi} span={span}")
     g = torch.Generator("cuda").manual_seed(M + epi)
     A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
@@ -330,7 +330,7 @@ def test_gemm_epilogue_operand_spans_2gib(M, N, K, epi, span):
     for x, l in ((X, N), (wide, ld)):
         out = torch.empty(M, N, device="cuda", dtype=dt)
         kw = dict(resid=x, ldr=l) if epi == 1 else dict(aux=x, ldaux=l)
-        ops.gemm(A, B, M, N, K, out, lda=K, ldb=K, epilogue=epi, **kw)
+        gemm_on(tile, A, B, M, N, K, out, lda=K, ldb=K, epilogue=epi, **kw)
         res.append(out)
     torch.cuda.synchronize()
     assert torch.equal(res[0], res[1])
@@ -340,10 +340,9 @@ def test_gemm_epilogue_operand_spans_2gib(M, N, K, epi, span):
 @pytest.mark.parametrize("M,N,K", [(128, 25600, 4096), (64, 64, 64)])
 @pytest.mark.parametrize("layout", [0, 1])
 def test_gemm_operand_spans_2gib(M, N, K, layout):
-    from paper_2309_01226_amd import ops
-    flush(f"gemm operand past 2 GiB M={M} N={N} K={K} layout={layout}")
     if layout == 1:
         K = 64
+    flush(f"gemm operand past 2 GiB M={M} N={N} K={K} layout={layout}")
     g = torch.Generator("cuda").manual_seed(M + layout)
     A = torch.randn(M, K, generator=g, device="cuda").bfloat16()
     B = torch.randn(N, K, generator=g, device="cuda").bfloat16()
@@ -354,7 +353,7 @@ def test_gemm_operand_spans_2gib(M, N, K, layout):
     res = []
     for x, l in ((S, S.shape[1]), (wide, ld)):
         out = torch.empty(M, N, device="cuda")
-        ops.gemm(x, B, M, N, K, out, lda=l, ldb=K, a_layout=layout)
+        gemm_on(M if x is S else -M, x, B, M, N, K, out, lda=l, ldb=K, a_layout=layout)
         res.append(out)
     torch.cuda.synchronize()
     assert torch.equal(res[0], res[1])
@@ -363,14 +362,13 @@ def test_gemm_operand_spans_2gib(M, N, K, layout):
 def test_gemm_mn_operand_past_2gib():
     """An M/N-contiguous operand of more than 2 GiB (21504 k-rows of 50264) in the 256 x 256 kernel:
     sampled rows against fp64."""
-    from paper_2309_01226_amd import ops
     M, N, K, lda = 16390, 4096, 21504, 50264
     flush(f"gemm M/N-contiguous operand of {2 * K * lda} bytes")
     g = torch.Generator("cuda").manual_seed(4)
     A = torch.randn(K, lda, generator=g, device="cuda", dtype=torch.bfloat16)
     B = torch.randn(K, N, generator=g, device="cuda", dtype=torch.bfloat16)
     out = torch.empty(M, N, device="cuda")
-    ops.gemm(A, B, M, N, K, out, lda=lda, ldb=N, a_layout=1, b_layout=1)
+    gemm_on(256, A, B, M, N, K, out, lda=lda, ldb=N, a_layout=1, b_layout=1)
     rows = torch.tensor([0, 1, 255, 256, 8191, 16383, 16384, 16389], device="cuda")
     ref = A[:, rows].double().t() @ B.double()
     assert rel(host(out[rows]), host(ref)) < 2e-6

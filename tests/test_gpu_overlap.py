@@ -1,14 +1,14 @@
 """The blocks' weight-gradient products on the library's second stream
 (SAT_OPT_OVERLAP_WGRAD, the default) give bitwise the results of running
 every launch on the model's stream: same kernels on the same operands, only
-the order in which independent launches run differs.  Checked over several
-steps on every architecture, with a frozen prefix, with activation
-checkpointing, with split-K weight-gradient products (their own workspace on
-the second stream), with the AdamW step fused into the products (the GPT-J
-layer at full width: every block weight fused) and with it in the separate
-pass, and with two models stepping on their own streams at once.  Step
-parity against the oracle runs with the overlap on (tests/test_gpu_step.py
-and the others use the default)."""
+the order in which independent launches run differs.  Models wide enough for a
+fused block weight use that stream (asserted); checked over several steps with
+a frozen prefix, with activation checkpointing, with split-K weight-gradient
+products (their own workspace on the second stream), with the AdamW step fused
+into the products and with it in the separate pass, and with models
+stepping on their own streams at once.  The narrow cases have one
+stream whatever the option says (asserted too): there it must change
+nothing.  Step parity against the oracle runs with the default."""
 
 import ctypes as C
 
@@ -93,14 +93,13 @@ def test_overlap_bitwise_equal(name):
         x, y = device_batch(kw, seed=5, step=step)
         la, lb = a.train_step(x, y), b.train_step(x, y)
         assert la == lb, (name, step, la, lb)
-    if kw["d_model"] >= 2048:
-        assert _side(a) and not _side(b)
+    assert _side(a) == (kw["d_model"] >= 2048) and not _side(b)
     _same(a, b, name)
     a.close()
     b.close()
 
 
-@pytest.mark.parametrize("name", ["gptj", "gpt2_splitk", "gpt2_wide"])
+@pytest.mark.parametrize("name", ["gptj", "gpt2_splitk", "gpt2_wide", "gptj_wide_ckpt", "gptj_wide_deep"])
 def test_overlap_gradients_and_separate_adamw(name):
     """Kept gradients (fused step) and the separate AdamW pass: gradients and
     parameters bitwise equal with and without the second stream."""
@@ -112,6 +111,7 @@ def test_overlap_gradients_and_separate_adamw(name):
         for step in range(2):
             x, y = device_batch(kw, seed=8, step=step)
             assert a.train_step(x, y) == b.train_step(x, y)
+        assert _side(a) == (kw["d_model"] >= 2048) and not _side(b)
         ga, gb = a.grads(), b.grads()
         for n in ga:
             assert np.array_equal(ga[n], gb[n]), (name, extra, "grad", n)

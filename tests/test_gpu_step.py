@@ -42,8 +42,7 @@ CASES = {
                        seq_len=40, batch=2, rotary_dim=16, lr=1e-3),
     "small_vit": dict(arch="vit", n_layers=2, d_model=160, n_heads=2, d_mlp=320, vocab=10,
                       img_size=28, patch=14, channels=3, batch=4, lr=1e-3),
-    # 40 tokens and 32 patches: the weight-gradient products (and the patch
-    # weight's, over 588 values per patch) on token-contiguous copies
+    # 40 tokens and 32 patches, the patch weight's gradient over 588 values per patch
     "small_vit_b8": dict(arch="vit", n_layers=2, d_model=160, n_heads=2, d_mlp=320, vocab=10,
                          img_size=28, patch=14, channels=3, batch=8, lr=1e-3),
     "tiny_gpt2_k1": dict(arch="gpt2", n_layers=3, d_model=64, n_heads=4, d_mlp=256, vocab=512,
@@ -54,6 +53,10 @@ CASES = {
     # fc1 input gradient and the fc2 forward (K = 1024) run split-K
     "gpt2_splitk": dict(arch="gpt2", n_layers=2, d_model=256, n_heads=4, d_mlp=1024, vocab=512,
                         seq_len=1024, batch=2, lr=1e-3),
+    # 2000 tokens: the fc1 bias gradient from the column sums of 64-row blocks (the 128 x 128 kernel's
+    # GELU' epilogue, a ragged last tile; the narrower models' come from 32-row blocks)
+    "gpt2_colsum64": dict(arch="gpt2", n_layers=1, d_model=512, n_heads=8, d_mlp=2048, vocab=300,
+                          seq_len=100, batch=20, lr=1e-3),
     # 18432 tokens: the token embedding's backward sums two chunks of positions
     "gpt2_long_t": dict(arch="gpt2", n_layers=1, d_model=128, n_heads=2, d_mlp=256, vocab=300,
                         seq_len=256, batch=72, lr=1e-3),
