@@ -310,7 +310,7 @@ static sat_status ln_bwd(sat_model* M, const float* dy, const float* x, long row
   float* pbb = M->part + (size_t)np_ * d;
   float* po = dbias ? M->part + (size_t)2 * np_ * d : nullptr;
   {
-    Timed tm(M, TK_LN_BWD, ln_bwd_bytes(rows, d, true));
+    Timed tm(M, TK_LN_BWD, ln_bwd_bytes(rows, d, out_bf != nullptr));
     SAT_HIP(launch_layernorm_bwd(dy, d, x, d, row_stride, master(M, gidx), mean, rstd, M->dh, d, pg,
                                  pbb, rows, d, np_, M->stream, out_bf, d, po));
   }
