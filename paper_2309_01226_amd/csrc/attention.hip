@@ -20,8 +20,8 @@
 //
 // This file serves head dims 16, 32 (first-generation kernels, whose output
 // may be split into head-dim slices) and the calls of 128 that attn_small.hip does
-// not take: outputs aligned to less than 8 bytes, a scale <= 0 (the pipelined *_fast
-// kernels); head dims 64, 80 and all other calls of 128 run in attn_small.hip and 256
+// not take: outputs aligned to less than 8 bytes, a scale <= 0, dQ written over Q or dO
+// (the pipelined *_fast kernels); head dims 64, 80 and all other calls of 128 run in attn_small.hip and 256
 // in attn256.hip.
 #include "common.h"
 #include "kernels.h"

@@ -49,7 +49,7 @@ __global__ void im2col8_kernel(const bf16* __restrict__ x, bf16* __restrict__ co
 }
 
 // The im2col matrix transposed, colT[(a k + b) C + c, p] (row stride ldt >=
-// P = N Ho Wo), which the weight-gradient product reads token-contiguous:
+// P = N Ho Wo), a K-contiguous operand for a weight-gradient product:
 // im2col and the transpose in one pass.  A lane gathers eight consecutive
 // output pixels' 16-byte pieces (8 channels of one tap, zeros outside the
 // image), transposes the 8 x 8 block with byte permutes (element j of pixels

@@ -82,8 +82,9 @@ struct GemmArgs {
   int splitk_kc;
   long split_stride;
   // Optional caller-owned fp32 workspace of splitk_ws_elems elements; with it,
-  // launch_gemm runs fp32-output products that have too few 256 x 256 tiles
-  // to fill the chip as split-K plus a reduction (gemm_splitk below).
+  // launch_gemm may run an fp32-output product as K slices plus a reduction: on
+  // K-contiguous operands one with too few 256 x 256 tiles to fill the chip
+  // (gemm_splitk below), on others one that the planner estimates faster so.
   float* splitk_ws;
   long splitk_ws_elems;
   // Most K slices the split-K plan may use (0: 16; 1: none).  Products with very few
@@ -209,8 +210,8 @@ hipError_t launch_attention_bwd(const AttnBwdArgs& a, hipStream_t s);
 bool attn256_bwd_eligible(const AttnBwdArgs& a);
 hipError_t launch_attn256_bwd_dkdv(const AttnBwdArgs& a, hipStream_t s);
 hipError_t launch_attn256_bwd_dq(const AttnBwdArgs& a, hipStream_t s);
-// 64-, 80- and 128-wide heads (attn_small.hip): forward, and dK / dV then dQ after
-// launch_attention_bwd has computed delta.
+// 64-, 80- and 128-wide heads (attn_small.hip): forward; dQ (which also writes delta),
+// then dK / dV.
 bool attn_small_fwd_eligible(const AttnArgs& a);
 bool attn_small_bwd_eligible(const AttnBwdArgs& a);
 hipError_t launch_attn_small_fwd(const AttnArgs& a, hipStream_t s);
@@ -301,7 +302,8 @@ hipError_t launch_sum_rows_batched(const float* dh, float* out, int B, int S, in
 hipError_t launch_im2col(const bf16* x, bf16* col, long ldc, int N, int H, int W, int C, int k,
                          int s, int pad, int Ho, int Wo, hipStream_t st);
 // The same matrix transposed, colT [k k C, N Ho Wo] (row stride ldt): the
-// token-contiguous operand of a convolution's weight-gradient product.
+// K-contiguous operand for a convolution's weight-gradient product (the entry point only:
+// the ResNet step reads its operands row-major).
 // C % 8 == 0, N Ho Wo % 8 == 0, ldt % 8 == 0, 16-byte aligned.
 hipError_t launch_im2col_t(const bf16* x, bf16* colT, long ldt, int N, int H, int W, int C, int k,
                            int s, int pad, int Ho, int Wo, hipStream_t st);
