@@ -660,6 +660,9 @@ def main():
                             "fwd_tflops": diag["attn_fwd"][2] / max(diag["attn_fwd"][0], 1e-9) / 1e9,
                             "bwd_tflops": diag["attn_bwd"][2] / max(diag["attn_bwd"][0], 1e-9) / 1e9}
     ncols = 3 * kw.get("d_model", 0) + kw.get("d_mlp", 0) if kw["arch"] == "gptj" else 3 * kw.get("d_model", 0)
+    qkv = "fused QKV + fc1" if kw["arch"] == "gptj" else "QKV"
+    # the shape that the committed counter summaries were taken on
+    profiled = not resnet and (m.rows(), ncols, kw["d_model"]) == (4096, 28672, 4096)
     if w_n and resnet:
         achieved = w_fl / w_n / (w_ms / w_n * 1e-3) / 1e12
         out["roofline"] = {
@@ -670,19 +673,20 @@ def main():
             "launches": w_n, "avg_ms": w_ms / w_n, "flop_per_launch": w_fl / w_n,
         }
     elif w_n:
-        fused = not args.separate_adamw
+        # the library fuses the AdamW step of a weight with at least 256 tiles of 256 x 256
+        tiles = -(-ncols // 256) * -(-kw["d_model"] // 256)
+        fused = not args.separate_adamw and tiles >= 256 and m.rows() % 8 == 0
         achieved = w_fl / w_n / (w_ms / w_n * 1e-3) / 1e12
         opt_bytes = 28.0 * ncols * kw["d_model"] if fused else 0.0
         serial_us = (w_fl / w_n / (PEAK_BF16_TFLOPS * 1e12) + opt_bytes / (PEAK_HBM_GBS * 1e9)) * 1e6
         out["roofline"] = {
-            "kernel": (f"gemm256_kernel<1, 1, 4, 0> (AdamW epilogue): weight gradient of the fused QKV + fc1 weight "
+            "kernel": (f"gemm256_kernel<1, 1, 4, 0> (AdamW epilogue): weight gradient of the {qkv} weight "
                        f"({ncols} x {kw['d_model']} x {m.rows()} tokens) with that weight's AdamW step"
                        if fused else
-                       f"gemm256_kernel<1, 1, 0, 0>: weight gradient of the fused QKV + fc1 weight "
-                       f"({ncols} x {kw['d_model']} x {m.rows()} tokens)"),
+                       f"weight gradient of the {qkv} weight ({ncols} x {kw['d_model']} x {m.rows()} tokens)"),
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS,
-            "traffic": traffic_from_profiles("gemm_qkv_wgrad_adamw_gptj_traffic.txt") if fused else None,
+            "traffic": traffic_from_profiles("gemm_qkv_wgrad_adamw_gptj_traffic.txt") if fused and profiled else None,
             "launches": w_n, "avg_ms": w_ms / w_n, "flop_per_launch": w_fl / w_n,
             "optimizer_bytes_per_launch": opt_bytes,
             "optimizer_bytes_per_element": 28 if fused else 0,
@@ -703,11 +707,11 @@ def main():
     if q_n:
         achieved = q_fl / q_n / (q_ms / q_n * 1e-3) / 1e12
         out["roofline_qkv_fwd"] = {
-            "kernel": "gemm256_kernel<0, 0, 2, 0> (bf16 epilogue, GELU on the fc1 columns): fused QKV + fc1 forward "
-                      f"({m.rows()} x {ncols} x {kw['d_model']})",
+            "kernel": ("gemm256_kernel<0, 0, 2, 0> (bf16 epilogue, GELU on the fc1 columns): " if profiled else "") +
+                      f"{qkv} forward ({m.rows()} x {ncols} x {kw['d_model']})",
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS,
-            "traffic": traffic_from_profiles("gemm_qkv_fc1_fwd_gptj_traffic.txt"),
+            "traffic": traffic_from_profiles("gemm_qkv_fc1_fwd_gptj_traffic.txt") if profiled else None,
             "launches": q_n, "avg_ms": q_ms / q_n, "flop_per_launch": q_fl / q_n,
         }
     if "seq_len" in kw:  # token workloads: LayerNorm and vocabulary cross-entropy shapes
