@@ -188,7 +188,9 @@ sat_status sat_model_stats(const sat_model* m, int64_t* n_params, int64_t* n_tra
  *   AdamW pass after the backward.
  * SAT_OPT_KEEP_GRADS (default 0): 1 also writes the gradients of those
  *   weights to the gradient arena, so that sat_grad_read returns them.
- * SAT_OPT_OVERLAP_WGRAD (default 1): the blocks' weight-gradient products
+ * SAT_OPT_OVERLAP_WGRAD (default 1 for models with a block weight whose AdamW
+ *   step can be fused (wide models, batch * seq_len % 8 == 0), 0 for narrower
+ *   ones): the blocks' weight-gradient products
  *   (with the AdamW steps fused into them) run on a second stream that the
  *   library creates on the first such backward (default priority; destroyed
  *   with the model), beside the input-gradient chain of the
@@ -196,10 +198,8 @@ sat_status sat_model_stats(const sat_model* m, int64_t* n_params, int64_t* n_tra
  *   alternating sets, and the step joins that stream back into the model's
  *   stream before the backward ends, so a caller that synchronizes the
  *   model's stream sees the whole step.  Results are bitwise those with 0
- *   (the same kernels on the same operands).  Applies to models with a block
- *   weight whose AdamW step can be fused (SAT_OPT_FUSED_ADAMW: wide models,
- *   batch * seq_len % 8 == 0); narrower models run these products on the
- *   model's stream whatever the option says.
+ *   (the same kernels on the same operands).  The ResNet has one stream
+ *   whatever the option says.
  * value is 0 or 1; the setting applies from the next train step.
  * Errors: SAT_EINVAL (null model, unknown option or value), SAT_ESTATE. */
 typedef enum {

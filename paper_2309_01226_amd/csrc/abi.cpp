@@ -121,12 +121,12 @@ extern "C" sat_status sat_model_create(const sat_config* cfg, void* arena, size_
   m->timing_used = 0;
   m->opt_fused = true;
   m->opt_keep_grads = false;
-  m->opt_overlap = true;
   m->tail_split = cfg->arch != SAT_RESNET;
   m->last_step_fused = false;
   m->last_step_kept = false;
   hipGetDevice(&m->device);
   size_t need = sat_model_layout(m, nullptr);
+  m->opt_overlap = m->overlap_default;
   if (arena == nullptr) {
     hipError_t e = hipMalloc(&m->arena, need);
     if (e != hipSuccess) {

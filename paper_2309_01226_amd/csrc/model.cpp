@@ -374,17 +374,13 @@ size_t carve(sat_model* M, char* base) {
   M->dh = c.take<float>(T * d);
   M->dA = c.take<float>(T * d);
   M->dout = c.take<bf16>(T * d);
-  M->two_sets = false;
-  for (const auto& p : M->params) M->two_sets = M->two_sets || (p.fused_opt && p.group >= 0 && p.group < D.L);
+  M->overlap_default = false;
+  for (const auto& p : M->params)
+    if (p.fused_opt && p.group >= 0 && p.group < D.L) M->overlap_default = true;
   // the blocks' gradients, and the side stream's split-K workspace
-  for (int i = 0; i < 2; ++i) {
-    WgradSet& W = M->wset[i];
-    if (i == 1 && !M->two_sets) {
-      W = M->wset[0];
-      break;
-    }
+  for (WgradSet& W : M->wset) {
     W.dy1 = c.take<bf16>(T * d);
-    W.dy2 = gptj ? nullptr : M->two_sets ? c.take<bf16>(T * d) : W.dy1;  // on one stream dy1 is read before
+    W.dy2 = gptj ? nullptr : c.take<bf16>(T * d);
     W.du = gptj ? nullptr : c.take<bf16>(T * m);
     W.qkv = c.take<bf16>(T * D.qkv_ld);
   }

@@ -101,8 +101,8 @@ struct sat_model {
   hipEvent_t ev_done[2];  // side -> model stream: set i may be rewritten
   hipEvent_t ev_join;     // side -> model stream: every product done
   bool side_pending[2];
-  bool opt_overlap;
-  WgradSet wset[2];  // block l's is wset[l % 2]; one set twice without the weight-gradient stream
+  bool opt_overlap;      // initially overlap_default
+  WgradSet wset[2];  // block l's is wset[l % 2]
   float* splitk_ws2;      // split-K workspace of the side stream
   int device;
   char* arena;
@@ -161,20 +161,21 @@ struct sat_model {
   float* dh;
   float* dA;
   bf16* dout;
-  // Models with a block weight whose AdamW step is fused into its weight-gradient product
-  // (fused_opt: at least 256 tiles of 256 x 256) run the blocks' weight-gradient
-  // products on the second stream, with two sets of gradients, so that one block's
-  // products run beside the next one's chain.  All products read row-major tensors:
-  // through the kernels' transposing LDS reads they cost at most 6 % more than
-  // token-contiguous copies would let them, and the copies cost more than that (28 GPT-J
-  // blocks on two streams: with copies 160.1 ms per step, without 158.5; recomputing
-  // activations 187.1 and 183.6).
-  // Narrower models use one stream.  That was decided when two streams meant copies
-  // (8 ViT-H blocks 25.7 ms, one stream without copies 24.6).  Two streams without copies, one
-  // stream beside them: GPT-2-small 12.56 and 13.32 ms, GPT-2-medium half frozen 11.59 and 11.93, 8
-  // ViT-H blocks 23.2 and 23.8, the 8-member grid 144.5 and 145.0, but the tiny decoder 0.28 and
-  // 0.23 (events and forks): the rule is not the best one for the wider of these.
-  bool two_sets;
+  // Whether the blocks' weight-gradient products run on the second stream unless the
+  // caller says otherwise (SAT_OPT_OVERLAP_WGRAD): models with a block weight whose
+  // AdamW step is fused into its product (fused_opt: at least 256 tiles of 256 x 256).
+  // Two sets of gradients let one block's products run beside the next one's chain.  All
+  // products read row-major tensors: through the kernels' transposing LDS reads they
+  // cost at most 6 % more than token-contiguous copies would let them, and the copies
+  // cost more than that (28 GPT-J blocks on two streams: with copies 160.1 ms per step,
+  // without 158.5; recomputing activations 187.1 and 183.6).
+  // Narrower models default to one stream.  That was decided when two streams meant
+  // copies (8 ViT-H blocks 25.7 ms, one stream without copies 24.6).  Two streams without
+  // copies, one stream beside them: GPT-2-small 12.56 and 13.32 ms, GPT-2-medium half frozen
+  // 11.59 and 11.93, 8 ViT-H blocks 23.2 and 23.8, the 8-member grid 144.5 and 145.0, but the
+  // tiny decoder 0.28 and 0.23 (events and forks): a caller of the wider of these gains by
+  // setting the option.
+  bool overlap_default;
   // split-K workspace of the fp32-output products with too few tiles
   float* splitk_ws;
   long splitk_ws_elems;

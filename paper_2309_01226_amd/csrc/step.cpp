@@ -386,7 +386,7 @@ sat_status sat_run_backward(sat_model* M, const void* inputs) {
   // (AdamW-fused) weight-gradient product.  Block l's last LayerNorm writes the first
   // tensor of the other set: before it, block l + 1's products are waited for,
   // under checkpointing before the recomputation that rewrites the activations they read.
-  const bool ov = M->opt_overlap && M->two_sets && D.k < D.L;
+  const bool ov = M->opt_overlap && D.k < D.L;
   if (ov) TRY(sat_side_ensure(M));
   for (int l = D.L - 1; l >= D.k; --l) {
     const WgradSet& W = M->wset[l & 1];

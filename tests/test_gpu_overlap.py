@@ -1,14 +1,14 @@
 """The blocks' weight-gradient products on the library's second stream
-(SAT_OPT_OVERLAP_WGRAD, the default) give bitwise the results of running
+(SAT_OPT_OVERLAP_WGRAD) give bitwise the results of running
 every launch on the model's stream: same kernels on the same operands, only
-the order in which independent launches run differs.  Models wide enough for a
-fused block weight use that stream (asserted); checked over several steps with
-a frozen prefix, with activation checkpointing, with split-K weight-gradient
-products (their own workspace on the second stream), with the AdamW step fused
-into the products and with it in the separate pass, and with models
-stepping on their own streams at once.  The narrow cases have one
-stream whatever the option says (asserted too): there it must change
-nothing.  Step parity against the oracle runs with the default."""
+the order in which independent launches run differs.  Checked over several
+steps on every architecture, with a frozen prefix, with activation
+checkpointing, with split-K weight-gradient products (their own workspace on
+the second stream), with the AdamW step fused into the products and with it
+in the separate pass, and with models stepping on their own streams at once;
+every case asserts that the second stream was used, and by default only by models
+wide enough for a fused block weight.  Step parity against the oracle runs
+with the default (tests/test_gpu_step.py and the others)."""
 
 import ctypes as C
 
@@ -93,7 +93,7 @@ def test_overlap_bitwise_equal(name):
         x, y = device_batch(kw, seed=5, step=step)
         la, lb = a.train_step(x, y), b.train_step(x, y)
         assert la == lb, (name, step, la, lb)
-    assert _side(a) == (kw["d_model"] >= 2048) and not _side(b)
+    assert _side(a) and not _side(b)
     _same(a, b, name)
     a.close()
     b.close()
@@ -111,7 +111,7 @@ def test_overlap_gradients_and_separate_adamw(name):
         for step in range(2):
             x, y = device_batch(kw, seed=8, step=step)
             assert a.train_step(x, y) == b.train_step(x, y)
-        assert _side(a) == (kw["d_model"] >= 2048) and not _side(b)
+        assert _side(a) and not _side(b)
         ga, gb = a.grads(), b.grads()
         for n in ga:
             assert np.array_equal(ga[n], gb[n]), (name, extra, "grad", n)
@@ -127,6 +127,8 @@ def test_overlap_two_models_on_their_own_streams():
     kws = [CASES["gptj_wide_ckpt"], dict(CASES["gpt2"], lr=3e-4), CASES["gpt2_wide"]]
     streams = [torch.cuda.Stream() for _ in kws]
     conc = [Model(kw, stream=s) for kw, s in zip(kws, streams)]
+    for m in conc:
+        m.set_option("overlap_wgrad", 1)
     ser = [Model(kw) for kw in kws]
     for m in ser:
         m.set_option("overlap_wgrad", 0)
@@ -142,3 +144,15 @@ def test_overlap_two_models_on_their_own_streams():
         _same(c, s, "two models")
         c.close()
         s.close()
+
+
+@pytest.mark.parametrize("name", ["gpt2", "gptj", "vit", "gpt2_wide", "gptj_wide_ckpt"])
+def test_overlap_default(name):
+    """Unless set, the option is on for wide models only."""
+    from paper_2309_01226_amd.model import Model, device_batch
+    kw = CASES[name]
+    flush(f"overlap default: {name}")
+    m = Model(kw)
+    m.train_step(*device_batch(kw, seed=5, step=0))
+    assert _side(m) == (kw["d_model"] >= 2048)
+    m.close()
